@@ -743,53 +743,24 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     for (double v : sd)
         if (!(v > 0.0) || !isfinite(v)) return fail(MALA_E_INVALID_ARG, "input std must be positive");
 
-    // padded shape for the precision: K multiple of the MFMA K (4 or 32)
+    // unit tiles of 16; a layer's K runs in steps of 32 units and one of 16 for an odd tile count
     const bool bf = precision == MALA_PREC_BF16;
     auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
-    const int KK = bf ? 32 : 4;
-    // fp32 batches 4 K-steps (16 units): input padded to a multiple of 16
-    const int in_pad = bf ? 32 * ceil_div(n_in, 32) : 16 * ceil_div(n_in, 16);
-    const int h1t = bf ? 2 * ceil_div(h1, 32) : ceil_div(h1, 16);
-    const int h2t = bf ? 2 * ceil_div(h2, 32) : ceil_div(h2, 16);
-    const int ot = ceil_div(n_out, 16);
-    const int KS1 = in_pad / KK, KS2 = h1t * 16 / KK, KS3 = h2t * 16 / KK;
-    // A operand of MFMA tile (mt, s): lane l holds row 16 mt + l%16 and, for
-    // bf16, k = 32 s + 8 (l/16) + q, q < 8; for fp32 the K order that makes
-    // four consecutive K-steps contiguous per lane: k = 16 (s/4) + 4 (l/16) + s%4.
-    auto pack = [&](const std::vector<double>& W, int fout, int fin, int mtiles, int ks, std::vector<float>& o) {
-        const int per = KK / 4;
-        o.assign((size_t)mtiles * ks * 64 * per, 0.f);
-        for (int mt = 0; mt < mtiles; ++mt)
-            for (int s = 0; s < ks; ++s)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int q = 0; q < per; ++q) {
-                        const int row = 16 * mt + (lane & 15);
-                        const int k = bf ? 32 * s + 8 * (lane >> 4) + q
-                                         : 16 * (s / 4) + 4 * (lane >> 4) + (s % 4);
-                        float v = 0.f;
-                        if (row < fout && k < fin) v = (float)W[(size_t)row * fin + k];
-                        o[(((size_t)mt * ks + s) * 64 + lane) * per + q] = v;
-                    }
+    const int in_t = ceil_div(n_in, 16), in_pad = 16 * in_t;
+    const int h1t = ceil_div(h1, 16), h2t = ceil_div(h2, 16), ot = ceil_div(n_out, 16);
+    // FP32 weights are split into two FP16 planes, v = hi + lo, after a
+    // power-of-two scale that brings the layer's largest weight to [2^14, 2^15)
+    auto scale_exponent = [](const std::vector<double>& W) {
+        float m = 0.f;
+        for (double v : W)
+            if (isfinite((float)v)) m = std::max(m, fabsf((float)v));
+        return m > 0.f ? std::min(14 - ilogbf(m), 100) : 0;
     };
-    std::vector<float> P1, P2, P3;
-    pack(W1, h1, n_in, h1t, KS1, P1);
-    pack(W2, h2, h1, h2t, KS2, P2);
-    pack(W3, n_out, h2, ot, KS3, P3);
-    // transposed weights for the network's vector-Jacobian product (FP32
-    // only): W^T is [in][out] row-major, packed like a layer with the widths
-    // swapped; its K runs over the padded output units of the forward layer
-    auto transpose = [](const std::vector<double>& W, int fout, int fin) {
-        std::vector<double> t((size_t)fin * fout);
-        for (int o = 0; o < fout; ++o)
-            for (int i = 0; i < fin; ++i) t[(size_t)i * fout + o] = W[(size_t)o * fin + i];
-        return t;
-    };
-    std::vector<float> T1, T2, T3;
-    if (!bf) {
-        pack(transpose(W1, h1, n_in), n_in, h1, in_pad / 16, h1t * 16 / KK, T1);
-        pack(transpose(W2, h2, h1), h1, h2, h1t, h2t * 16 / KK, T2);
-        pack(transpose(W3, n_out, h2), h2, n_out, h2t, ot * 16 / KK, T3);
-    }
+    const int we[3] = {bf ? 0 : scale_exponent(W1), bf ? 0 : scale_exponent(W2), bf ? 0 : scale_exponent(W3)};
+    std::vector<float> raw;                 // the three layers in FP32, packed on the device
+    raw.reserve(W1.size() + W2.size() + W3.size());
+    for (const std::vector<double>* W : {&W1, &W2, &W3})
+        for (double v : *W) raw.push_back((float)v);
     auto padv = [](const std::vector<double>& v, int n) {
         std::vector<float> o(n, 0.f);
         for (size_t i = 0; i < v.size() && (int)i < n; ++i) o[i] = (float)v[i];
@@ -809,32 +780,32 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
         if (hipMemcpy(d, v.data(), sizeof(float) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return nullptr;
         return d;
     };
-    auto upload_bf = [&](const std::vector<float>& v) -> void* {
-        std::vector<uint16_t> h(v.size());
-        for (size_t i = 0; i < v.size(); ++i) {   // round to nearest even
-            uint32_t x;
-            memcpy(&x, &v[i], 4);
-            const uint32_t lsb = (x >> 16) & 1u;
-            h[i] = (uint16_t)((x + 0x7FFFu + lsb) >> 16);
-        }
+    // packed A operands of one layer, or of its transpose (for the network's
+    // vector-Jacobian product, FP32 only: its K runs over the padded output units)
+    float* raw_d = static_cast<float*>(upload_f(raw));
+    const int planes = bf ? 1 : 2;
+    auto pack = [&](size_t off, int fout, int fin, bool transposed, int mtiles, int kt, int wexp) -> void* {
         void* d = nullptr;
-        if (hipMalloc(&d, sizeof(uint16_t) * (h.size() ? h.size() : 1)) != hipSuccess) return nullptr;
+        if (!raw_d || hipMalloc(&d, sizeof(uint16_t) * packed_weight_elems(mtiles, kt, planes)) != hipSuccess) return nullptr;
         w->allocs.push_back(d);
-        if (hipMemcpy(d, h.data(), sizeof(uint16_t) * h.size(), hipMemcpyHostToDevice) != hipSuccess) return nullptr;
+        if (launch_pack_weights(nullptr, raw_d + off, fout, fin, transposed, mtiles, kt, planes, wexp, d) != hipSuccess)
+            return nullptr;
         return d;
     };
+    const size_t o2 = W1.size(), o3 = W1.size() + W2.size();
     MlpArgs& a = w->args;
     a.precision = bf ? 1 : 0;
     a.n_in = n_in; a.n_h1 = h1; a.n_h2 = h2; a.n_out = n_out;
     a.in_pad = in_pad; a.h1_tiles = h1t; a.h2_tiles = h2t; a.out_tiles = ot;
     a.slope = (float)slope;
     a.out_act = out_act ? 1 : 0;
-    a.W1 = bf ? upload_bf(P1) : upload_f(P1);
-    a.W2 = bf ? upload_bf(P2) : upload_f(P2);
-    a.W3 = bf ? upload_bf(P3) : upload_f(P3);
-    a.W1T = bf ? nullptr : upload_f(T1);
-    a.W2T = bf ? nullptr : upload_f(T2);
-    a.W3T = bf ? nullptr : upload_f(T3);
+    for (int l = 0; l < 3; ++l) a.wexp[l] = we[l];
+    a.W1 = pack(0, h1, n_in, false, h1t, in_t, we[0]);
+    a.W2 = pack(o2, h2, h1, false, h2t, h1t, we[1]);
+    a.W3 = pack(o3, n_out, h2, false, ot, h2t, we[2]);
+    a.W1T = bf ? nullptr : pack(0, h1, n_in, true, in_t, h1t, we[0]);
+    a.W2T = bf ? nullptr : pack(o2, h2, h1, true, h1t, h2t, we[1]);
+    a.W3T = bf ? nullptr : pack(o3, n_out, h2, true, h2t, ot, we[2]);
     a.b1 = (const float*)upload_f(pb1);
     a.b2 = (const float*)upload_f(pb2);
     a.b3 = (const float*)upload_f(pb3);
@@ -843,10 +814,13 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     a.out_scale = (const float*)upload_f(psc);
     a.out_shift = (const float*)upload_f(psh);
     if (!a.W1 || !a.W2 || !a.W3 || (!bf && (!a.W1T || !a.W2T || !a.W3T)) || !a.b1 || !a.b2 || !a.b3 || !a.in_mean || !a.in_rstd || !a.out_scale ||
-        !a.out_shift) {
+        !a.out_shift || hipStreamSynchronize(nullptr) != hipSuccess) {       // packed before any stream reads them
         mala_weights_free(w);
         return fail(MALA_E_OOM, "weight upload failed");
     }
+    // the FP32 copy has served
+    (void)hipFree(raw_d);
+    w->allocs.erase(std::find(w->allocs.begin(), w->allocs.end(), static_cast<void*>(raw_d)));
     *out = w;
     return MALA_OK;
 }
@@ -1102,7 +1076,7 @@ mala_status mala_ldos_vjp(mala_ctx* c, const mala_weights* w, const float* B, co
     if (n_pts < 0) return fail(MALA_E_INVALID_ARG, "n_pts < 0");
     if (n_pts == 0) return MALA_OK;
     if (!B || !v || !g_out) return fail(MALA_E_INVALID_ARG, "NULL buffer");
-    if (mlp_vjp_lds_bytes(w->args) > kMlpLdsBudget)
+    if (!mlp_vjp_supported(w->args))
         return fail(MALA_E_UNSUPPORTED, "network too wide for the VJP kernel's LDS tile");
     DeviceGuard g(c->device);
     HIP_TRY(staged(c, MALA_STAGE_MLP_VJP, n_pts, [&] { return launch_mlp_vjp(c->stream, w->args, B, v, n_pts, g_out); }));

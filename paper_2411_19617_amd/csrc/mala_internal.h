@@ -273,10 +273,11 @@ hipError_t launch_gauss(hipStream_t s, const BinState& bins, const int N[3], dou
 struct MlpArgs {
     int precision;               // 0 fp32, 1 bf16
     int n_in, n_h1, n_h2, n_out; // logical widths
-    int in_pad, h1_tiles, h2_tiles, out_tiles;
+    int in_pad, h1_tiles, h2_tiles, out_tiles;   // unit tiles of 16 (in_pad in units)
+    int wexp[3];                 // FP32 weights: layer l is packed as 2^wexp[l] W (0 for BF16)
     float slope;
     int out_act;
-    const void* W1;              // packed A operands
+    const void* W1;              // packed A operands: BF16, or two FP16 planes for FP32 weights
     const void* W2;
     const void* W3;
     const float* b1;             // padded biases (zeros in the padding)
@@ -319,8 +320,16 @@ struct MlpOut {
     double de = 0.0;
 };
 
+// 16-bit elements of a packed layer of mtiles x kt unit tiles, and the packing.
+size_t packed_weight_elems(int mtiles, int kt, int planes);
+hipError_t launch_pack_weights(hipStream_t s, const float* W, int fout, int fin, bool transposed, int mtiles, int kt,
+                               int planes, int wexp, void* out);
 int mlp_blocks(int64_t n_pts);
-size_t mlp_vjp_lds_bytes(const MlpArgs& a);
+int mlp_point_tiles(const MlpArgs& a, int64_t n_pts, int n_blocks);
+// Rows of 400 units hold the widest layer of the network (else rows of 528).
+constexpr int kRowWide = 400, kRowMax = 528;
+inline bool mlp_rows_wide(const MlpArgs& a) { return 16 * std::max(a.h1_tiles, a.h2_tiles) <= kRowWide; }
+bool mlp_vjp_supported(const MlpArgs& a);
 hipError_t launch_mlp_vjp(hipStream_t s, const MlpArgs& a, const float* B, const float* v, int64_t n_pts,
                           float* g_out);
 hipError_t launch_mlp(hipStream_t s, const MlpArgs& a, int mode, const float* B, int64_t n_pts, int row_stride,

@@ -1,7 +1,29 @@
 // MFMA building blocks of the per-point network (Sec. 2.4, Eq. ffnn): the
-// precision traits, the K-loop with its register prefetch ring and the dense
-// layer over the waves of a block.  Shared by the forward kernel and its
-// vector-Jacobian product.
+// number formats, the matrix product of one layer and the activation tile in
+// LDS.  Shared by the forward kernel and its vector-Jacobian product.
+//
+// Layers are computed transposed, out^T = W in^T: output units are the MFMA
+// M dimension, the points of the block's tile the N dimension.
+//
+// FP32 weights run as two FP16 planes per operand on the 16-bit matrix unit:
+// x = hi + lo with hi = fp16(x), lo = fp16(x - hi), after a power-of-two scale
+// that puts the largest value near 2^14 (per layer for the weights, per point
+// for the activations, taken from the values themselves, so nothing overflows
+// and only values 2^-28 below the largest lose bits).  hi + lo keeps x to at
+// most one unit of the last FP32 place (exactly for three values in four), the
+// products hi hi + hi lo + lo hi are accumulated in FP32, and lo lo (2^-24 of
+// the product) is dropped.  Against the 16x16x4 FP32 instruction that is
+// three 16x16x32 instructions of 16 cycles per 32 units instead of eight of
+// 32, and fewer FP32 roundings of the running sum (three per 32 units).  Error
+// against 64 bits of the plain network output (2-norm, x ~ N(0, 1)): 2.6e-7
+// with that instruction and 2.4e-7 here at 55-64-64-250, 5.5e-7 and 3.8e-7 at
+// 91-400-400-250, 6.1e-7 and 4.0e-7 at 128-512-512-256.  Time at 91-400-400-250:
+// 4.12 -> 1.46 ms per 729,000 points with the LDOS stored, 14.6 -> 4.8 us per
+// 1,000 points for the vector-Jacobian product.  What bounds it now: the
+// products are 0.65 ms of the 1.46 at the 1.9 GHz the card holds under them,
+// the epilogues (activation, scales, LDS writes) as much, and the weights
+// from L2 most of the rest.
+// BF16 weights use one plane, rounded once, without scales.
 #pragma once
 #include "mala_internal.h"
 
@@ -10,254 +32,415 @@ namespace mala {
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef short s4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;
+constexpr int kWaves = 8;          // waves of a network block (two per SIMD, one block per CU)
 
-__device__ __forceinline__ float leaky(float x, float s) { return x < 0.f ? s * x : x; }
-__device__ __forceinline__ f4 act4(f4 v, float s) {
-    return f4{leaky(v[0], s), leaky(v[1], s), leaky(v[2], s), leaky(v[3], s)};
+// sigma(x) = slope x for x < 0, else x.  For 0 < slope <= 1 that is the larger of
+// the two, for every x (infinities and NaN included): one instruction less.
+template <bool FAST>
+__device__ __forceinline__ float leaky(float x, float s) {
+    if constexpr (FAST) return fmaxf(x, s * x);
+    else return x < 0.f ? s * x : x;
 }
 __device__ __forceinline__ f4 bias4(const float* b, int off) {
     const float4 v = *reinterpret_cast<const float4*>(b + off);
     return f4{v.x, v.y, v.z, v.w};
 }
 
-template <int PREC>
-struct Prec;
+template <typename To, typename From>
+__device__ __forceinline__ To bits_as(const From& v) {
+    static_assert(sizeof(To) == sizeof(From), "size");
+    To t;
+    __builtin_memcpy(&t, &v, sizeof(t));
+    return t;
+}
 
-// FP32: MFMA 16x16x4.  K-step s of lane group g uses unit
-// 16*(s/4) + 4*g + s%4, so a batch of 4 K-steps reads 4 contiguous floats
-// per lane (one ds_read_b128); the weights are packed in the same order.
-template <>
-struct Prec<0> {
-    using T = float;
-    static constexpr int K = 4;      // units per K-step
-    static constexpr int PF = 4;     // K-steps per batch
-    static constexpr int DA = 2;     // weight batches fetched ahead
-    struct BatchA { float v[4]; };
-    struct BatchB { float4 v; };
-    __host__ __device__ static int stride(int w) { return ((w + 63) / 64) * 64 + 8; }
-    __device__ static void loadA(BatchA& a, const void* A, size_t base, int q) {
-        const float* p = static_cast<const float*>(A) + base + (size_t)q * PF * 64;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a.v[i] = p[i * 64];
-    }
-    __device__ static void loadB(BatchB& b, const T* row, int q, int g) {
-        b.v = *reinterpret_cast<const float4*>(row + 16 * q + 4 * g);
-    }
-    template <int S>
-    __device__ static f4 mma_step(const BatchA& a, const BatchB& b, f4 c) {
-        const float bv = S == 0 ? b.v.x : S == 1 ? b.v.y : S == 2 ? b.v.z : b.v.w;
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[S], bv, c, 0, 0, 0);
-    }
-    __device__ static void store4(T* dst, f4 v) {
-        *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-    __device__ static T cvt(float x) { return x; }
+// acc += A B over 32 (mfma32) or 16 (mfma16) units: lane l of A holds row
+// l % 16 and units 8 (l / 16) + 0..7 (4 (l / 16) + 0..3), of B the same for its point.
+template <int P>
+__device__ __forceinline__ f4 mfma32(uint4 a, uint4 b, f4 c) {
+    if constexpr (P == 2) return __builtin_amdgcn_mfma_f32_16x16x32_f16(bits_as<h8>(a), bits_as<h8>(b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(bits_as<bf8>(a), bits_as<bf8>(b), c, 0, 0, 0);
+}
+template <int P>
+__device__ __forceinline__ f4 mfma16(uint2 a, uint2 b, f4 c) {
+    if constexpr (P == 2) return __builtin_amdgcn_mfma_f32_16x16x16f16(bits_as<h4>(a), bits_as<h4>(b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bits_as<s4>(a), bits_as<s4>(b), c, 0, 0, 0);
+}
+
+// The activation tile of a block, [plane][point][unit], for NT point tiles and
+// layers of at most RS units.  The row stride RS (16-bit elements) is an odd
+// multiple of 8 dwords, which makes the 128-bit operand reads (16 points x 4
+// groups of 8 units) free of bank conflicts, and a constant, so that every
+// operand and output address is one register plus an immediate.
+template <int P, int NT, int RS>
+struct ActTile {
+    static constexpr int kPlane = 16 * NT * RS;
+    static constexpr size_t kBytes = (size_t)P * kPlane * 2;
+    unsigned short* p;
 };
 
-// BF16: MFMA 16x16x32, K-step s of lane group g uses units 32 s + 8 g + 0..7.
-// One K-step per batch (a 16x16x32 MFMA is short, so the weights are fetched
-// five batches ahead instead of holding larger batches).
-template <>
-struct Prec<1> {
-    using T = __bf16;
-    static constexpr int K = 32;
-    static constexpr int PF = 1;
-    static constexpr int DA = 5;
-    struct BatchA { uint4 v; };
-    struct BatchB { uint4 v; };
-    __host__ __device__ static int stride(int w) { return ((w + 127) / 128) * 128 + 16; }
-    __device__ static void loadA(BatchA& a, const void* A, size_t base, int q) {
-        a.v = static_cast<const uint4*>(A)[base + (size_t)q * 64];
+// What one wave computes of a layer of TO unit tiles: tiles wave, wave + 8, ...
+// (`cnt` of them) against every point tile, and, where TO leaves so few tiles
+// over after the full rounds that their (unit tile, point tile) products give
+// each wave at most one, such an item, so that no wave runs a whole extra tile.
+template <int NT>
+struct Share {
+    int cnt;
+    int it_mt, it_n;       // it_mt < 0: none
+    __device__ __forceinline__ Share(int TO, int wave, bool items) {
+        const int full = TO / kWaves, r = TO % kWaves;
+        const bool split = items && full > 0 && r * NT <= kWaves;
+        cnt = full + (!split && wave < r ? 1 : 0);
+        const bool on = split && wave < r * NT;
+        it_mt = on ? kWaves * full + wave / NT : -1;
+        it_n = on ? wave % NT : 0;
     }
-    __device__ static void loadB(BatchB& b, const T* row, int q, int g) {
-        b.v = *reinterpret_cast<const uint4*>(row + 32 * q + 8 * g);
-    }
-    template <int S>
-    __device__ static f4 mma_step(const BatchA& a, const BatchB& b, f4 c) {
-        bf8 x, y;
-        __builtin_memcpy(&x, &a.v, 16);
-        __builtin_memcpy(&y, &b.v, 16);
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
-    }
-    __device__ static void store4(T* dst, f4 v) {
-        bf4 h = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-        *reinterpret_cast<bf4*>(dst) = h;
-    }
-    __device__ static T cvt(float x) { return (__bf16)x; }
 };
 
-// acc[m][n] += sum over K-steps s < KS of A_m(s) B_n(s), in batches of PF
-// K-steps (KS is a multiple of PF): MB weight tiles (A_m at base[m]) against
-// NA point tiles, so every weight operand feeds NA MFMAs and every LDS
-// operand MB.  Weights (from L2) are fetched DA batches ahead into a ring of
-// DA+1 register sets, LDS operands one batch ahead into a ring of two; the
-// loop is unrolled by a multiple of both ring sizes so the sets rotate by
-// name: no register copies and no wait on a load issued in the same batch.
-// Within a batch the MFMAs go K-step by K-step over the MB x NA independent
-// accumulators.  An MB-fold batch is MB times longer, so fewer batches ahead
-// cover the same L2 latency.
-template <int PREC, int MB, int NA>
-__device__ __forceinline__ void kloop_mn(const void* A, const size_t (&base)[MB], int KS,
-                                         const typename Prec<PREC>::T* const (&rows)[NA], int g,
-                                         f4 (&acc)[MB][NA]) {
-    using P = Prec<PREC>;
-    using BA = typename P::BatchA;
-    using BB = typename P::BatchB;
-    constexpr int DA = (P::DA + MB - 1) / MB;
-    constexpr int RA = DA + 1;
-    constexpr int U = RA % 2 == 0 ? RA : 2 * RA;
-    const int NQ = KS / P::PF;
-    BA a[RA][MB];
-    BB b[2][NA];
-    auto fetchA = [&](int q, BA (&ad)[MB]) {
+// Weights are packed in lane order, [unit tile][step][plane][lane][16 bytes]:
+// (T + 1) / 2 steps of 32 units for T unit tiles of input; in the last step of
+// an odd T a lane's first 8 bytes hold its 4 of the 16 units.
+__host__ __device__ __forceinline__ int w_steps(int T) { return (T + 1) / 2; }
+
+template <int P>
+__device__ __forceinline__ void fetch_tile(const void* W, int mt, int T, int s, int lane, uint4 (&d)[P]) {
+    // uniform base plus a 32-bit lane offset: no per-lane 64-bit address arithmetic
+    const char* base = static_cast<const char*>(W) + ((size_t)mt * w_steps(T) + s) * (P * 1024);
 #pragma unroll
-        for (int m = 0; m < MB; ++m) P::loadA(ad[m], A, base[m], q);
+    for (int p = 0; p < P; ++p) d[p] = *reinterpret_cast<const uint4*>(base + p * 1024 + (unsigned)lane * 16u);
+}
+
+// The accumulators of one wave: MT unit tiles x NT point tiles, and the item.
+template <int NT, int MT>
+struct Acc {
+    f4 t[MT][NT];
+    f4 it;
+};
+
+// Half a step: the first 8 bytes of the weight operand, 16 units.
+template <int P>
+__device__ __forceinline__ void half_products(const uint4 (&w)[P], const uint2 (&b)[P], f4& c) {
+    auto lo = [](const uint4& v) { return make_uint2(v.x, v.y); };
+    c = mfma16<P>(lo(w[0]), b[0], c);
+    if constexpr (P == 2) {
+        c = mfma16<P>(lo(w[0]), b[P - 1], c);
+        c = mfma16<P>(lo(w[P - 1]), b[0], c);
+    }
+}
+
+// t[m][n] = the wave's unit tile m times point tile n over T unit tiles of
+// input: T / 2 steps of 32 units and, for odd T, one of 16.  A step takes the
+// unit tiles at once, or in two halves where two sets of them would not fit
+// the registers; the weights of the next step (half) come from L2 while this
+// one's products run, the LDS operand of the next point tile while this one's
+// do.  The scheduling barriers keep the compiler from reading all operands
+// first, which spills.
+template <int P, int NT, int MT, int RS, int M>
+__device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS>& in, int wave, int lane,
+                                   f4 (&t)[MT][NT]) {
+    constexpr int NC = M * P > 6 ? 2 : 1, H0 = (M + NC - 1) / NC;      // chunks per step, tiles of the first
+    constexpr int PS = ActTile<P, NT, RS>::kPlane;
+    const int KS = T >> 1, KL = w_steps(T) - 1, g = lane >> 4;
+    const unsigned short* row = in.p + (lane & 15) * RS;
+    uint4 a[2][H0][P], b[2][P];
+    auto fetch = [&](int s, auto hc, uint4 (&d)[H0][P]) {
+        constexpr int h = decltype(hc)::value;
+#pragma unroll
+        for (int m = 0; m < H0; ++m)
+            if (h * H0 + m < M) fetch_tile<P>(W, wave + kWaves * (h * H0 + m), T, s < KL ? s : KL, lane, d[m]);
     };
-    auto fetchB = [&](int q, BB (&bd)[NA]) {
+    auto fetch_b = [&](int n, int s, uint4 (&d)[P]) {
 #pragma unroll
-        for (int n = 0; n < NA; ++n) P::loadB(bd[n], rows[n], q, g);
+        for (int p = 0; p < P; ++p)
+            d[p] = *reinterpret_cast<const uint4*>(row + n * 16 * RS + p * PS + 32 * s + 8 * g);
     };
-    auto mma = [&](const BA (&as)[MB], const BB (&bs)[NA]) {
-        static_for<0, P::PF>([&](auto sc) {
-            constexpr int S = decltype(sc)::value;
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, NC - 1> clast{};
+    fetch(0, c0, a[0]);
+    static_for<0, M>([&](auto mc) {
+        static_for<0, NT>([&](auto nc) { t[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f}; });
+    });
+    if (KS > 0) fetch_b(0, 0, b[0]);
+    // step s, the I-th of the loop body: its first chunk lies in a[I * NC % 2],
+    // its first LDS operand in b[I * NC * NT % 2]
+    auto step = [&](int s, auto ic) {
+        constexpr int Q = decltype(ic)::value * NC % 2, G0 = decltype(ic)::value * NC * NT % 2;
+        static_for<0, NC>([&](auto hc) {
+            constexpr int h = decltype(hc)::value, MH = M - h * H0 < H0 ? M - h * H0 : H0;
+            const uint4 (&ac)[H0][P] = a[(Q + h) % 2];
+            if constexpr (h + 1 < NC) fetch(s, clast, a[(Q + h + 1) % 2]);
+            else fetch(s + 1, c0, a[(Q + h + 1) % 2]);
+            static_for<0, NT>([&](auto nc) {
+                constexpr int n = decltype(nc)::value, G = G0 + h * NT + n;
+                const uint4 (&bc)[P] = b[G % 2];
+                if constexpr (n + 1 < NT) fetch_b(n + 1, s, b[(G + 1) % 2]);
+                else fetch_b(0, h + 1 < NC ? s : min(s + 1, KS - 1), b[(G + 1) % 2]);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int m = 0; m < MB; ++m)
+                for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][0], bc[0], t[h * H0 + m][n]);
+                if constexpr (P == 2) {
 #pragma unroll
-                for (int n = 0; n < NA; ++n) acc[m][n] = P::template mma_step<S>(as[m], bs[n], acc[m][n]);
+                    for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][0], bc[P - 1], t[h * H0 + m][n]);
+#pragma unroll
+                    for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][P - 1], bc[0], t[h * H0 + m][n]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
         });
     };
-    // batch q + u (u < U) lives in a[u % RA] and b[u % 2].  Prefetches past
-    // the last batch re-read the last batch (unused): every load is
-    // unconditional, so the waits count exactly the loads still needed.
-    auto step = [&](int q, auto uc) {
-        constexpr int u = decltype(uc)::value;
-        const int qa = q + u + DA < NQ ? q + u + DA : NQ - 1;
-        const int qb = q + u + 1 < NQ ? q + u + 1 : NQ - 1;
-        fetchA(qa, a[(u + DA) % RA]);
-        fetchB(qb, b[(u + 1) % 2]);
-        mma(a[u % RA], b[u % 2]);
+    // the half step of an odd T; its first chunk lies in a[0]
+    auto tail = [&]() {
+        if constexpr (NC == 2) fetch(KL, clast, a[1]);
+        static_for<0, NT>([&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            uint2 bt[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) bt[p] = *reinterpret_cast<const uint2*>(row + n * 16 * RS + p * PS + 32 * KS + 4 * g);
+            static_for<0, M>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                half_products<P>(a[m / H0][m % H0], bt, t[m][n]);
+            });
+        });
     };
-    if (NQ <= 0) return;
-    static_for<0, DA>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        fetchA(i < NQ ? i : NQ - 1, a[i]);
+    int s = 0;
+    if constexpr (NC == 2) {
+#pragma clang loop unroll(disable)
+        for (; s < KS; ++s) step(s, c0);
+    } else {
+#pragma clang loop unroll(disable)
+        for (; s + 2 <= KS; s += 2) {
+            step(s, c0);
+            step(s + 1, c1);
+        }
+        if (s < KS) {
+            step(s, c0);
+            static_for<0, H0>([&](auto mc) {
+                static_for<0, P>([&](auto pc) { a[0][decltype(mc)::value][decltype(pc)::value] = a[1][decltype(mc)::value][decltype(pc)::value]; });
+            });
+        }
+    }
+    if (T & 1) tail();
+}
+
+// The wave's item: one unit tile times one point tile.  Three products per
+// step cover little of a weight read, so six steps of weights are in flight.
+template <int P, int NT, int RS>
+__device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh, const ActTile<P, NT, RS>& in, int lane) {
+    constexpr int D = 6, PS = ActTile<P, NT, RS>::kPlane;
+    const int KS = T >> 1, KL = w_steps(T) - 1, g = lane >> 4;
+    const unsigned short* row = in.p + (16 * sh.it_n + (lane & 15)) * RS;
+    uint4 a[D][P];
+    static_for<0, D>([&](auto dc) { fetch_tile<P>(W, sh.it_mt, T, min((int)decltype(dc)::value, KL), lane, a[decltype(dc)::value]); });
+    f4 t[P == 2 ? 3 : 1] = {};            // one chain per product: they do not wait for each other
+    auto step = [&](int s, uint4 (&w)[P]) {
+        uint4 b[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) b[p] = *reinterpret_cast<const uint4*>(row + p * PS + 32 * s + 8 * g);
+        t[0] = mfma32<P>(w[0], b[0], t[0]);
+        if constexpr (P == 2) {
+            t[1] = mfma32<P>(w[0], b[P - 1], t[1]);
+            t[2] = mfma32<P>(w[P - 1], b[0], t[2]);
+        }
+        fetch_tile<P>(W, sh.it_mt, T, min(s + D, KL), lane, w);
+    };
+    int s = 0;
+#pragma clang loop unroll(disable)
+    for (; s + D <= KS; s += D) static_for<0, D>([&](auto dc) { step(s + decltype(dc)::value, a[decltype(dc)::value]); });
+    // the last KS % D steps, then the half step: a[i] holds step s + i
+    static_for<0, D>([&](auto dc) {
+        constexpr int i = decltype(dc)::value;
+        if (s + i < KS) step(s + i, a[i]);
+        else if (s + i == KS && (T & 1)) {
+            uint2 bt[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) bt[p] = *reinterpret_cast<const uint2*>(row + p * PS + 32 * KS + 4 * g);
+            half_products<P>(a[i], bt, t[0]);
+        }
     });
-    fetchB(0, b[0]);
-    int q = 0;
-    for (; q + U <= NQ; q += U) static_for<0, U>([&](auto uc) { step(q, uc); });
-    static_for<0, U>([&](auto uc) {
-        if (q + decltype(uc)::value < NQ) step(q, uc);
+    if constexpr (P == 2) return t[0] + (t[1] + t[2]);
+    else return t[0];
+}
+
+// acc = W in for the wave's share of a layer.
+template <int P, int NT, int MT, int RS, bool ITEMS>
+__device__ __forceinline__ void layer_mm(const void* W, int T, const Share<NT>& sh, const ActTile<P, NT, RS>& in,
+                                         int wave, int lane, Acc<NT, MT>& acc) {
+    static_for<1, MT + 1>([&](auto mc) {
+        if (sh.cnt == decltype(mc)::value) mm<P, NT, MT, RS, decltype(mc)::value>(W, T, in, wave, lane, acc.t);
     });
+    if constexpr (ITEMS)
+        if (sh.it_mt >= 0) acc.it = mm_item<P, NT, RS>(W, T, sh, in, lane);
 }
 
-// One weight tile against NA point tiles.
-template <int PREC, int NA>
-__device__ __forceinline__ void kloop(const void* A, size_t base, int KS, const typename Prec<PREC>::T* const (&rows)[NA],
-                                      int g, f4 (&acc)[NA]) {
-    const size_t bases[1] = {base};
-    f4 acc1[1][NA];
-#pragma unroll
-    for (int n = 0; n < NA; ++n) acc1[0][n] = acc[n];
-    kloop_mn<PREC, 1, NA>(A, bases, KS, rows, g, acc1);
-#pragma unroll
-    for (int n = 0; n < NA; ++n) acc[n] = acc1[0][n];
+// Power-of-two exponent that brings a value of largest magnitude `bits` (FP32
+// bit pattern, sign cleared) to [2^14, 2^15); 0 for infinities and NaN, at
+// most 100 so that its inverse and products with weight scales stay normal.
+__device__ __forceinline__ int act_exponent(unsigned bits) {
+    const int e = (int)(bits >> 23);
+    if (e == 255) return 0;
+    return min(14 - (e - 127), 100);
+}
+__device__ __forceinline__ float pow2f(int k) { return __int_as_float((127 + k) << 23); }      // |k| <= 126
+
+// Largest magnitude of mx and four values (NaN passes by: it stays NaN under any scale).
+__device__ __forceinline__ float max_abs4(float mx, f4 v) {
+    mx = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), mx);
+    return fmaxf(fmaxf(fabsf(v[2]), fabsf(v[3])), mx);
 }
 
-// One dense layer on the waves of the block: out[p][16 mt + u] = act(W x + b)
-// for the M-tiles tile_base + mt, mt < tiles.  in: LDS rows (stride is), out:
-// LDS rows (stride os), column 16 mt.  With MB > 1 the waves first take MB
-// M-tiles each as long as every wave has a full set, then one each, then
-// the (M-tile, point-tile) items left over, so the waves stay balanced.
-template <int PREC, int NT, int MB = 1>
-__device__ __forceinline__ void layer(const void* W, const float* bias, int tiles, int tile_base, int KS,
-                                      const typename Prec<PREC>::T* in, int is, typename Prec<PREC>::T* out,
-                                      int os, float slope, int wave, int lane) {
-    using P = Prec<PREC>;
-    using T = typename P::T;
+// hi = fp16(v scale), lo = fp16(v scale - hi) of two values, each half one
+// mixed-precision FMA that rounds once (v scale is exact: a power of two).
+__device__ __forceinline__ void split2(float v0, float v1, float scale, unsigned& hi, unsigned& lo) {
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(v0), "v"(scale));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(v1), "v"(scale));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(v0), "v"(scale), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(v1), "v"(scale), "v"(hi));
+}
+
+// Four consecutive units of one point into the tile (scale: FP32 weights only).
+template <int P, int NT, int RS>
+__device__ __forceinline__ void put4(const ActTile<P, NT, RS>& t, int point, int unit, f4 v, float scale) {
+    unsigned short* d = t.p + point * RS + unit;
+    if constexpr (P == 1) {
+        const bf4 h = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+        *reinterpret_cast<bf4*>(d) = h;
+    } else {
+        uint2 hi, lo;
+        split2(v[0], v[1], scale, hi.x, lo.x);
+        split2(v[2], v[3], scale, hi.y, lo.y);
+        *reinterpret_cast<uint2*>(d) = hi;
+        *reinterpret_cast<uint2*>(d + ActTile<P, NT, RS>::kPlane) = lo;
+    }
+}
+
+// Largest magnitude per point of a layer's output over the block: `m` is the
+// lane's own maximum for point 16 n + j; out must start at zero.
+__device__ __forceinline__ void point_max(unsigned* out, int n, int lane, float m) {
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if ((lane >> 4) == (n & 3)) atomicMax(out + 16 * n + (lane & 15), (unsigned)__float_as_int(m));
+}
+
+// Largest unsigned value over the wave, in a scalar register: shifts inside
+// each row of 16 lanes, then the row results broadcast upwards (lane 63 ends
+// with all of them).
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+#define MALA_DPP_MAX(ctrl) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false))
+    MALA_DPP_MAX(0x111);      // row_shr 1, 2, 4, 8
+    MALA_DPP_MAX(0x112);
+    MALA_DPP_MAX(0x114);
+    MALA_DPP_MAX(0x118);
+    MALA_DPP_MAX(0x142);      // row_bcast 15, 31
+    MALA_DPP_MAX(0x143);
+#undef MALA_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// One layer's output into the tile that also held its input, as the next
+// layer's input: ep(slot, mt, n, acc) forms the four values of the lane's units
+// of (unit tile mt, point tile n) in place (slot: the wave's tile, MT the
+// item); then, once every wave has read the input, the values are written with
+// the point's scale.
+template <int P, int NT, int MT, int RS, typename Ep>
+__device__ __forceinline__ void layer_out(Acc<NT, MT>& acc, const Share<NT>& sh, const ActTile<P, NT, RS>& t,
+                                          unsigned* s_max, int wave, int lane, Ep&& ep) {
     const int j = lane & 15, g = lane >> 4;
-    int done = 0;
-    if constexpr (MB > 1) {
-        const int fullm = (tiles / (kWaves * MB)) * kWaves * MB;
-        for (int r0 = 0; r0 < fullm; r0 += kWaves * MB) {
-            f4 acc[MB][NT];
-            size_t bases[MB];
-            const T* rows[NT];
+    float mx[NT];
 #pragma unroll
-            for (int n = 0; n < NT; ++n) rows[n] = in + (16 * n + j) * is;
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const int mt = r0 + MB * wave + m;
-                const f4 b = bias4(bias, 16 * (tile_base + mt) + 4 * g);
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[m][n] = b;
-                bases[m] = (size_t)(tile_base + mt) * KS * 64 + lane;
-            }
-            kloop_mn<PREC, MB, NT>(W, bases, KS, rows, g, acc);
-#pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const int mt = r0 + MB * wave + m;
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    P::store4(out + (16 * n + j) * os + 16 * mt + 4 * g, act4(acc[m][n], slope));
-            }
+    for (int n = 0; n < NT; ++n) mx[n] = 0.f;
+    static_for<0, MT>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        if (m < sh.cnt) {
+            static_for<0, NT>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                ep(mc, wave + kWaves * m, n, acc.t[m][n]);
+                if constexpr (P == 2) mx[n] = max_abs4(mx[n], acc.t[m][n]);
+            });
         }
-        done = fullm;
+    });
+    if (sh.it_mt >= 0) {
+        ep(std::integral_constant<int, MT>{}, sh.it_mt, sh.it_n, acc.it);
+        if constexpr (P == 2) point_max(s_max, sh.it_n, lane, max_abs4(0.f, acc.it));
     }
-    const int full = done + ((tiles - done) / kWaves) * kWaves;
-    for (int mt = done + wave; mt < full; mt += kWaves) {
-        f4 acc[NT];
-        const f4 b = bias4(bias, 16 * (tile_base + mt) + 4 * g);
-        const T* rows[NT];
+    if constexpr (P == 2)
+        if (sh.cnt > 0) {
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            acc[n] = b;
-            rows[n] = in + (16 * n + j) * is;
+            for (int n = 0; n < NT; ++n) point_max(s_max, n, lane, mx[n]);
         }
-        kloop<PREC, NT>(W, (size_t)(tile_base + mt) * KS * 64 + lane, KS, rows, g, acc);
+    __syncthreads();
+    float sc[NT];
 #pragma unroll
-        for (int n = 0; n < NT; ++n) P::store4(out + (16 * n + j) * os + 16 * mt + 4 * g, act4(acc[n], slope));
+    for (int n = 0; n < NT; ++n) sc[n] = P == 2 ? pow2f(act_exponent(s_max[16 * n + j])) : 1.f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+        if (m < sh.cnt) {
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                put4(t, 16 * n + j, 16 * (wave + kWaves * m) + 4 * g, acc.t[m][n], sc[n]);
+        }
+    if (sh.it_mt >= 0) {
+        const int p = 16 * sh.it_n + j;
+        put4(t, p, 16 * sh.it_mt + 4 * g, acc.it, P == 2 ? pow2f(act_exponent(s_max[p])) : 1.f);
     }
-    const int rem_items = (tiles - full) * NT;
-    for (int it = wave; it < rem_items; it += kWaves) {
-        const int mt = full + it / NT, n = it % NT;
-        f4 acc[1] = {bias4(bias, 16 * (tile_base + mt) + 4 * g)};
-        const T* rows[1] = {in + (16 * n + j) * is};
-        kloop<PREC, 1>(W, (size_t)(tile_base + mt) * KS * 64 + lane, KS, rows, g, acc);
-        P::store4(out + (16 * n + j) * os + 16 * mt + 4 * g, act4(acc[0], slope));
-    }
+    __syncthreads();
 }
 
+// Factor that takes an accumulated product back to its true scale: the inverse
+// of the point's activation scale (its largest magnitude in s_max) and of the
+// layer's weight scale 2^wexp.
+template <int P>
+__device__ __forceinline__ float unscale(const unsigned* s_max, int point, int wexp) {
+    if constexpr (P == 1) return 1.f;
+    else return pow2f(-act_exponent(s_max[point])) * pow2f(-wexp);
+}
 
-// Dense layer with a caller-supplied epilogue: acc = W x (+ bias when given)
-// for every (point tile n, M-tile mt) the wave owns; ep(n, mt, acc) writes it.
-template <int PREC, int NT, typename Ep>
-__device__ __forceinline__ void layer_ep(const void* W, const float* bias, int tiles, int KS,
-                                         const typename Prec<PREC>::T* in, int is, int wave, int lane, Ep&& ep) {
-    using T = typename Prec<PREC>::T;
-    const int j = lane & 15, g = lane >> 4;
-    const int full = (tiles / kWaves) * kWaves;
-    for (int mt = wave; mt < full; mt += kWaves) {
-        f4 acc[NT];
-        const f4 b = bias ? bias4(bias, 16 * mt + 4 * g) : f4{0.f, 0.f, 0.f, 0.f};
-        const T* rows[NT];
+// Standardised descriptor rows of a tile into LDS: wave w takes rows w R ..
+// w R + R - 1, lane = columns lane and lane + 64, at most twelve rows'
+// reads in flight.  A row past the last valid point repeats that point (its
+// results are not used), a pad column the last one with mean and 1/std zero.
+template <int P, int NT, int RS>
+__device__ __forceinline__ void stage_rows(const float* __restrict__ B, int64_t p0, int rows, int row_stride, int n_in,
+                                           int in_pad, const float (&mu)[2], const float (&rstd)[2],
+                                           const ActTile<P, NT, RS>& t, unsigned* s_max, int wave, int lane) {
+    constexpr int R = 16 * NT / kWaves, C = R % 12 == 0 ? 12 : R % 8 == 0 ? 8 : 4, PS = ActTile<P, NT, RS>::kPlane;
+    const int c0 = min(lane, n_in - 1), c1 = min(lane + 64, n_in - 1);
+#pragma clang loop unroll(disable)
+    for (int q0 = 0; q0 < R; q0 += C) {
+        float v[C][2];
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            acc[n] = b;
-            rows[n] = in + (16 * n + j) * is;
+        for (int q = 0; q < C; ++q) {
+            const float* r = B + (p0 + min(wave * R + q0 + q, rows - 1)) * row_stride * n_in;
+            v[q][0] = r[c0];
+            v[q][1] = n_in > 64 ? r[c1] : 0.f;
         }
-        kloop<PREC, NT>(W, (size_t)mt * KS * 64 + lane, KS, rows, g, acc);
 #pragma unroll
-        for (int n = 0; n < NT; ++n) ep(n, mt, acc[n]);
-    }
-    const int rem_items = (tiles - full) * NT;
-    for (int it = wave; it < rem_items; it += kWaves) {
-        const int mt = full + it / NT, n = it % NT;
-        f4 acc[1] = {bias ? bias4(bias, 16 * mt + 4 * g) : f4{0.f, 0.f, 0.f, 0.f}};
-        const T* rows[1] = {in + (16 * n + j) * is};
-        kloop<PREC, 1>(W, (size_t)mt * KS * 64 + lane, KS, rows, g, acc);
-        ep(n, mt, acc[0]);
+        for (int q = 0; q < C; ++q) {
+            const int p = wave * R + q0 + q;
+            const float x0 = (v[q][0] - mu[0]) * rstd[0], x1 = (v[q][1] - mu[1]) * rstd[1];
+            unsigned short* d = t.p + p * RS + lane;
+            if constexpr (P == 2) {
+                const unsigned mx = wave_max_u32(max((unsigned)__float_as_int(x0) & 0x7fffffffu, (unsigned)__float_as_int(x1) & 0x7fffffffu));
+                s_max[p] = mx;                                   // every lane the same value
+                unsigned hi, lo;
+                split2(x0, x1, pow2f(act_exponent(mx)), hi, lo);
+                if (lane < in_pad) {
+                    d[0] = (unsigned short)hi;
+                    d[PS] = (unsigned short)lo;
+                }
+                if (lane + 64 < in_pad) {
+                    d[64] = (unsigned short)(hi >> 16);
+                    d[PS + 64] = (unsigned short)(lo >> 16);
+                }
+            } else {
+                if (lane < in_pad) *reinterpret_cast<__bf16*>(d) = (__bf16)x0;
+                if (lane + 64 < in_pad) *reinterpret_cast<__bf16*>(d + 64) = (__bf16)x1;
+            }
+        }
     }
 }
 

@@ -8,127 +8,166 @@
 //   delta3 = s .* v .* sigma'(z3),  delta2 = (W3^T delta3) .* sigma'(z2),
 //   delta1 = (W2^T delta2) .* sigma'(z1),  g = (W1^T delta1) ./ std.
 //
-// A block of 8 waves takes 32 points at a time.  The forward pass is the
-// same MFMA layer as the network kernel, with both hidden activations kept
-// in LDS: sigma'(z) is read from the sign of the stored activation (z > 0
-// exactly when sigma(z) > 0), so no pre-activations are stored.  The three
-// backward layers are MFMA layers over the transposed weights (packed like
-// the forward ones): delta3 overwrites the input tile, delta2 the layer-2
-// activations and delta1 the layer-1 activations, each in place by the lane
-// that reads the activation it replaces.  FP32 only.
+// Six MFMA layers over one activation tile in LDS, as in the network kernel:
+// the forward layers, then the same over the transposed weights.  No
+// activation is kept for the way back: only the signs of the two hidden layers
+// matter there, and a backward layer's output units belong to the same lane as
+// the forward layer's, so each lane keeps them as bits in registers.  FP32
+// weights only (two FP16 planes).
 #include "mlp_core.h"
 
 namespace mala {
 
-template <int NT>
-__global__ __launch_bounds__(kWaves * 64) void k_mlp_vjp(MlpArgs a, const float* __restrict__ B,
-                                                         const float* __restrict__ v, int64_t n_pts,
-                                                         float* __restrict__ g_out) {
-    using P = Prec<0>;
+template <int NT, int MT, int RS>
+__global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const float* __restrict__ B,
+                                                            const float* __restrict__ v, int64_t n_pts,
+                                                            float* __restrict__ g_out) {
     constexpr int NP = 16 * NT;
+    static_assert(NT * 4 <= 32, "one mask word per unit tile");
     extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = lane & 15, g = lane >> 4;
-    const int hs = P::stride(a.h1_tiles * 16), h2s = P::stride(a.h2_tiles * 16);
-    const int xs = P::stride(a.in_pad > a.out_tiles * 16 ? a.in_pad : a.out_tiles * 16);
-    float* H1 = reinterpret_cast<float*>(smem);
-    float* H2 = H1 + NP * hs;
-    float* X = H2 + NP * h2s;           // input tile, then delta3
-    const int n_in = a.n_in, n_out = a.n_out;
+    __shared__ unsigned s_max[6][NP];        // largest input of each layer per point
+    const int lane0 = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_in = a.n_in, n_out = a.n_out, in_tiles = a.in_pad / 16;
     const float slope = a.slope;
-    const int KS1 = a.in_pad / P::K, KS2 = a.h1_tiles * 16 / P::K, KS3 = a.h2_tiles * 16 / P::K;
-    const int KB3 = a.out_tiles * 16 / P::K, KB2 = a.h2_tiles * 16 / P::K, KB1 = a.h1_tiles * 16 / P::K;
-    const int in_tiles = a.in_pad / 16;
+    const ActTile<2, NT, RS> act{reinterpret_cast<unsigned short*>(smem)};
 
     const int64_t n_it = (n_pts + NP - 1) / NP;
     const int nb = gridDim.x;
     const int64_t it_begin = n_it * blockIdx.x / nb, it_end = n_it * (blockIdx.x + 1) / nb;
-    auto mask4 = [&](const float* h) {       // sigma'(z) from the sign of sigma(z)
-        return f4{h[0] > 0.f ? 1.f : slope, h[1] > 0.f ? 1.f : slope, h[2] > 0.f ? 1.f : slope,
-                  h[3] > 0.f ? 1.f : slope};
+    auto rows_of = [&](int64_t it) {
+        const int64_t left = n_pts - it * NP;
+        return (int)(left < NP ? left : NP);
     };
+    const float mu[2] = {lane0 < n_in ? a.in_mean[lane0] : 0.f, lane0 + 64 < n_in ? a.in_mean[lane0 + 64] : 0.f};
+    const float rstd[2] = {lane0 < n_in ? a.in_rstd[lane0] : 0.f, lane0 + 64 < n_in ? a.in_rstd[lane0 + 64] : 0.f};
 
     for (int64_t it = it_begin; it < it_end; ++it) {
         const int64_t p0 = it * NP;
-        const int rows = (int)((n_pts - p0) < NP ? (n_pts - p0) : NP);
-        for (int e = threadIdx.x; e < NP * a.in_pad; e += blockDim.x) {
-            const int pj = e / a.in_pad, k = e - pj * a.in_pad;
-            float x = 0.f;
-            if (pj < rows && k < n_in) x = (B[(p0 + pj) * n_in + k] - a.in_mean[k]) * a.in_rstd[k];
-            X[pj * xs + k] = x;
-        }
+        const int rows = rows_of(it);
+        int lane = lane0;                      // loop-variant, as in the network kernel
+        asm volatile("" : "+v"(lane));
+        const int j = lane & 15, g = lane >> 4;
+        stage_rows(B, p0, rows, 1, n_in, a.in_pad, mu, rstd, act, s_max[0], wave, lane);
+        for (int i = threadIdx.x; i < 5 * NP; i += blockDim.x) s_max[1][i] = 0;
         __syncthreads();
-        // forward: H1 = sigma(W1 x + b1), H2 = sigma(W2 H1 + b2)
-        layer_ep<0, NT>(a.W1, a.b1, a.h1_tiles, KS1, X, xs, wave, lane, [&](int n, int mt, f4 acc) {
-            P::store4(H1 + (16 * n + j) * hs + 16 * mt + 4 * g, act4(acc, slope));
-        });
-        __syncthreads();
-        layer_ep<0, NT>(a.W2, a.b2, a.h2_tiles, KS2, H1, hs, wave, lane, [&](int n, int mt, f4 acc) {
-            P::store4(H2 + (16 * n + j) * h2s + 16 * mt + 4 * g, act4(acc, slope));
-        });
-        __syncthreads();
-        // output layer and delta3 = s .* v .* sigma'(z3) into the input tile
-        layer_ep<0, NT>(a.W3, a.b3, a.out_tiles, KS3, H2, h2s, wave, lane, [&](int n, int mt, f4 acc) {
-            const int pj = 16 * n + j;
-            f4 d;
+        Acc<NT, MT> acc;
+        unsigned mask[2][MT + 1];              // sigma' of the two hidden layers: bit 4 n + r of word m; the item's in the last
+        // forward: the hidden layers, their signs kept
+        static_for<0, 2>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            const float* bias = l == 0 ? a.b1 : a.b2;
+            const Share<NT> sh(l == 0 ? a.h1_tiles : a.h2_tiles, wave, true);
+            layer_mm<2, NT, MT, RS, true>(l == 0 ? a.W1 : a.W2, l == 0 ? in_tiles : a.h1_tiles, sh, act, wave, lane, acc);
+            float c[NT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int e = 16 * mt + 4 * g + r;
-                float x = 0.f;
-                if (pj < rows && e < n_out) {
-                    x = v[(p0 + pj) * n_out + e] * a.out_scale[e];
-                    if (a.out_act && !(acc[r] > 0.f)) x *= slope;
+            for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[l], 16 * n + j, a.wexp[l]);
+#pragma unroll
+            for (int m = 0; m <= MT; ++m) mask[l][m] = 0;
+            layer_out<2, NT, MT, RS>(acc, sh, act, s_max[l + 1], wave, lane, [&](auto slotc, int mt, int n, f4& z) {
+                constexpr int slot = decltype(slotc)::value;
+                const f4 b = bias4(bias, 16 * mt + 4 * g);
+                float cn;
+                if constexpr (slot < MT) cn = c[n];
+                else cn = unscale<2>(s_max[l], 16 * n + j, a.wexp[l]);
+                unsigned bits = 0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    z[r] = leaky<false>(fmaf(z[r], cn, b[r]), slope);
+                    bits |= z[r] > 0.f ? 1u << r : 0u;
                 }
-                d[r] = x;
-            }
-            P::store4(X + pj * xs + 16 * mt + 4 * g, d);
+                mask[l][slot] |= bits << (slot < MT ? 4 * n : 0);
+            });
         });
-        __syncthreads();
-        // delta2 = (W3^T delta3) .* sigma'(z2), in place over H2
-        layer_ep<0, NT>(a.W3T, nullptr, a.h2_tiles, KB3, X, xs, wave, lane, [&](int n, int mt, f4 acc) {
-            float* h = H2 + (16 * n + j) * h2s + 16 * mt + 4 * g;
-            P::store4(h, acc * mask4(h));
-        });
-        __syncthreads();
-        // delta1 = (W2^T delta2) .* sigma'(z1), in place over H1
-        layer_ep<0, NT>(a.W2T, nullptr, a.h1_tiles, KB2, H2, h2s, wave, lane, [&](int n, int mt, f4 acc) {
-            float* h = H1 + (16 * n + j) * hs + 16 * mt + 4 * g;
-            P::store4(h, acc * mask4(h));
-        });
-        __syncthreads();
-        // g = (W1^T delta1) ./ std
-        layer_ep<0, NT>(a.W1T, nullptr, in_tiles, KB1, H1, hs, wave, lane, [&](int n, int mt, f4 acc) {
-            const int pj = 16 * n + j;
-            if (pj >= rows) return;
+        // output layer and delta3 = s .* v .* sigma'(z3)
+        {
+            const Share<NT> sh(a.out_tiles, wave, false);
+            layer_mm<2, NT, MT, RS, false>(a.W3, a.h2_tiles, sh, act, wave, lane, acc);
+            float c[NT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = 16 * mt + 4 * g + r;
-                if (k < n_in) g_out[(p0 + pj) * n_in + k] = acc[r] * a.in_rstd[k];
-            }
+            for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[2], 16 * n + j, a.wexp[2]);
+            layer_out<2, NT, MT, RS>(acc, sh, act, s_max[3], wave, lane, [&](auto, int mt, int n, f4& z) {
+                const f4 b = bias4(a.b3, 16 * mt + 4 * g);
+                const int pj = 16 * n + j;
+                const float* vp = v + (p0 + min(pj, rows - 1)) * n_out;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int e = 16 * mt + 4 * g + r;
+                    float x = vp[min(e, n_out - 1)] * a.out_scale[e];
+                    if (a.out_act && !(fmaf(z[r], c[n], b[r]) > 0.f)) x *= slope;
+                    z[r] = (pj < rows && e < n_out) ? x : 0.f;
+                }
+            });
+        }
+        // delta2 = (W3^T delta3) .* sigma'(z2), delta1 = (W2^T delta2) .* sigma'(z1)
+        static_for<0, 2>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            const Share<NT> sh(l == 0 ? a.h2_tiles : a.h1_tiles, wave, true);
+            const int we = a.wexp[l == 0 ? 2 : 1];
+            layer_mm<2, NT, MT, RS, true>(l == 0 ? a.W3T : a.W2T, l == 0 ? a.out_tiles : a.h2_tiles, sh, act, wave, lane, acc);
+            float c[NT];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[3 + l], 16 * n + j, we);
+            layer_out<2, NT, MT, RS>(acc, sh, act, s_max[4 + l], wave, lane, [&](auto slotc, int, int n, f4& z) {
+                constexpr int slot = decltype(slotc)::value;
+                float cn;
+                if constexpr (slot < MT) cn = c[n];
+                else cn = unscale<2>(s_max[3 + l], 16 * n + j, we);
+                const unsigned bits = mask[1 - l][slot] >> (slot < MT ? 4 * n : 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = z[r] * cn * ((bits >> r) & 1u ? 1.f : slope);
+            });
         });
-        // the next staging writes X only, which no wave reads after delta3 has
-        // been consumed (the barrier after delta2 orders that)
+        // g = (W1^T delta1) ./ std
+        const Share<NT> sh(in_tiles, wave, false);
+        layer_mm<2, NT, MT, RS, false>(a.W1T, a.h1_tiles, sh, act, wave, lane, acc);
+        if (sh.cnt > 0) {                      // at most eight input tiles: one per wave
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const int pj = 16 * n + j;
+                const float c = unscale<2>(s_max[5], pj, a.wexp[0]);
+                if (pj >= rows) continue;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = 16 * wave + 4 * g + r;
+                    if (k < n_in) g_out[(p0 + pj) * n_in + k] = acc.t[0][n][r] * c * a.in_rstd[k];
+                }
+            }
+        }
+        __syncthreads();                       // every wave has read the activation tile
     }
 }
 
-size_t mlp_vjp_lds_bytes(const MlpArgs& a) {
-    using P = Prec<0>;
-    const int x = a.in_pad > a.out_tiles * 16 ? a.in_pad : a.out_tiles * 16;
-    return sizeof(float) * 32 * ((size_t)P::stride(a.h1_tiles * 16) + P::stride(a.h2_tiles * 16) + P::stride(x));
+// The widths the call accepts: 32 points' FP32 activations of both hidden
+// layers and of the wider of input and output (rows padded to 64 units and 8)
+// within the LDS of one block.
+bool mlp_vjp_supported(const MlpArgs& a) {
+    auto row = [](int w) { return (size_t)((w + 63) / 64) * 64 + 8; };
+    return sizeof(float) * 32 * (row(a.h1_tiles * 16) + row(a.h2_tiles * 16) + row(std::max(a.in_pad, a.out_tiles * 16))) <=
+           kMlpLdsBudget;
 }
 
+template <int NT, int MT, int RS>
+static hipError_t launch_vjp_n(hipStream_t s, const MlpArgs& a, const float* B, const float* v, int64_t n_pts,
+                               float* g_out, int n_blocks) {
+    constexpr size_t lds = ActTile<2, NT, RS>::kBytes;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_vjp<NT, MT, RS>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((k_mlp_vjp<NT, MT, RS>), dim3(n_blocks), dim3(kWaves * 64), lds, s, a, B, v, n_pts, g_out);
+    return hipGetLastError();
+}
+
+// Point tiles per block by the rule of the network kernel.
 hipError_t launch_mlp_vjp(hipStream_t s, const MlpArgs& a, const float* B, const float* v, int64_t n_pts,
                           float* g_out) {
     if (n_pts <= 0) return hipSuccess;
-    if (a.precision != 0 || !a.W1T || !a.W2T || !a.W3T) return hipErrorInvalidValue;
-    const size_t lds = mlp_vjp_lds_bytes(a);
-    if (lds > kMlpLdsBudget) return hipErrorInvalidValue;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_vjp<2>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const int64_t it = (n_pts + 31) / 32;
-    const int n_blocks = (int)(it < kMlpBlocks ? it : kMlpBlocks);
-    hipLaunchKernelGGL(k_mlp_vjp<2>, dim3(n_blocks), dim3(kWaves * 64), lds, s, a, B, v, n_pts, g_out);
-    return hipGetLastError();
+    if (a.precision != 0 || !a.W1T || !a.W2T || !a.W3T || !mlp_vjp_supported(a)) return hipErrorInvalidValue;
+    const int nb = mlp_blocks(n_pts), nt = mlp_point_tiles(a, n_pts, nb);
+    if (mlp_rows_wide(a)) {
+        if (nt == 4) return launch_vjp_n<4, 3, kRowWide>(s, a, B, v, n_pts, g_out, nb);
+        return launch_vjp_n<2, 3, kRowWide>(s, a, B, v, n_pts, g_out, nb);
+    }
+    if (nt == 4) return launch_vjp_n<4, 4, kRowMax>(s, a, B, v, n_pts, g_out, nb);
+    return launch_vjp_n<2, 4, kRowMax>(s, a, B, v, n_pts, g_out, nb);
 }
 
 }  // namespace mala
