@@ -256,11 +256,11 @@ mala_status mala_integrate(mala_ctx* ctx, const float* ldos, int64_t n_pts, doub
 /* mala_integrate for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * same arguments, kernels and results (bit for bit) as mala_integrate, but
- * its scratch (2048 FP64 partial rows of 256 energies plus 256 FP64 weights,
- * 4 MiB + 2 KiB) is a fixed device array of the library, one per GPU, held
+ * its scratch (512 FP64 partial rows of 256 energies plus 256 FP64 weights,
+ * 1 MiB + 2 KiB) is a fixed device array of the library, one per GPU, held
  * until the process ends and looked up once per device by mala_create.  It
  * calls no hipMalloc/hipFree and records no profiling events.  Every n_pts
- * fits (points are split over at most 2048 partial rows); eg->n above 256 is
+ * fits (points are split over at most 512 partial rows); eg->n above 256 is
  * rejected (MALA_E_UNSUPPORTED) as in mala_integrate.  All calls on one GPU
  * share that scratch: calls that overlap on one GPU (different streams or
  * contexts without ordering between them) race and give wrong results.     */

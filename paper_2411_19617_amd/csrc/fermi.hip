@@ -30,22 +30,32 @@ namespace mala {
 constexpr double kPi = 3.14159265358979323846;
 
 // Li_s(-y), s in {2, 3}, 0 <= y <= 1.  coef: [2][kLiTerms] Taylor
-// coefficients at y = 1, then [2][kLiPow] inverse powers 1/k^s.
-__device__ double li_neg(int s, double y, const double* __restrict__ coef) {
+// coefficients at y = 1, then [2][kLiPow] inverse powers 1/k^s, in LDS: every
+// lane reads the same one, and a global read per term had made each of the
+// some fifty dependent terms wait for the cache.  The series runs four terms
+// at a time until the last of them no longer counts.
+__device__ double li_neg(int s, double y, const double* coef) {
     if (y <= 0.5) {
+        static_assert(kLiPow % 4 == 1, "whole groups of four terms after k = 0");
         const double* ik = coef + 2 * kLiTerms + (s - 2) * kLiPow;
         double term = -y, sum = 0.0;
-        for (int k = 1; k < kLiPow; ++k) {
-            const double t = term * ik[k];
+        for (int k = 1; k < kLiPow; k += 4) {
+            const double c0 = ik[k], c1 = ik[k + 1], c2 = ik[k + 2], c3 = ik[k + 3];
+            const double t1 = term * -y, t2 = t1 * -y, t3 = t2 * -y;
+            sum += term * c0;
+            sum += t1 * c1;
+            sum += t2 * c2;
+            const double t = t3 * c3;
             sum += t;
             if (fabs(t) <= 1e-18 * fabs(sum)) break;
-            term *= -y;
+            term = t3 * -y;
         }
         return sum;
     }
     const double t = log(y);                    // in (-ln 2, 0]
     const double* c = coef + (s - 2) * kLiTerms;
     double acc = c[kLiTerms - 1];
+#pragma unroll 8
     for (int n = kLiTerms - 2; n >= 0; --n) acc = acc * t + c[n];
     return acc;
 }
@@ -86,46 +96,65 @@ __device__ void gfun(double x, const double* coef, bool final, double& g0, doubl
     if (!final) g2 = s0 = s1 = 0.0;
 }
 
-// Fixed-shape sum over the 256 threads: butterfly inside each wave, then the
-// four wave sums in order.
-__device__ double block_sum(double v, double* red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+// Fixed-shape sums of two values over each group of 256 threads: butterflies
+// inside each wave, then the four wave sums in order.
+__device__ void block_sum2(double& a, double& b, double* red) {
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        b += __shfl_xor(b, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[2 * ((threadIdx.x >> 6) & 3)] = a;
+        red[2 * ((threadIdx.x >> 6) & 3) + 1] = b;
+    }
     __syncthreads();
-    const double r = (red[0] + red[1]) + (red[2] + red[3]);
+    a = (red[0] + red[2]) + (red[4] + red[6]);
+    b = (red[1] + red[3]) + (red[5] + red[7]);
     __syncthreads();
-    return r;
 }
 
+// What one group of 256 threads holds of an evaluation at its Fermi level.
+struct FermiEval {
+    double red[8], g0[256], g1[256], g2[256], f[256], s0[256], s1[256];
+};
+
 struct FermiShared {
-    double D[256], red[256], g0[256], g1[256], g2[256], f[256], cum[256], s0[256], s1[256];
+    double D[256], cum[4];
     double mu0;
     int first;
 };
 
+// Threads of k_fermi: the sum of the partial rows is 256 columns wide and waits
+// on memory, so four groups of threads each take a quarter of the rows with
+// sixteen reads in flight (one group with eight: 32 us for 256 rows, the
+// latency of 32 dependent rounds; now about 6).  Three groups then evaluate the
+// two ends of the energy grid and the start of the root search at once; the
+// rest of the solve is the first group's.
+constexpr int kFermiThreads = 1024;
+
 // Antiderivatives and f at every grid point for Fermi level mu (one per thread).
-__device__ void grid_g(FermiShared& sh, int n_e, double e0, double de, double mu, double kT, const double* coef,
+__device__ void grid_g(FermiEval& ev, int n_e, double e0, double de, double mu, double kT, const double* coef,
                        bool final) {
-    const int e = threadIdx.x;
+    const int e = threadIdx.x & 255;
     if (e < n_e) {
         double g0, g1, g2, f, s0, s1;
         gfun((e0 + e * de - mu) / kT, coef, final, g0, g1, g2, f, s0, s1);
-        sh.g0[e] = g0;
-        sh.g1[e] = g1;
-        sh.g2[e] = g2;
-        sh.f[e] = f;
-        sh.s0[e] = s0;
-        sh.s1[e] = s1;
+        ev.g0[e] = g0;
+        ev.g1[e] = g1;
+        ev.g2[e] = g2;
+        ev.f[e] = f;
+        ev.s0[e] = s0;
+        ev.s1[e] = s1;
     }
     __syncthreads();
 }
 
 // Hat-piece integrals over interval i = [e_i, e_i + de] from the shared G's:
 // wl = int f (1-t), wr = int f t; vl, vr the same with f*e.
-__device__ void interval(const FermiShared& sh, int i, double e0, double de, double mu, double kT, double& wl,
+__device__ void interval(const FermiEval& ev, int i, double e0, double de, double mu, double kT, double& wl,
                          double& wr, double& vl, double& vr) {
     const double xa = (e0 + i * de - mu) / kT, D = de / kT;
-    const double d0 = sh.g0[i + 1] - sh.g0[i], d1 = sh.g1[i + 1] - sh.g1[i], d2 = sh.g2[i + 1] - sh.g2[i];
+    const double d0 = ev.g0[i + 1] - ev.g0[i], d1 = ev.g1[i + 1] - ev.g1[i], d2 = ev.g2[i + 1] - ev.g2[i];
     const double I0 = d0 * kT;
     const double I1 = (d1 - xa * d0) * kT / D;
     const double K0 = d1 * kT;
@@ -138,42 +167,42 @@ __device__ void interval(const FermiShared& sh, int i, double e0, double de, dou
 
 // N(mu) and dN/dmu.  On [a, b] with t = (e-a)/de, int (-df/de) = f(a) - f(b)
 // and int t (-df/de) = (kT/de)(G0(xb) - G0(xa)) - f(b).
-__device__ void electrons(FermiShared& sh, int n_e, double e0, double de, double mu, double kT,
+__device__ void electrons(const FermiShared& sh, FermiEval& ev, int n_e, double e0, double de, double mu, double kT,
                           const double* coef, double& n, double& dn) {
-    grid_g(sh, n_e, e0, de, mu, kT, coef, false);
-    const int e = threadIdx.x;
-    double c = 0.0, dc = 0.0;
+    grid_g(ev, n_e, e0, de, mu, kT, coef, false);
+    const int e = threadIdx.x & 255;
+    n = dn = 0.0;
     if (e < n_e - 1) {
         double wl, wr, vl, vr;
-        interval(sh, e, e0, de, mu, kT, wl, wr, vl, vr);
-        c = wl * sh.D[e] + wr * sh.D[e + 1];
-        const double P = sh.f[e] - sh.f[e + 1];
-        const double Q = kT / de * (sh.g0[e + 1] - sh.g0[e]) - sh.f[e + 1];
-        dc = (P - Q) * sh.D[e] + Q * sh.D[e + 1];
+        interval(ev, e, e0, de, mu, kT, wl, wr, vl, vr);
+        n = wl * sh.D[e] + wr * sh.D[e + 1];
+        const double P = ev.f[e] - ev.f[e + 1];
+        const double Q = kT / de * (ev.g0[e + 1] - ev.g0[e]) - ev.f[e + 1];
+        dn = (P - Q) * sh.D[e] + Q * sh.D[e + 1];
     }
-    n = block_sum(c, sh.red);
-    dn = block_sum(dc, sh.red);
+    block_sum2(n, dn, ev.red);
 }
 
 // Zero-temperature root of int_{e0}^{mu} D = n_target for the piecewise-linear
-// D (a block scan of the trapezoids, then the quadratic on the crossing
-// interval); the midpoint of the grid if the count never crosses.
+// D (a scan of the trapezoids, then the quadratic on the crossing interval);
+// the midpoint of the grid if the count never crosses.
 __device__ double zero_t_root(FermiShared& sh, int n_e, double e0, double de, double n_target) {
-    const int e = threadIdx.x;
+    const int e = threadIdx.x & 255;
     const double piece = e < n_e - 1 ? 0.5 * de * (sh.D[e] + sh.D[e + 1]) : 0.0;
-    sh.cum[e] = piece;
-    if (e == 0) sh.mu0 = e0 + 0.5 * (n_e - 1) * de;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {          // inclusive scan
-        const double v = e >= off ? sh.cum[e - off] : 0.0;
-        __syncthreads();
-        sh.cum[e] += v;
-        __syncthreads();
+    double scan = piece;                               // inclusive over the wave, then the waves before it
+    for (int off = 1; off < 64; off <<= 1) {
+        const double v = __shfl_up(scan, off, 64);
+        if ((e & 63) >= off) scan += v;
     }
-    const double after = sh.cum[e], before = after - piece;
-    const bool cross = e < n_e - 1 && before <= n_target && n_target < after;
-    if (e == 0) sh.first = n_e;
+    if ((e & 63) == 63) sh.cum[e >> 6] = scan;
+    if (e == 0) {
+        sh.mu0 = e0 + 0.5 * (n_e - 1) * de;
+        sh.first = n_e;
+    }
     __syncthreads();
+    for (int w = 0; w < (e >> 6); ++w) scan += sh.cum[w];
+    const double after = scan, before = after - piece;
+    const bool cross = e < n_e - 1 && before <= n_target && n_target < after;
     if (cross) atomicMin(&sh.first, e);               // lowest crossing interval
     __syncthreads();
     if (e == sh.first) {
@@ -189,34 +218,62 @@ __device__ double zero_t_root(FermiShared& sh, int n_e, double e0, double de, do
 
 // mode 0: exact solve (DOS, result, weights; window coverage if win != NULL)
 // mode 1: estimate from a subsample -> energy window for the stored LDOS
-__global__ __launch_bounds__(256) void k_fermi(const double* __restrict__ partials, int n_parts, int n_e,
+__global__ __launch_bounds__(kFermiThreads) void k_fermi(const double* __restrict__ partials, int n_parts, int n_e,
                                                double dV, double e0, double de, double kT, double n_target,
                                                double* __restrict__ dos_out, double* __restrict__ w_out,
                                                ResultRec* __restrict__ res, WindowRec* __restrict__ win,
-                                               const double* __restrict__ coef, int mode, int w_max,
+                                               const double* __restrict__ coef_g, int mode, int w_max,
                                                double margin, const int* __restrict__ cap_err) {
     __shared__ FermiShared sh;
-    const int e = threadIdx.x;
+    __shared__ double s_sum[kFermiThreads / 256][256];
+    __shared__ double coef[kLiCoef];
+    __shared__ FermiEval evs[3];
+    __shared__ double s_ends[2];
+    const int e = threadIdx.x & 255, group = threadIdx.x >> 8;
+    constexpr int G = kFermiThreads / 256, U = 16;
+    {
+        // sixteen running sums per thread, combined in a fixed order
+        double acc[U] = {};
+        const int w_end = (int)((int64_t)n_parts * (group + 1) / G);
+        int w = (int)((int64_t)n_parts * group / G);
+        for (; w + U <= w_end; w += U) {
+#pragma unroll
+            for (int q = 0; q < U; ++q) acc[q] += partials[(size_t)(w + q) * kMlpMaxOut + e];
+        }
+        double v[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) v[q] = w + q < w_end ? partials[(size_t)(w + q) * kMlpMaxOut + e] : 0.0;
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc[q] += v[q];
+#pragma unroll
+        for (int h = U / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int q = 0; q < h; ++q) acc[q] += acc[q + h];
+        s_sum[group][e] = acc[0];
+        for (int i = threadIdx.x; i < kLiCoef; i += kFermiThreads) coef[i] = coef_g[i];
+    }
+    __syncthreads();
     double d = 0.0;
     if (e < n_e) {
-        // eight independent running sums (loads in flight), combined in a fixed order
-        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        int w = 0;
-        for (; w + 8 <= n_parts; w += 8) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] += partials[(size_t)(w + q) * kMlpMaxOut + e];
-        }
-        for (; w < n_parts; ++w) acc[0] += partials[(size_t)w * kMlpMaxOut + e];
-        d = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-        d *= dV;
-        if (mode == 0) dos_out[e] = d;
+        d = ((s_sum[0][e] + s_sum[1][e]) + (s_sum[2][e] + s_sum[3][e])) * dV;
+        if (mode == 0 && group == 0) dos_out[e] = d;
     }
-    sh.D[e] = d;
+    if (group == 0) sh.D[e] = d;
     __syncthreads();
     const double elast = e0 + (n_e - 1) * de;
-    double nlo, nhi, dn;
-    electrons(sh, n_e, e0, de, e0, kT, coef, nlo, dn);
-    electrons(sh, n_e, e0, de, elast, kT, coef, nhi, dn);
+    double mu = zero_t_root(sh, n_e, e0, de, n_target);
+    double n, dn;
+    FermiEval& ev = evs[group < 3 ? group : 0];
+    {
+        // the start of the search, the first and the last energy; the fourth
+        // group repeats the first's values into the same places
+        const double at = group == 1 ? e0 : group == 2 ? elast : mu;
+        electrons(sh, ev, n_e, e0, de, at, kT, coef, n, dn);
+    }
+    if (e == 0 && (group == 1 || group == 2)) s_ends[group - 1] = n;
+    __syncthreads();
+    const double nlo = s_ends[0], nhi = s_ends[1];
+    if (group > 0) return;                     // whole waves: the rest is the first group's
     const bool ok = nlo <= n_target && n_target <= nhi;
     if (!ok) {
         if (e == 0) {
@@ -244,11 +301,9 @@ __global__ __launch_bounds__(256) void k_fermi(const double* __restrict__ partia
     }
     const double tol = mode == 0 ? 1e-12 : 1e-6;
     double lo = e0, hi = elast;
-    double mu = zero_t_root(sh, n_e, e0, de, n_target);
     int it = 0;
     while (it < 200) {
-        double n;
-        electrons(sh, n_e, e0, de, mu, kT, coef, n, dn);
+        if (it > 0) electrons(sh, ev, n_e, e0, de, mu, kT, coef, n, dn);      // at the start: done above
         ++it;
         if (n == n_target) break;                       // mu is the root
         if (n < n_target) lo = mu;
@@ -280,32 +335,32 @@ __global__ __launch_bounds__(256) void k_fermi(const double* __restrict__ partia
         }
         return;
     }
-    grid_g(sh, n_e, e0, de, ef, kT, coef, true);
+    grid_g(ev, n_e, e0, de, ef, kT, coef, true);
     double wl = 0, wr = 0, vl = 0, vr = 0, sc = 0;
     if (e < n_e - 1) {
-        interval(sh, e, e0, de, ef, kT, wl, wr, vl, vr);
+        interval(ev, e, e0, de, ef, kT, wl, wr, vl, vr);
         // entropy (Eq. electronicentropyDOS) on the same hat pieces: int s,
         // int s t over the interval, t = (x - xa)/D
         const double xa = (e0 + e * de - ef) / kT, xb = (e0 + (e + 1) * de - ef) / kT, D = de / kT;
-        double d0 = sh.s0[e + 1] - sh.s0[e];
+        double d0 = ev.s0[e + 1] - ev.s0[e];
         if (xa <= 0.0 && xb > 0.0) d0 += kPi * kPi / 3.0;
-        const double J0 = d0 * kT, J1 = (sh.s1[e + 1] - sh.s1[e] - xa * d0) * kT / D;
+        const double J0 = d0 * kT, J1 = (ev.s1[e + 1] - ev.s1[e] - xa * d0) * kT / D;
         sc = (J0 - J1) * sh.D[e] + J1 * sh.D[e + 1];
     }
-    const double s_kb = block_sum(sc, sh.red);
     __syncthreads();
     // reuse the g arrays for the per-interval pieces
-    sh.g0[e] = wr;
-    sh.g1[e] = vr;
+    ev.g0[e] = wr;
+    ev.g1[e] = vr;
     __syncthreads();
     double we = 0.0, ve = 0.0;
     if (e < n_e) {
         if (e < n_e - 1) { we += wl; ve += vl; }
-        if (e >= 1) { we += sh.g0[e - 1]; ve += sh.g1[e - 1]; }
+        if (e >= 1) { we += ev.g0[e - 1]; ve += ev.g1[e - 1]; }
         w_out[e] = we;
     }
-    const double nf = block_sum(we * sh.D[e], sh.red);
-    const double eb = block_sum(ve * sh.D[e], sh.red);
+    double nf = we * sh.D[e], eb = ve * sh.D[e], s_kb = sc, unused = 0.0;
+    block_sum2(nf, eb, ev.red);
+    block_sum2(s_kb, unused, ev.red);
     if (e == 0) {
         res->e_fermi = ef;
         res->e_band = eb;
@@ -383,19 +438,41 @@ __global__ __launch_bounds__(256) void k_density_window(const double* __restrict
 }
 
 // Column sums of a stored LDOS [n][n_e] into FP64 partial rows, one per block
-// over a fixed contiguous range of points.
-__global__ __launch_bounds__(256) void k_ldos_colsum(const float* __restrict__ ldos, int64_t n_pts, int n_e,
-                                                     double* __restrict__ partials, int n_blocks) {
-    const int e = threadIdx.x;
+// over a fixed contiguous range of points.  Thread = (energy, row group): four
+// groups take every fourth row with eight reads in flight each and are combined
+// in a fixed order, so that few blocks (and few partial rows for the Fermi
+// kernel, which one block sums) keep the memory busy.
+constexpr int kColThreads = 1024;
+__global__ __launch_bounds__(kColThreads) void k_ldos_colsum(const float* __restrict__ ldos, int64_t n_pts, int n_e,
+                                                             double* __restrict__ partials, int n_blocks) {
+    constexpr int G = kColThreads / 256, U = 8;
+    __shared__ double s_sum[G][256];
+    const int e = threadIdx.x & 255, group = threadIdx.x >> 8;
     const int64_t b = blockIdx.x;
     const int64_t p_begin = n_pts * b / n_blocks, p_end = n_pts * (b + 1) / n_blocks;
     double s = 0.0;
-    if (e < n_e)
-        for (int64_t p = p_begin; p < p_end; ++p) s += (double)ldos[p * n_e + e];
-    partials[b * kMlpMaxOut + e] = e < n_e ? s : 0.0;
+    if (e < n_e) {
+        const float* col = ldos + e;
+        int64_t p = p_begin + group;
+        for (; p + (U - 1) * G < p_end; p += U * G) {
+            float v[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) v[q] = col[(p + q * G) * n_e];
+#pragma unroll
+            for (int q = 0; q < U; ++q) s += (double)v[q];
+        }
+        for (; p < p_end; p += G) s += (double)col[p * n_e];
+    }
+    s_sum[group][e] = s;
+    __syncthreads();
+    if (group == 0) partials[b * kMlpMaxOut + e] = (s_sum[0][e] + s_sum[1][e]) + (s_sum[2][e] + s_sum[3][e]);
 }
 
-// n(p) = sum_e w_e d_e(p), one wave per point (grid-stride).
+// n(p) = sum_e w_e d_e(p), one wave per four points at a time: sixteen reads in
+// flight, and the four sums over the lanes share their butterfly (two steps that
+// halve the values a lane holds, then four on one value).  The points run
+// backwards: the column sums read the rows forwards just before, so the last
+// ones are the ones still in the memory-side cache.
 __global__ __launch_bounds__(256) void k_density_ldos(const float* __restrict__ ldos, int64_t n_pts, int n_e,
                                                       const double* __restrict__ w,
                                                       const ResultRec* __restrict__ res,
@@ -403,22 +480,47 @@ __global__ __launch_bounds__(256) void k_density_ldos(const float* __restrict__ 
     if (res->status != 0) return;
     const int lane = threadIdx.x & 63;
     double wr[4];
-    for (int q = 0; q < 4; ++q) wr[q] = (lane + 64 * q < n_e) ? w[lane + 64 * q] : 0.0;
-    for (int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); p < n_pts; p += (int64_t)gridDim.x * 4) {
-        double s = 0.0;
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane + 64 * q;
-            if (e < n_e) s += wr[q] * (double)ldos[p * n_e + e];
+    int off[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = lane + 64 * q;
+        wr[q] = e < n_e ? w[e] : 0.0;
+        off[q] = e < n_e ? e : n_e - 1;        // in range; its weight is zero
+    }
+    const int64_t quads = (n_pts + 3) / 4;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < quads; i += (int64_t)gridDim.x * 4) {
+        const int64_t p0 = (quads - 1 - i) * 4;
+        float v[4][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float* row = ldos + (p0 + r < n_pts ? p0 + r : n_pts - 1) * n_e;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[r][q] = row[off[q]];
         }
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (lane == 0) dens[p] = s;
+        double s[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s[r] = 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (lane + 64 * q < n_e) s[r] += wr[q] * (double)v[r][q];
+        }
+        // lanes with bit 5 keep points 2, 3; with bit 4 the odd one of their two
+        const bool h5 = lane & 32, h4 = lane & 16;
+        const double a0 = (h5 ? s[2] : s[0]) + __shfl_xor(h5 ? s[0] : s[2], 32, 64);
+        const double a1 = (h5 ? s[3] : s[1]) + __shfl_xor(h5 ? s[1] : s[3], 32, 64);
+        double t = (h4 ? a1 : a0) + __shfl_xor(h4 ? a0 : a1, 16, 64);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+        const int64_t p = p0 + (h5 ? 2 : 0) + (h4 ? 1 : 0);
+        if ((lane & 15) == 0 && p < n_pts) dens[p] = t;
     }
 }
 
 hipError_t launch_fermi(hipStream_t s, const double* partials, int n_parts, int n_e, double dV, double e0,
                         double de, double kT, double n_target, double* dos_out, double* weights_out,
                         void* result, WindowRec* win, const double* li_coef, const int* cap_err) {
-    hipLaunchKernelGGL(k_fermi, dim3(1), dim3(256), 0, s, partials, n_parts, n_e, dV, e0, de, kT, n_target,
+    hipLaunchKernelGGL(k_fermi, dim3(1), dim3(kFermiThreads), 0, s, partials, n_parts, n_e, dV, e0, de, kT, n_target,
                        dos_out, weights_out, static_cast<ResultRec*>(result), win, li_coef, 0, 0, 0.0, cap_err);
     return hipGetLastError();
 }
@@ -426,7 +528,7 @@ hipError_t launch_fermi(hipStream_t s, const double* partials, int n_parts, int 
 hipError_t launch_fermi_estimate(hipStream_t s, const double* partials, int n_parts, int n_e, double dV,
                                  double e0, double de, double kT, double n_target, WindowRec* win,
                                  const double* li_coef, int w_max, double margin) {
-    hipLaunchKernelGGL(k_fermi, dim3(1), dim3(256), 0, s, partials, n_parts, n_e, dV, e0, de, kT, n_target,
+    hipLaunchKernelGGL(k_fermi, dim3(1), dim3(kFermiThreads), 0, s, partials, n_parts, n_e, dV, e0, de, kT, n_target,
                        nullptr, nullptr, nullptr, win, li_coef, 1, w_max, margin, nullptr);
     return hipGetLastError();
 }
@@ -456,14 +558,14 @@ hipError_t launch_density_window(hipStream_t s, const double* prefix, const floa
 
 hipError_t launch_ldos_colsum(hipStream_t s, const float* ldos, int64_t n_pts, int n_e, double* partials,
                               int n_blocks) {
-    hipLaunchKernelGGL(k_ldos_colsum, dim3(n_blocks), dim3(256), 0, s, ldos, n_pts, n_e, partials, n_blocks);
+    hipLaunchKernelGGL(k_ldos_colsum, dim3(n_blocks), dim3(kColThreads), 0, s, ldos, n_pts, n_e, partials, n_blocks);
     return hipGetLastError();
 }
 
 hipError_t launch_density_from_ldos(hipStream_t s, const float* ldos, int64_t n_pts, int n_e,
                                     const double* weights, const void* result, double* density) {
-    int64_t blocks = (n_pts + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
+    int64_t blocks = (n_pts + 15) / 16;          // four waves of four points
+    if (blocks > 2048) blocks = 2048;
     if (blocks < 1) return hipSuccess;
     hipLaunchKernelGGL(k_density_ldos, dim3((unsigned)blocks), dim3(256), 0, s, ldos, n_pts, n_e, weights,
                        static_cast<const ResultRec*>(result), density);

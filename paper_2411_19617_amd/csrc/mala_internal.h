@@ -25,7 +25,7 @@ constexpr int kMlpMaxHidden = 512;   // hidden width limit
 constexpr int kMlpMaxOut = 256;      // output width limit
 // DOS partial rows of the stored-LDOS reductions (mala_integrate): one per
 // block over a fixed contiguous range of points, at most this many.
-constexpr int kIntegrateMaxParts = 2048;
+constexpr int kIntegrateMaxParts = 512;
 // fixed scratch of mala_integrate_noalloc: the partial rows and the weights
 constexpr int kNoallocScratchDoubles = kIntegrateMaxParts * kMlpMaxOut + kMlpMaxOut;
 constexpr double kBoltzmannEv = 8.617333262e-5;
@@ -386,7 +386,7 @@ hipError_t launch_dedr(hipStream_t s, int twojmax, const BinState& bins, const i
 void plan_y_units(int twojmax, int c_lo, int c_hi, int n_waves, int* wave_units, int stride);
 void plan_zb_waves(int twojmax, int n_waves, int* wave_triples, int stride);
 constexpr int kLiTerms = 32;
-constexpr int kLiPow = 64;
+constexpr int kLiPow = 65;
 constexpr int kLiCoef = 2 * kLiTerms + 2 * kLiPow;
 void polylog_coefficients(double* coef);   // [kLiCoef]: Taylor coefficients at y=1, inverse powers
 
