@@ -1,20 +1,8 @@
 // Grid bispectrum descriptors on gfx950 (Sec. 3.2.2: Eqs. ionicdensity,
 // SNAPExpansion and the triple products that give B(r, j), Eq. snap_dim).
 //
-// Two kernels per tile of 64 consecutive grid points (one point per lane):
-//
-//  k_ui  -- neighbour gather and the expansion coefficients
-//           u^J = I + sum_k f_c(r_k) U^J(g_k).  U^J is the spin-J/2 irrep of
-//           g written as a polynomial action on (xi, eta); its unnormalised
-//           coefficients are products of powers of a, b and their conjugates.
-//           The rows that share J-ma form independent chains: the first row
-//           of a chain comes from powers of b and f_c conj(a), each later row
-//           from the previous one (one more factor), and everything is
-//           normalised once after the neighbour sum.  The chains are split
-//           over the waves of the block so that each wave keeps its share of
-//           u in registers over the whole neighbour loop.  Only rows
-//           ma <= J/2 are formed; the rest follow from
-//           u_{J-ma,J-mb} = (-1)^(ma-mb) conj(u_{ma,mb}).
+// The second of two kernels per tile of 64 consecutive grid points (one point
+// per lane), after k_ui (ui.hip):
 //
 //  k_zb  -- the tile's half-u (271 complex per point at twojmax 10, 139 KB
 //           for 64 points) is staged in LDS; every wave of the block owns a
@@ -32,216 +20,8 @@
 #include <mutex>
 
 #include "snap_core.h"
-#include "tile_gather.h"
 
 namespace mala {
-
-// Accumulate f_c * c(g) of one neighbour into the group's registers, where
-// c^J[ma][mb] is the coefficient of xi^mb eta^(J-mb) in
-// (a xi - conj(b) eta)^ma (b xi + conj(a) eta)^(J-ma); U^J = N c^J with
-// N = sqrt(mb! (J-mb)! / (ma! (J-ma)!)) applied once at write-out.
-// Row 0 of level q is binom(q, mb) b^mb conj(a)^(q-mb) (from powers of b
-// and f_c conj(a) shared by the group's chains); the later rows of a chain
-// follow from multiplying by one more factor:
-//   row k:   c^J[k][mb]  = a c^{J-1}[k-1][mb-1] - conj(b) c^{J-1}[k-1][mb]
-// and the chain's last row is summed into the accumulators directly.
-template <int TJ, int G, int NACC>
-__device__ __forceinline__ void ui_neighbour(float ar, float ai, float br, float bi, float fc,
-                                             float (&accr)[NACC], float (&acci)[NACC]) {
-    constexpr int QMAX = group_qmax(TJ, G);
-    float pbr[QMAX + 1], pbi[QMAX + 1], par[QMAX + 1], pai[QMAX + 1];   // b^k, fc conj(a)^k
-    par[0] = fc;
-    pai[0] = 0.f;
-    static_for<1, QMAX + 1>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        if constexpr (k == 1) {
-            pbr[1] = br;
-            pbi[1] = bi;
-            par[1] = fc * ar;
-            pai[1] = -fc * ai;
-        } else {
-            pbr[k] = fmaf(pbr[k - 1], br, -pbi[k - 1] * bi);
-            pbi[k] = fmaf(pbr[k - 1], bi, pbi[k - 1] * br);
-            par[k] = fmaf(par[k - 1], ar, pai[k - 1] * ai);
-            pai[k] = fmaf(pai[k - 1], ar, -par[k - 1] * ai);
-        }
-    });
-    static_for<0, TJ + 1>([&](auto qc) {
-        constexpr int Q = decltype(qc)::value;
-        if constexpr (in_group(TJ, G, Q)) {
-            constexpr int base = chain_slot(TJ, G, Q);
-            constexpr int NR = chain_rows(TJ, Q);
-            float cr[TJ + 1], ci[TJ + 1];
-            static_for<0, Q + 1>([&](auto mc) {
-                constexpr int mb = decltype(mc)::value;
-                constexpr float bin = (float)ce_binom(Q, mb);
-                float xr, xi;
-                if constexpr (mb == 0) {
-                    xr = par[Q];
-                    xi = pai[Q];
-                } else if constexpr (mb == Q) {
-                    xr = fc * pbr[Q];
-                    xi = fc * pbi[Q];
-                } else {
-                    xr = fmaf(pbr[mb], par[Q - mb], -pbi[mb] * pai[Q - mb]);
-                    xi = fmaf(pbr[mb], pai[Q - mb], pbi[mb] * par[Q - mb]);
-                }
-                if constexpr (bin != 1.f) {
-                    xr *= bin;
-                    xi *= bin;
-                }
-                cr[mb] = xr;
-                ci[mb] = xi;
-                accr[base + mb] += xr;
-                if constexpr (Q > 0) acci[base + mb] += xi;     // level 0 is the real f_c
-            });
-            static_for<1, NR>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                constexpr int Jp = Q + k;
-                constexpr int rb = base + row_slot(Q, k);
-                if constexpr (k == NR - 1) {
-                    static_for<0, Jp + 1>([&](auto mc) {
-                        constexpr int mb = decltype(mc)::value;
-                        float sr = accr[rb + mb], si = acci[rb + mb];
-                        if constexpr (mb >= 1) {                // a * old[mb-1]
-                            sr = fmaf(ar, cr[mb - 1], sr);
-                            sr = fmaf(-ai, ci[mb - 1], sr);
-                            si = fmaf(ar, ci[mb - 1], si);
-                            si = fmaf(ai, cr[mb - 1], si);
-                        }
-                        if constexpr (mb <= Jp - 1) {           // - conj(b) * old[mb]
-                            sr = fmaf(-br, cr[mb], sr);
-                            sr = fmaf(-bi, ci[mb], sr);
-                            si = fmaf(-br, ci[mb], si);
-                            si = fmaf(bi, cr[mb], si);
-                        }
-                        accr[rb + mb] = sr;
-                        acci[rb + mb] = si;
-                    });
-                } else {
-                    static_for<0, Jp + 1>([&](auto ic) {
-                        constexpr int mb = Jp - decltype(ic)::value;   // in place, high mb first
-                        float nr = 0.f, ni = 0.f;
-                        if constexpr (mb >= 1) {                // a * old[mb-1]
-                            const float orr = cr[mb - 1], oi = ci[mb - 1];
-                            nr = fmaf(ar, orr, -ai * oi);
-                            ni = fmaf(ar, oi, ai * orr);
-                        }
-                        if constexpr (mb <= Jp - 1) {           // - conj(b) * old[mb]
-                            const float orr = cr[mb], oi = ci[mb];
-                            nr = fmaf(-br, orr, fmaf(-bi, oi, nr));
-                            ni = fmaf(-br, oi, fmaf(bi, orr, ni));
-                        }
-                        cr[mb] = nr;
-                        ci[mb] = ni;
-                    });
-                    static_for<0, Jp + 1>([&](auto mc) {
-                        constexpr int mb = decltype(mc)::value;
-                        accr[rb + mb] += cr[mb];
-                        acci[rb + mb] += ci[mb];
-                    });
-                }
-            });
-        }
-    });
-}
-
-template <int TJ>
-__global__ __launch_bounds__(64 * n_groups(TJ), 2) void k_ui(BinState bins, int Nx, int Ny, int Nz,
-                                                          double rcut, int64_t pt_begin, int64_t n_pts,
-                                                          float2* __restrict__ u_out,
-                                                          int* __restrict__ err) {
-    constexpr int NG = n_groups(TJ);
-    constexpr int NH = n_half(TJ);
-    __shared__ float4 cand[kMaxCand];
-    __shared__ unsigned short nbr[kMaxNbr][kTile];
-    __shared__ int nnbr[kTile];
-    __shared__ int scan_tmp[16];
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t tile = blockIdx.x;
-    const int64_t idx = tile * kTile + lane;
-    const bool valid = idx < n_pts;
-    const int64_t p = pt_begin + (valid ? idx : tile * kTile);
-    const int64_t pk = p % Nz, pj = (p / Nz) % Ny, pi = p / ((int64_t)Ny * Nz);
-    const double rx = (double)pi * bins.L[0] / Nx, ry = (double)pj * bins.L[1] / Ny,
-                 rz = (double)pk * bins.L[2] / Nz;
-    const int64_t p0 = pt_begin + tile * kTile;
-    // bounding boxes of the tile's points
-    const TileBoxes boxes = tile_boxes(p, p0, Ny, Nz, rx, ry, rz);
-
-    // ---- candidate atom images within rcut of the boxes, in a fixed order
-    int n0;
-    const int base = gather_candidates(bins, boxes, rcut, cand, kMaxCand, scan_tmp, &n0);
-    if (base > kMaxCand && threadIdx.x == 0) atomicOr(err, kErrCand);
-    const int ncand = base < kMaxCand ? base : kMaxCand;
-    __syncthreads();
-
-    // ---- per-point neighbour lists (wave 0), in candidate order
-    const PointFrame frame = point_frame(boxes, n0, rx, ry, rz);
-    const float rcf = (float)rcut;
-    if (wave == 0) build_neighbour_lists(cand, ncand, frame, rcf, valid, lane, nbr, nnbr, err);
-    __syncthreads();
-
-    // ---- expansion coefficients, this wave's chain group
-    static_for<0, NG>([&](auto gc) {
-        constexpr int G = decltype(gc)::value;
-        if (wave != G) return;
-        constexpr int NACC = group_size(TJ, G);
-        float accr[NACC], acci[NACC];
-        static_for<0, NACC>([&](auto ec) {
-            accr[decltype(ec)::value] = 0.f;
-            acci[decltype(ec)::value] = 0.f;
-        });
-        const int my_n = nnbr[lane];
-        const int n_iter = wave_max_int(my_n);
-        const float kpi = 3.14159265358979f;
-        // angle and cutoff phase per unit distance, formed once: a quotient
-        // per neighbour is a full-precision division (a dozen instructions)
-        const float kth = kRfac0 * kpi / rcf, kcut = kpi / rcf;
-        for (int s = 0; s < n_iter; ++s) {
-            float ar = 1.f, ai = 0.f, br = 0.f, bi = 0.f, fc = 0.f;
-            if (s < my_n) {
-                const int c = nbr[s][lane];
-                const float4 q = cand[c];
-                const float3 o = frame.at(c);
-                const float dx = q.x - o.x, dy = q.y - o.y, dz = q.z - o.z;
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                // 1/r and r from one hardware reciprocal square root (about
-                // 1 ulp; an atom on the point gives r = 0)
-                const float inv = r2 > kMinR2 ? __builtin_amdgcn_rsqf(r2) : 0.f;
-                const float r = r2 * inv;
-                float sn, cs;
-                sincosf(kth * r, &sn, &cs);
-                ar = cs;
-                ai = -dz * inv * sn;
-                br = -dy * inv * sn;
-                bi = -dx * inv * sn;
-                fc = 0.5f * (cosf(kcut * r) + 1.f);
-            }
-            ui_neighbour<TJ, G, NACC>(ar, ai, br, bi, fc, accr, acci);
-        }
-        // normalisation, self term (identity on the diagonal, N = 1 there), write-out
-        static_for<0, TJ + 1>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            if constexpr (in_group(TJ, G, q)) {
-                static_for<0, chain_rows(TJ, q)>([&](auto kc) {
-                    constexpr int k = decltype(kc)::value;
-                    constexpr int J = q + k;
-                    constexpr int rb = chain_slot(TJ, G, q) + row_slot(q, k);
-                    static_for<0, J + 1>([&](auto mc) {
-                        constexpr int mb = decltype(mc)::value;
-                        constexpr float nrm =
-                            (float)ce_sqrt(ce_fact(mb) * ce_fact(J - mb) / (ce_fact(k) * ce_fact(J - k)));
-                        constexpr int e = half_off(J) + k * (J + 1) + mb;
-                        const float re = nrm * accr[rb + mb] + (mb == k ? 1.f : 0.f);
-                        u_out[(tile * NH + e) * kTile + lane] = make_float2(re, nrm * acci[rb + mb]);
-                    });
-                });
-            }
-        });
-    });
-}
 
 // ------------------------------------------------------------------ Z / B
 // B(j1,j2,j) of the lane's point.  For each output column mb:
@@ -437,16 +217,6 @@ __global__ __launch_bounds__(768) void k_zb(const float2* __restrict__ u, int64_
 }
 
 template <int TJ>
-static hipError_t ui_tj(hipStream_t s, const BinState& bins, const int N[3], double rcut, int64_t pt_begin,
-                        int64_t n_pts, float2* u_scratch, int* err_flag) {
-    const int64_t n_tiles = (n_pts + kTile - 1) / kTile;
-    if (n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ui<TJ>, dim3((unsigned)n_tiles), dim3(64 * n_groups(TJ)), 0, s, bins, N[0], N[1],
-                       N[2], rcut, pt_begin, n_pts, u_scratch, err_flag);
-    return hipGetLastError();
-}
-
-template <int TJ>
 static hipError_t zb_tj(hipStream_t s, int64_t n_pts, const float2* u_scratch, float* B_out,
                         const float* cg_table, const int* cg_offsets, const int* wave_triples, int zb_waves) {
     const int64_t n_tiles = (n_pts + kTile - 1) / kTile;
@@ -463,18 +233,6 @@ static hipError_t zb_tj(hipStream_t s, int64_t n_pts, const float2* u_scratch, f
     hipLaunchKernelGGL(k_zb<TJ>, dim3((unsigned)n_tiles), dim3(64 * zb_waves), lds, s, u_scratch, n_pts, B_out,
                        cg_table, cg_offsets, wave_triples, kMaxZbStride);
     return hipGetLastError();
-}
-
-hipError_t launch_ui(hipStream_t s, int twojmax, const BinState& bins, const int N[3], double rcut,
-                     int64_t pt_begin, int64_t n_pts, float2* u_scratch, int* err_flag) {
-    switch (twojmax) {
-    case 2: return ui_tj<2>(s, bins, N, rcut, pt_begin, n_pts, u_scratch, err_flag);
-    case 4: return ui_tj<4>(s, bins, N, rcut, pt_begin, n_pts, u_scratch, err_flag);
-    case 6: return ui_tj<6>(s, bins, N, rcut, pt_begin, n_pts, u_scratch, err_flag);
-    case 8: return ui_tj<8>(s, bins, N, rcut, pt_begin, n_pts, u_scratch, err_flag);
-    case 10: return ui_tj<10>(s, bins, N, rcut, pt_begin, n_pts, u_scratch, err_flag);
-    default: return hipErrorInvalidValue;
-    }
 }
 
 hipError_t launch_zb(hipStream_t s, int twojmax, int64_t n_pts, const float2* u_scratch, float* B_out,

@@ -192,4 +192,46 @@ __device__ __forceinline__ void build_neighbour_lists(const float4* cand, int nc
     nnbr[lane] = valid ? (cnt < kMaxNbr ? cnt : kMaxNbr) : 0;
 }
 
+// The same lists by all NW waves of the block (called by all of them): wave w
+// takes the w-th part of the candidates, counts its hits per point, and writes
+// them behind those of the waves before it, so the order is the same.
+// Returns the lane's list length; a barrier has passed since the last write.
+template <int NW>
+__device__ __forceinline__ int build_neighbour_lists_block(const float4* cand, int ncand, const PointFrame& f, float rc,
+                                                           bool valid, int lane, int wave,
+                                                           unsigned short (*nbr)[kTile], int (*nnbr)[kTile], int* err) {
+    const int begin = ncand * wave / NW, end = ncand * (wave + 1) / NW;
+    const float rc2 = rc * rc;
+    auto scan = [&](auto&& hit) {
+        auto part = [&](int c0, int c1, float3 p) {
+            for (int c = c0; c < c1; ++c) {
+                const float4 q = cand[c];
+                const float dx = q.x - p.x, dy = q.y - p.y, dz = q.z - p.z;
+                if (dx * dx + dy * dy + dz * dz < rc2) hit(c);
+            }
+        };
+        const int split = min(max(f.n0, begin), end);
+        part(begin, split, f.p0);
+        part(split, end, f.p1);
+    };
+    int cnt = 0;
+    scan([&](int) { ++cnt; });
+    nnbr[wave][lane] = cnt;
+    __syncthreads();
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int c = nnbr[w][lane];
+        if (w < wave) at += c;
+        total += c;
+    }
+    scan([&](int c) {
+        if (at < kMaxNbr) nbr[at][lane] = (unsigned short)c;
+        ++at;
+    });
+    if (total > kMaxNbr && wave == 0) atomicOr(err, kErrNbr);
+    __syncthreads();
+    return valid ? min(total, kMaxNbr) : 0;
+}
+
 }  // namespace mala
