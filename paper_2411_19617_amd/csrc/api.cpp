@@ -757,42 +757,56 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
         return m > 0.f ? std::min(14 - ilogbf(m), 100) : 0;
     };
     const int we[3] = {bf ? 0 : scale_exponent(W1), bf ? 0 : scale_exponent(W2), bf ? 0 : scale_exponent(W3)};
-    std::vector<float> raw;                 // the three layers in FP32, packed on the device
-    raw.reserve(W1.size() + W2.size() + W3.size());
-    for (const std::vector<double>* W : {&W1, &W2, &W3})
-        for (double v : *W) raw.push_back((float)v);
-    auto padv = [](const std::vector<double>& v, int n) {
-        std::vector<float> o(n, 0.f);
-        for (size_t i = 0; i < v.size() && (int)i < n; ++i) o[i] = (float)v[i];
-        return o;
+    // every FP32 array in one upload, each on 256 bytes and zero-padded to its
+    // length on the device: the layers' weights (packed there), biases, scalers
+    std::vector<float> f32;
+    auto add = [&](const std::vector<double>& v, size_t n, auto&& value) {
+        const size_t at = (f32.size() + 63) / 64 * 64;
+        f32.resize(at + n, 0.f);
+        for (size_t i = 0; i < v.size() && i < n; ++i) f32[at + i] = value(v[i]);
+        return at;
     };
-    std::vector<float> pb1 = padv(b1, 16 * h1t), pb2 = padv(b2, 16 * h2t), pb3 = padv(b3, 16 * ot);
-    std::vector<float> pm = padv(mean, n_in), prs(n_in), psc = padv(osc, kMlpMaxOut), psh = padv(osh, kMlpMaxOut);
-    for (int i = 0; i < n_in; ++i) prs[i] = (float)(1.0 / sd[i]);
+    auto as_float = [](double v) { return (float)v; };
+    const size_t off_w[3] = {add(W1, W1.size(), as_float), add(W2, W2.size(), as_float), add(W3, W3.size(), as_float)};
+    const size_t off_b[3] = {add(b1, 16 * h1t, as_float), add(b2, 16 * h2t, as_float), add(b3, 16 * ot, as_float)};
+    const size_t off_mean = add(mean, n_in, as_float), off_rstd = add(sd, n_in, [](double v) { return (float)(1.0 / v); });
+    const size_t off_sc = add(osc, kMlpMaxOut, as_float), off_sh = add(osh, kMlpMaxOut, as_float);
+
+    // packed A operands of every layer, and of the transposes (for the network's
+    // vector-Jacobian product, FP32 only: their K runs over the padded output
+    // units of the forward layer), in one buffer
+    struct Pack { int layer; bool transposed; int fout, fin, mtiles, kt; size_t off; };
+    Pack packs[6] = {{0, false, h1, n_in, h1t, in_t, 0}, {1, false, h2, h1, h2t, h1t, 0}, {2, false, n_out, h2, ot, h2t, 0},
+                     {0, true, h1, n_in, in_t, h1t, 0}, {1, true, h2, h1, h1t, h2t, 0}, {2, true, n_out, h2, h2t, ot, 0}};
+    const int n_packs = bf ? 3 : 6, planes = bf ? 1 : 2;
+    size_t packed = 0;
+    for (int i = 0; i < n_packs; ++i) {
+        packs[i].off = packed;
+        packed += packed_weight_elems(packs[i].mtiles, packs[i].kt, planes);
+    }
 
     DeviceGuard g(c->device);
     mala_weights* w = new mala_weights();
     w->device = c->device;
-    auto upload_f = [&](const std::vector<float>& v) -> void* {
-        void* d = nullptr;
-        if (hipMalloc(&d, sizeof(float) * (v.size() ? v.size() : 1)) != hipSuccess) return nullptr;
-        w->allocs.push_back(d);
-        if (hipMemcpy(d, v.data(), sizeof(float) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return nullptr;
-        return d;
-    };
-    // packed A operands of one layer, or of its transpose (for the network's
-    // vector-Jacobian product, FP32 only: its K runs over the padded output units)
-    float* raw_d = static_cast<float*>(upload_f(raw));
-    const int planes = bf ? 1 : 2;
-    auto pack = [&](size_t off, int fout, int fin, bool transposed, int mtiles, int kt, int wexp) -> void* {
-        void* d = nullptr;
-        if (!raw_d || hipMalloc(&d, sizeof(uint16_t) * packed_weight_elems(mtiles, kt, planes)) != hipSuccess) return nullptr;
-        w->allocs.push_back(d);
-        if (launch_pack_weights(nullptr, raw_d + off, fout, fin, transposed, mtiles, kt, planes, wexp, d) != hipSuccess)
-            return nullptr;
-        return d;
-    };
-    const size_t o2 = W1.size(), o3 = W1.size() + W2.size();
+    float* fd = nullptr;
+    uint16_t* pd = nullptr;
+    hipError_t e = hipMalloc(&fd, sizeof(float) * f32.size());
+    if (e == hipSuccess) w->allocs.push_back(fd);
+    if (e == hipSuccess) e = hipMalloc(&pd, sizeof(uint16_t) * packed);
+    if (e == hipSuccess) w->allocs.push_back(pd);
+    if (e == hipSuccess) e = hipMemcpy(fd, f32.data(), sizeof(float) * f32.size(), hipMemcpyHostToDevice);
+    const void* packed_ptr[6] = {};
+    for (int i = 0; i < n_packs && e == hipSuccess; ++i) {
+        const Pack& k = packs[i];
+        packed_ptr[i] = pd + k.off;
+        e = launch_pack_weights(nullptr, fd + off_w[k.layer], k.fout, k.fin, k.transposed, k.mtiles, k.kt, planes,
+                                we[k.layer], pd + k.off);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);       // packed before any stream reads them
+    if (e != hipSuccess) {
+        mala_weights_free(w);
+        return fail(MALA_E_OOM, "weight upload failed");
+    }
     MlpArgs& a = w->args;
     a.precision = bf ? 1 : 0;
     a.n_in = n_in; a.n_h1 = h1; a.n_h2 = h2; a.n_out = n_out;
@@ -800,27 +814,19 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     a.slope = (float)slope;
     a.out_act = out_act ? 1 : 0;
     for (int l = 0; l < 3; ++l) a.wexp[l] = we[l];
-    a.W1 = pack(0, h1, n_in, false, h1t, in_t, we[0]);
-    a.W2 = pack(o2, h2, h1, false, h2t, h1t, we[1]);
-    a.W3 = pack(o3, n_out, h2, false, ot, h2t, we[2]);
-    a.W1T = bf ? nullptr : pack(0, h1, n_in, true, in_t, h1t, we[0]);
-    a.W2T = bf ? nullptr : pack(o2, h2, h1, true, h1t, h2t, we[1]);
-    a.W3T = bf ? nullptr : pack(o3, n_out, h2, true, h2t, ot, we[2]);
-    a.b1 = (const float*)upload_f(pb1);
-    a.b2 = (const float*)upload_f(pb2);
-    a.b3 = (const float*)upload_f(pb3);
-    a.in_mean = (const float*)upload_f(pm);
-    a.in_rstd = (const float*)upload_f(prs);
-    a.out_scale = (const float*)upload_f(psc);
-    a.out_shift = (const float*)upload_f(psh);
-    if (!a.W1 || !a.W2 || !a.W3 || (!bf && (!a.W1T || !a.W2T || !a.W3T)) || !a.b1 || !a.b2 || !a.b3 || !a.in_mean || !a.in_rstd || !a.out_scale ||
-        !a.out_shift || hipStreamSynchronize(nullptr) != hipSuccess) {       // packed before any stream reads them
-        mala_weights_free(w);
-        return fail(MALA_E_OOM, "weight upload failed");
-    }
-    // the FP32 copy has served
-    (void)hipFree(raw_d);
-    w->allocs.erase(std::find(w->allocs.begin(), w->allocs.end(), static_cast<void*>(raw_d)));
+    a.W1 = packed_ptr[0];
+    a.W2 = packed_ptr[1];
+    a.W3 = packed_ptr[2];
+    a.W1T = packed_ptr[3];
+    a.W2T = packed_ptr[4];
+    a.W3T = packed_ptr[5];
+    a.b1 = fd + off_b[0];
+    a.b2 = fd + off_b[1];
+    a.b3 = fd + off_b[2];
+    a.in_mean = fd + off_mean;
+    a.in_rstd = fd + off_rstd;
+    a.out_scale = fd + off_sc;
+    a.out_shift = fd + off_sh;
     *out = w;
     return MALA_OK;
 }
