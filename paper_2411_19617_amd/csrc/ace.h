@@ -10,6 +10,7 @@ constexpr int kAceMaxN = 4;      // radial functions
 constexpr int kAceMaxL = 4;      // angular momentum
 
 inline int ace_count_ranks12(int nmax, int lmax) { return nmax + (lmax + 1) * nmax * (nmax + 1) / 2; }
+int ace_count_rank3(int nmax, int lmax);         // descriptors of the rank-3 set
 // rank-3 groups (p1, p2, l3): a header of kAceGroupInts ints each, its
 // outputs (A row base of n3 | descriptor position << 7, at most kAceMaxN)
 // inline, then the first rank-3 position of its pair (p1, p2) and the pair's

@@ -898,10 +898,7 @@ mala_status mala_descriptors_vjp(mala_ctx* c, const double* positions, int32_t n
 
 int32_t mala_ace_count(int32_t nmax, int32_t lmax) {
     if (nmax < 1 || nmax > kAceMaxN || lmax < 0 || lmax > kAceMaxL) return MALA_E_UNSUPPORTED;
-    std::vector<int> groups, groups_dm;
-    std::vector<float> coef;
-    const int n3 = build_ace_tables(nmax, lmax, groups, groups_dm, coef);
-    return n3 < 0 ? MALA_E_UNSUPPORTED : ace_count_ranks12(nmax, lmax) + n3;
+    return ace_count_ranks12(nmax, lmax) + ace_count_rank3(nmax, lmax);
 }
 
 mala_status mala_ace_descriptors(mala_ctx* c, const double* positions, int32_t n_atoms, const mala_cell_grid* cg,

@@ -189,6 +189,19 @@ void plan_y_units(int twojmax, int c_lo, int c_hi, int n_waves, int* wave_units,
     }
 }
 
+// Rank-3 descriptors: multisets of three (n, l) that obey the triangle rule, with an even l-sum.
+int ace_count_rank3(int nmax, int lmax) {
+    const int nl = lmax + 1, np = nmax * nl;
+    int nd = 0;
+    for (int p1 = 0; p1 < np; ++p1)
+        for (int p2 = p1; p2 < np; ++p2)
+            for (int p3 = p2; p3 < np; ++p3) {
+                const int l1 = p1 % nl, l2 = p2 % nl, l3 = p3 % nl;
+                nd += l3 >= abs(l1 - l2) && l3 <= l1 + l2 && (l1 + l2 + l3) % 2 == 0;
+            }
+    return nd;
+}
+
 // Rank-3 grid ACE tables.  The descriptors (multisets of three (n, l)
 // pairs, key p = n (lmax+1) + l, p1 <= p2 <= p3, l1+l2+l3 even and triangle,
 // in that order) are grouped by (p1, p2, l3).  A group's partial sums
@@ -348,7 +361,11 @@ int build_ace_tables(int nmax, int lmax, std::vector<int>& groups, std::vector<i
 // The set: multisets p1 <= p2 <= p3 <= p4 with an even l-sum; for each, the
 // couplings L (in increasing order) whose coefficients, summed over the
 // permutations that exchange equal keys, are linearly independent of those
-// kept before (Gram-Schmidt on the coefficient tensors).
+// kept before.  Without equal keys every L is; an equal pair inside (p1 p2) or
+// (p3 p4) leaves the even L; where p2 = p3 the first L are, as many as the
+// symmetric states allow (a count, no coefficients: Gram-Schmidt on the
+// coefficient tensors gives the same set and took 4.9 ms at nmax4 = lmax4 = 3,
+// this takes 2 us, and a caller that sizes its output asks on every call).
 // Evaluation: with the coupled pairs P_a(M) = sum_m1 <l1 m1 l2 m2|L M>
 // A_p1,m1 A_p2,m2 (a = (p1 p2), m2 = M - m1) and A_{l,-m} = (-1)^m conj A_{l,m},
 // P_a(-M) = (-1)^(l1+l2-L+M) conj P_a(M); for an even l-sum the descriptor is
@@ -378,68 +395,54 @@ struct Ace4Cg {
 
 }  // namespace
 
+namespace {
+
+// Multiplicity of the angular momentum `total` in the symmetric product of k
+// equal momenta l: the symmetric states of sum M = total less those of total + 1.
+int sym_multiplicity(int l, int k, int total) {
+    // ways[s]: multisets of k values from 0..2l of sum s (m + l each)
+    std::array<std::array<int, 4 * 2 * kAce4MaxL + 1>, 5> ways{};
+    ways[0][0] = 1;
+    for (int m = 0; m <= 2 * l; ++m)
+        for (int j = 1; j <= k; ++j)
+            for (int s = m; s <= 2 * l * k; ++s) ways[j][s] += ways[j - 1][s - m];
+    const int at = total + k * l;
+    return at > 2 * l * k ? 0 : ways[k][at] - (at + 1 > 2 * l * k ? 0 : ways[k][at + 1]);
+}
+
+// How many couplings L of (l1 l2)(l3 l4) are independent after symmetrising
+// over equal keys, where the second and third key are equal.
+int ace4_independent(int l1, int l, int l4, bool eq12, bool eq34) {
+    if (eq12 && eq34) return sym_multiplicity(l, 4, 0);
+    if (eq12) return sym_multiplicity(l, 3, l4);
+    if (eq34) return sym_multiplicity(l, 3, l1);
+    int n = 0;                                       // even couplings of (l2 l3) that reach (l1 l4)
+    for (int L = 0; L <= 2 * l; L += 2) n += L >= abs(l1 - l4) && L <= l1 + l4;
+    return n;
+}
+
+}  // namespace
+
 int ace4_descriptor_set(int nmax4, int lmax4, std::vector<int>& desc) {
     desc.clear();
-    Ace4Cg cg;
     const int nl = lmax4 + 1, np = nmax4 * nl;
+    desc.reserve((size_t)5 * 1024);
     for (int p1 = 0; p1 < np; ++p1)
         for (int p2 = p1; p2 < np; ++p2)
             for (int p3 = p2; p3 < np; ++p3)
                 for (int p4 = p3; p4 < np; ++p4) {
-                    const int ps[4] = {p1, p2, p3, p4};
-                    const int l[4] = {p1 % nl, p2 % nl, p3 % nl, p4 % nl};
-                    if ((l[0] + l[1] + l[2] + l[3]) % 2) continue;
-                    const int d1 = 2 * l[1] + 1, d2 = 2 * l[2] + 1, d3 = 2 * l[3] + 1;
-                    const int dim = (2 * l[0] + 1) * d1 * d2 * d3;
-                    // permutations of the four slots that map every key onto an equal key
-                    std::vector<std::array<int, 4>> perms;
-                    std::array<int, 4> q = {0, 1, 2, 3};
-                    do {
-                        bool ok = true;
-                        for (int i = 0; i < 4; ++i) ok = ok && ps[q[i]] == ps[i];
-                        if (ok) perms.push_back(q);
-                    } while (std::next_permutation(q.begin(), q.end()));
-                    std::vector<std::vector<double>> kept;
-                    const int Llo = std::max(abs(l[0] - l[1]), abs(l[2] - l[3]));
-                    const int Lhi = std::min(l[0] + l[1], l[2] + l[3]);
-                    for (int L = Llo; L <= Lhi; ++L) {
-                        std::vector<double> T(dim, 0.0);
-                        auto at = [&](const int (&m)[4]) {
-                            return (((m[0] + l[0]) * d1 + m[1] + l[1]) * d2 + m[2] + l[2]) * d3 + m[3] + l[3];
-                        };
-                        for (int m1 = -l[0]; m1 <= l[0]; ++m1)
-                            for (int m2 = -l[1]; m2 <= l[1]; ++m2)
-                                for (int m3 = -l[2]; m3 <= l[2]; ++m3) {
-                                    const int m4 = -m1 - m2 - m3, M = m1 + m2;
-                                    if (abs(m4) > l[3] || abs(M) > L) continue;
-                                    const double c = cg(l[0], m1, l[1], m2, L, M) * cg(l[2], m3, l[3], m4, L, -M) *
-                                                     (((L - M) & 1) ? -1.0 : 1.0) / sqrt(2.0 * L + 1.0);
-                                    if (c == 0.0) continue;
-                                    const int m[4] = {m1, m2, m3, m4};
-                                    // symmetrised: the coefficient lands on every slot order
-                                    // that exchanges equal keys
-                                    for (const auto& pr : perms) {
-                                        int mp[4];
-                                        for (int i = 0; i < 4; ++i) mp[pr[i]] = m[i];
-                                        T[at(mp)] += c / (double)perms.size();
-                                    }
-                                }
-                        double n0 = 0.0;
-                        for (double x : T) n0 += x * x;
-                        for (const auto& k : kept) {            // Gram-Schmidt against the kept ones
-                            double dot = 0.0;
-                            for (int i = 0; i < dim; ++i) dot += k[i] * T[i];
-                            for (int i = 0; i < dim; ++i) T[i] -= dot * k[i];
-                        }
-                        double n1 = 0.0;
-                        for (double x : T) n1 += x * x;
-                        if (n0 > 0.0 && n1 > 1e-18 * std::max(1.0, n0)) {
-                            const double inv = 1.0 / sqrt(n1);
-                            for (double& x : T) x *= inv;
-                            kept.push_back(T);
-                            for (int i = 0; i < 4; ++i) desc.push_back(ps[i]);
-                            desc.push_back(L);
-                        }
+                    const int l1 = p1 % nl, l2 = p2 % nl, l3 = p3 % nl, l4 = p4 % nl;
+                    if ((l1 + l2 + l3 + l4) % 2) continue;
+                    const bool eq12 = p1 == p2, eq34 = p3 == p4;
+                    // (l l) of equal keys couples to even L only
+                    const int step = eq12 || eq34 ? 2 : 1;
+                    int L = std::max(abs(l1 - l2), abs(l3 - l4));
+                    const int hi = std::min(l1 + l2, l3 + l4);
+                    if (step == 2) L += L & 1;
+                    int left = p2 == p3 ? ace4_independent(l1, l2, l4, eq12, eq34) : hi + 1;
+                    for (; L <= hi && left > 0; L += step, --left) {
+                        const int d[5] = {p1, p2, p3, p4, L};
+                        desc.insert(desc.end(), d, d + 5);
                     }
                 }
     return (int)(desc.size() / 5);
