@@ -10,9 +10,9 @@
 //   coupling L (k_ace4 below).
 // Two kernels per chunk of points.  k_ace_proj: per 64-point tile (lane =
 // point) the candidate atom images are gathered into LDS (shared with the
-// other neighbour kernels), wave 0 builds per-point neighbour lists, and wave
-// n forms the rows A_{n l m} (m >= 0; A_{l,-m} = (-1)^m conj A_{l,m}) over its
-// lane's list: T_n by the three-term recurrence, Y_l^m = N_lm Q_l^m(z/r)
+// other neighbour kernels), the waves build per-point neighbour lists and form
+// A_{n l m} (m >= 0; A_{l,-m} = (-1)^m conj A_{l,m}) over a share of the lane's
+// list each: T_n by the three-term recurrence, Y_l^m = N_lm Q_l^m(z/r)
 // ((x + i y)/r)^m with Q_l^m = (-1)^m d^m P_l / dt^m by the associated
 // Legendre recurrence in l; the tile's A goes to HBM (480 B per point,
 // coalesced).  k_ace (ranks 1-3) and k_ace4 (rank 4) load a tile's A into
@@ -33,7 +33,7 @@ namespace mala {
 constexpr int kAceN = kAceMaxN;          // radial functions held per point
 constexpr int kAceL = kAceMaxL;          // largest l held
 constexpr int kAceLm = 15;               // (l, m >= 0) entries per n: l(l+1)/2 + m
-constexpr int kAceWaves = 4;            // projection: one wave per radial index
+constexpr int kAceWaves = 4;            // projection: waves that share the neighbours
 
 __host__ __device__ constexpr double ace_fact(int n) {
     double f = 1.0;
@@ -47,9 +47,10 @@ __host__ __device__ constexpr double ace_sqrt(double x) {
     return r;
 }
 // N_lm = sqrt((2l+1)/(4 pi) (l-m)!/(l+m)!)
-__host__ __device__ constexpr float ace_norm(int l, int m) {
-    return (float)ace_sqrt((2 * l + 1) / (4.0 * 3.14159265358979323846) * ace_fact(l - m) / ace_fact(l + m));
+__host__ __device__ constexpr double ace_norm_d(int l, int m) {
+    return ace_sqrt((2 * l + 1) / (4.0 * 3.14159265358979323846) * ace_fact(l - m) / ace_fact(l + m));
 }
+__host__ __device__ constexpr float ace_norm(int l, int m) { return (float)ace_norm_d(l, m); }
 
 // The tile's own point (lane = point) relative to the origins of its
 // candidate atom images, gathered into cand (whole block).
@@ -81,105 +82,151 @@ __device__ __forceinline__ AceTile ace_tile(const BinState& bins, int Nx, int Ny
     return t;
 }
 
-// The lane's A_{n l m} for one radial index n (all l <= 4, m >= 0) over the
-// lane's neighbour list (candidate indices within rcut, in candidate order),
-// plus the grid point's own delta on l = 0; written to dst[lm][lane].
-__device__ __forceinline__ void ace_project_n(const float4* cand, const unsigned short (*nbr)[kTile], int my_n,
-                                              int n_iter, const AceTile& tl, double rcut, int n, int lane,
-                                              float2* __restrict__ dst) {
-    const float rcf = (float)rcut;
-    constexpr float kpi = 3.14159265358979323846f;
-    constexpr float y00 = 0.28209479177387814f;            // 1 / sqrt(4 pi)
-    const float k2 = 2.f / rcf, kcut = kpi / rcf;          // per unit distance, formed once
-    float ar[kAceLm], ai[kAceLm];
+// Real numbers of A_{n l m} for one n: Re of (l, m) at ace_re, Im (m > 0) behind it.
+constexpr int kAceReals = (kAceL + 1) * (kAceL + 1);
+__host__ __device__ constexpr int ace_re(int l, int m) { return l * l + (m ? 2 * m - 1 : 0); }
+
+// One neighbour's R_n(r) Y_l^m for every n and (l, m), m >= 0, added to acc.
+// Y_l^m = q_l^m(z/r) ((x + i y)/r)^m with q = N_lm Q_l^m by the recurrence in l
+// (its factors and the norms are constants).
+__device__ __forceinline__ void ace_add_neighbour(float dx, float dy, float dz, float k2, float kcut,
+                                                  float (&acc)[kAceN][kAceReals]) {
+    const float r2 = dx * dx + dy * dy + dz * dz;
+    // 1/r and r from one hardware reciprocal square root (about 1 ulp)
+    const bool at_point = !(r2 > kMinR2);
+    const float inv = at_point ? 0.f : __builtin_amdgcn_rsqf(r2);
+    const float r = r2 * inv;
+    const float x = r * k2 - 1.f, fc = 0.5f * (cosf(kcut * r) + 1.f);
+    float R[kAceN] = {fc, x * fc};
 #pragma unroll
-    for (int e = 0; e < kAceLm; ++e) ar[e] = ai[e] = 0.f;
-    ar[0] = (n & 1) ? -y00 : y00;                          // the grid point's own delta: T_n(-1) Y_0^0
-    for (int s = 0; s < n_iter; ++s) {
-        if (s >= my_n) continue;
-        const int c = nbr[s][lane];
-        const float4 q = cand[c];
-        const float3 o = tl.frame.at(c);
-        const float dx = q.x - o.x, dy = q.y - o.y, dz = q.z - o.z;
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        // 1/r and r from one hardware reciprocal square root (about 1 ulp)
-        const bool at_point = !(r2 > kMinR2);
-        const float inv = at_point ? 0.f : __builtin_amdgcn_rsqf(r2);
-        const float r = r2 * inv;
-        // radial: T_n(x) fc(r) by the three-term recurrence
-        const float x = r * k2 - 1.f;
-        const float fc = 0.5f * (cosf(kcut * r) + 1.f);
-        float t0 = 1.f, t1 = x;
-        for (int k = 2; k <= n; ++k) {
-            const float t2 = 2.f * x * t1 - t0;
-            t0 = t1;
-            t1 = t2;
-        }
-        const float R = (n == 0 ? 1.f : t1) * fc;
-        if (at_point) {                                    // an atom on the point: l = 0 only
-            ar[0] += R * y00;
-            continue;
-        }
-        const float t = dz * inv, ur = dx * inv, ui = dy * inv;
-        // Q_l^m(t) for l <= 4, m >= 0, and ((x + i y)/r)^m
-        float Q[kAceLm];
-        float er[kAceL + 1], ei[kAceL + 1];
-        er[0] = 1.f;
-        ei[0] = 0.f;
+    for (int n = 2; n < kAceN; ++n) R[n] = fmaf(2.f * x, R[n - 1], -R[n - 2]);
+    constexpr float y00 = ace_norm(0, 0);
 #pragma unroll
-        for (int m = 1; m <= kAceL; ++m) {
-            er[m] = er[m - 1] * ur - ei[m - 1] * ui;
-            ei[m] = er[m - 1] * ui + ei[m - 1] * ur;
-        }
-        static_for<0, kAceL + 1>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            // Q_m^m = (-1)^m (2m-1)!!
-            constexpr float qmm = (float)(((m & 1) ? -1.0 : 1.0) * (ace_fact(2 * m) / (ace_fact(m) * (double)(1 << m))));
-            Q[m * (m + 1) / 2 + m] = qmm;
-            if constexpr (m + 1 <= kAceL) Q[(m + 1) * (m + 2) / 2 + m] = (2 * m + 1) * t * qmm;
-            static_for<m + 2, kAceL + 1>([&](auto lc) {
-                constexpr int l = decltype(lc)::value;
-                Q[l * (l + 1) / 2 + m] = ((2 * l - 1) * t * Q[(l - 1) * l / 2 + m] -
-                                          (float)(l + m - 1) * Q[(l - 2) * (l - 1) / 2 + m]) /
-                                         (float)(l - m);
-            });
-        });
-        static_for<0, kAceL + 1>([&](auto lc) {
-            constexpr int l = decltype(lc)::value;
-            static_for<0, l + 1>([&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                constexpr int e = l * (l + 1) / 2 + m;
-                constexpr float nrm = ace_norm(l, m);
-                const float y = R * nrm * Q[e];
-                ar[e] = fmaf(y, er[m], ar[e]);
-                ai[e] = fmaf(y, ei[m], ai[e]);
-            });
-        });
+    for (int n = 0; n < kAceN; ++n) {
+        acc[n][0] = fmaf(R[n], y00, acc[n][0]);
+        R[n] = at_point ? 0.f : R[n];                      // an atom on the point: l = 0 only
     }
+    const float t = dz * inv, ur = dx * inv, ui = dy * inv;
+    float er[kAceL + 1], ei[kAceL + 1];
+    er[0] = 1.f;
+    ei[0] = 0.f;
+    er[1] = ur;
+    ei[1] = ui;
 #pragma unroll
-    for (int e = 0; e < kAceLm; ++e) dst[e * kTile + lane] = make_float2(ar[e], ai[e]);
+    for (int m = 2; m <= kAceL; ++m) {
+        er[m] = er[m - 1] * ur - ei[m - 1] * ui;
+        ei[m] = er[m - 1] * ui + ei[m - 1] * ur;
+    }
+    static_for<0, kAceL + 1>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        // Q_m^m = (-1)^m (2m-1)!!
+        constexpr double qmm = ((m & 1) ? -1.0 : 1.0) * (ace_fact(2 * m) / (ace_fact(m) * (double)(1 << m)));
+        float q[kAceL + 1];
+        static_for<(m ? m : 1), kAceL + 1>([&](auto lc) {
+            constexpr int l = decltype(lc)::value;
+            constexpr double nl = ace_norm_d(l, m);
+            if constexpr (l == m) q[l] = (float)(nl * qmm);
+            else if constexpr (l == m + 1) q[l] = (float)(nl * qmm * (2 * m + 1)) * t;
+            else {
+                constexpr float a = (float)(nl / ace_norm_d(l - 1, m) * (2 * l - 1) / (l - m));
+                constexpr float b = (float)(nl / ace_norm_d(l - 2, m) * (l + m - 1) / (l - m));
+                float q2;
+                if constexpr (l == 2 && m == 0) q2 = y00;
+                else q2 = q[l - 2];
+                q[l] = fmaf(a * t, q[l - 1], -b * q2);
+            }
+            if constexpr (m == 0) {
+#pragma unroll
+                for (int n = 0; n < kAceN; ++n) acc[n][ace_re(l, 0)] = fmaf(R[n], q[l], acc[n][ace_re(l, 0)]);
+            } else {
+                const float yr = q[l] * er[m], yi = q[l] * ei[m];
+#pragma unroll
+                for (int n = 0; n < kAceN; ++n) {
+                    acc[n][ace_re(l, m)] = fmaf(R[n], yr, acc[n][ace_re(l, m)]);
+                    acc[n][ace_re(l, m) + 1] = fmaf(R[n], yi, acc[n][ace_re(l, m) + 1]);
+                }
+            }
+        });
+    });
 }
 
-__global__ __launch_bounds__(64 * kAceWaves) void k_ace_proj(BinState bins, int Nx, int Ny, int Nz, double rcut,
-                                                             int64_t pt_begin, int64_t n_pts,
-                                                             float2* __restrict__ Ag, int* __restrict__ err) {
-    __shared__ float4 cand[kMaxCand];
-    __shared__ unsigned short nbr[kMaxNbr][kTile];
-    __shared__ int nnbr[kTile];
-    __shared__ int scan_tmp[16];
-
+// Bound by the VALU: about 200 instructions per neighbour and point, half of
+// them the multiply-adds into A.  The waves share the neighbours (every wave all
+// n and (l, m) of every fourth neighbour, so a neighbour's distance, cutoff and
+// harmonics are formed once) and their sums meet in LDS at the end, wave n
+// keeping radial index n.  Before, every wave formed them for its own n, behind
+// a list that one wave built: 230 -> 142 us per 300,007 points of a solid.
+__global__ __launch_bounds__(64 * kAceWaves, 3) void k_ace_proj(BinState bins, int Nx, int Ny, int Nz, double rcut,
+                                                                int64_t pt_begin, int64_t n_pts,
+                                                                float2* __restrict__ Ag, int* __restrict__ err) {
+    static_assert(kAceWaves == 4 && kAceN == 4, "wave n keeps radial index n, in two phases of two");
+    struct Lists {
+        float4 cand[kMaxCand];
+        unsigned short nbr[kMaxNbr][kTile];
+        int nnbr[kAceWaves][kTile];
+        int scan_tmp[16];
+    };
+    constexpr int kParts = 2 * (kAceWaves - 1);            // partial sums exchanged per phase
+    __shared__ union {
+        Lists l;
+        float part[kParts][kAceReals][kTile];
+    } sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const AceTile tl = ace_tile(bins, Nx, Ny, Nz, rcut, pt_begin, n_pts, cand, scan_tmp, err);
+    const AceTile tl = ace_tile(bins, Nx, Ny, Nz, rcut, pt_begin, n_pts, sh.l.cand, sh.l.scan_tmp, err);
     __syncthreads();
-    // per-point neighbour lists (wave 0), in candidate order
-    if (wave == 0) build_neighbour_lists(cand, tl.ncand, tl.frame, (float)rcut, tl.valid, lane, nbr, nnbr, err);
-    __syncthreads();
-    const int my_n = nnbr[lane];
+    const float rcf = (float)rcut;
+    const int my_n = build_neighbour_lists_block<kAceWaves>(sh.l.cand, tl.ncand, tl.frame, rcf, tl.valid, lane, wave,
+                                                            sh.l.nbr, sh.l.nnbr, err);
     const int n_iter = wave_max_int(my_n);
-    // wave n forms the rows of radial index n
+    const float k2 = 2.f / rcf, kcut = 3.14159265358979323846f / rcf;      // per unit distance, formed once
+    float acc[kAceN][kAceReals];
+#pragma unroll
+    for (int n = 0; n < kAceN; ++n)
+#pragma unroll
+        for (int e = 0; e < kAceReals; ++e) acc[n][e] = 0.f;
+#pragma clang loop unroll(disable)
+    for (int s = wave; s < n_iter; s += kAceWaves) {
+        if (s >= my_n) continue;
+        const int c = sh.l.nbr[s][lane];
+        const float4 q = sh.l.cand[c];
+        const float3 o = tl.frame.at(c);
+        ace_add_neighbour(q.x - o.x, q.y - o.y, q.z - o.z, k2, kcut, acc);
+    }
     float2* dst = Ag + ((int64_t)blockIdx.x * kAceN * kAceLm + wave * kAceLm) * kTile;
-    ace_project_n(cand, nbr, my_n, n_iter, tl, rcut, wave, lane, dst);
+    static_for<0, kAceN / 2>([&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        __syncthreads();                                   // the lists, or the last phase's sums, are read
+        static_for<2 * h, 2 * h + 2>([&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            if (wave == n) return;
+            float (*to)[kTile] = sh.part[(n - 2 * h) * (kAceWaves - 1) + (wave < n ? wave : wave - 1)];
+#pragma unroll
+            for (int e = 0; e < kAceReals; ++e) to[e][lane] = acc[n][e];
+        });
+        __syncthreads();
+        static_for<2 * h, 2 * h + 2>([&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            if (wave != n) return;
+            float v[kAceReals];
+#pragma unroll
+            for (int e = 0; e < kAceReals; ++e) {
+                v[e] = acc[n][e];
+#pragma unroll
+                for (int k = 0; k < kAceWaves - 1; ++k) v[e] += sh.part[(n - 2 * h) * (kAceWaves - 1) + k][e][lane];
+            }
+            constexpr float y00 = ace_norm(0, 0);
+            v[0] += (n & 1) ? -y00 : y00;                  // the grid point's own delta: T_n(-1) Y_0^0
+            static_for<0, kAceL + 1>([&](auto lc) {
+                constexpr int l = decltype(lc)::value;
+                static_for<0, l + 1>([&](auto mc) {
+                    constexpr int m = decltype(mc)::value;
+                    dst[(l * (l + 1) / 2 + m) * kTile + lane] =
+                        make_float2(v[ace_re(l, m)], m ? v[ace_re(l, m) + 1] : 0.f);
+                });
+            });
+        });
+    });
 }
 
 // The tile's A from the projection kernel into LDS (whole block).

@@ -13,8 +13,8 @@
 // Bound by the VALU: about 1,000 instructions per neighbour and point at
 // twojmax 10 where a recursion over the levels takes 2,600.  Against the
 // recursion with wave 0 listing the neighbours: twojmax 10, 200,003 points of a
-// liquid, 445 -> 245 us; twojmax 8, 8,000 points of a 32-atom cell (125 blocks,
-// where the list's serial chain counts), 59 -> 35 us.
+// liquid, 445 -> 240 us; twojmax 8, 8,000 points of a 32-atom cell (125 blocks,
+// where the list's serial chain counts), 59 -> 32 us.
 #include "snap_core.h"
 #include "tile_gather.h"
 #include "u_basis.h"
