@@ -11,21 +11,19 @@ constexpr int kAceMaxL = 4;      // angular momentum
 
 inline int ace_count_ranks12(int nmax, int lmax) { return nmax + (lmax + 1) * nmax * (nmax + 1) / 2; }
 int ace_count_rank3(int nmax, int lmax);         // descriptors of the rank-3 set
-// rank-3 groups (p1, p2, l3): a header of kAceGroupInts ints each, its
-// outputs (A row base of n3 | descriptor position << 7, at most kAceMaxN)
-// inline, then the first rank-3 position of its pair (p1, p2) and the pair's
-// width | (last group of the pair) << 8.  The outputs of a pair are
-// contiguous (at most kAceMaxPairCols).  Two tables: `groups` for
-// point-major output, laid out for kAce3Waves waves (entry k * kAce3Waves + w
-// is wave w's k-th group, each wave holding whole pairs, balanced by their
-// terms, padded with empty groups of combination -1), and `groups_dm` in
-// (p1, p2, l3) order for descriptor-major output (the waves take every
-// kAce3Waves-th group).
-constexpr int kAceGroupInts = 12;
+// Plan of ranks 1-3 for kAce3Waves waves whose lanes form `groups` groups: the
+// starts of the waves' lists (kAce3Waves + 1 ints), then rounds of
+// ace_round_ints(groups) ints: kind | first n3 << 8, and per lane group its pair
+// n1 | n2 << 2 | place of its first value << 4 | that value's output column << 8
+// (place 15: no pair).  Kind l1 (kAceMaxL + 1) + l2, l1 <= l2, is rank 3 of pairs
+// (n1 l1), (n2 l2): a value's place counts (n3, l3) from n3 = 0, and the pair's
+// values are those from its later key on.  kAceRank2 + l is rank 2, kAceRank1 rank 1.
+constexpr int kAceRank2 = (kAceMaxL + 1) * (kAceMaxL + 1), kAceRank1 = kAceRank2 + kAceMaxL + 1;
 constexpr int kAce3Waves = 8;
-constexpr int kAceMaxPairCols = kAceMaxN * (kAceMaxL + 1);
-int build_ace_tables(int nmax, int lmax, std::vector<int>& groups, std::vector<int>& groups_dm,
-                     std::vector<float>& coef);
+constexpr int kAceRowPoints = 16;               // points per block, point-major
+__host__ __device__ constexpr int ace_round_ints(int groups) { return groups == 1 ? 2 : groups + 1; }
+constexpr int kAceMaxPairCols = 3 * kAceMaxN;    // three l3 at most couple with (l1, l2)
+void build_ace_plan(int nmax, int lmax, int groups, std::vector<int>& plan);
 // rank 4: descriptor set (p1, p2, p3, p4, L per entry) and its evaluation tables
 constexpr int kAce4MaxN = 3;
 constexpr int kAce4MaxL = 3;
@@ -53,8 +51,9 @@ hipError_t launch_ace4(hipStream_t s, const float2* Ag, int lmax4, int n_phases,
                        int n4, float* out, int64_t ps, int64_t ds);   // descriptor k of point p at out[p ps + k ds]
 // out[p n_cols + k] = in[k ld + p] (p < n_rows <= ld, k < n_cols)
 hipError_t launch_planes_to_rows(hipStream_t s, const float* in, int64_t ld, int64_t n_rows, int n_cols, float* out);
-hipError_t launch_ace(hipStream_t s, const float2* Ag, int nmax, int lmax, int64_t n_pts, const int* groups,
-                      int n_groups, const float* coef, int n_desc, float* out, int64_t ps,
-                      int64_t ds);
+// point-major rows of n_desc (rows, plan for kTile / kAceRowPoints groups) or one
+// plane of ds values per descriptor (plan for one group)
+hipError_t launch_ace(hipStream_t s, const float2* Ag, int nmax, int lmax, int64_t n_pts, const int* plan,
+                      int plan_ints, bool rows, int n_desc, float* out, int64_t ds);
 
 }  // namespace mala

@@ -16,12 +16,7 @@
 // ((x + i y)/r)^m with Q_l^m = (-1)^m d^m P_l / dt^m by the associated
 // Legendre recurrence in l; the tile's A goes to HBM (480 B per point,
 // coalesced).  k_ace (ranks 1-3) and k_ace4 (rank 4) load a tile's A into
-// LDS and contract it with few registers, so many waves share a CU.  Rank 3
-// is grouped by (p1, p2, l3): the partial sums
-// P(m3) = sum_m1 (l1 l2 l3; m1 m2 m3) A_{n1 l1 m1} A_{n2 l2 m2} from a table of
-// packed terms (storage indices, conjugation flags, 3j symbol with signs,
-// sorted by m3) read with wave-uniform loads, then B = sum_m3 P(m3) A_{n3 l3 m3}
-// for every n3 of the group.  Outputs are written point-major or
+// LDS and contract it there.  Outputs are written point-major or
 // descriptor-major (one plane per descriptor, coalesced stores).
 #include <mutex>
 
@@ -43,7 +38,11 @@ __host__ __device__ constexpr double ace_fact(int n) {
 __host__ __device__ constexpr double ace_sqrt(double x) {
     if (x <= 0.0) return 0.0;
     double r = x > 1.0 ? x : 1.0;
-    for (int i = 0; i < 64; ++i) r = 0.5 * (r + x / r);
+    for (int i = 0; i < 64; ++i) {
+        const double next = 0.5 * (r + x / r);
+        if (next == r) break;
+        r = next;
+    }
     return r;
 }
 // N_lm = sqrt((2l+1)/(4 pi) (l-m)!/(l+m)!)
@@ -235,172 +234,254 @@ __device__ __forceinline__ void ace_load_tile(const float2* __restrict__ Ag, flo
     for (int e = threadIdx.x; e < kAceN * kAceLm * kTile; e += blockDim.x) sA[e / kTile][e % kTile] = src[e];
 }
 
-// Position of the structural term (m3, m1) in the coefficient block of a
-// rank-3 combination (l1, l2, l3): m3 = -l3..l3, m1 = -l1..l1 with
-// |m1 + m3| <= l2 (the host builds the block in the same order).
-__host__ __device__ constexpr int ace3_k(int L1, int L2, int L3, int m3, int m1) {
-    int k = 0;
-    for (int a = -L3; a <= L3; ++a)
-        for (int b = -L1; b <= L1; ++b) {
-            if (a == m3 && b == m1) return k;
-            if (-b - a >= -L2 && -b - a <= L2) ++k;
-        }
-    return k;
-}
-
-// P(m3) = sum_m1 (l1 l2 l3; m1, m2 = -m1-m3, m3) A1(m1) A2(m2) of one group,
-// code specialised for (L1, L2, L3): the group's A values are read from LDS
-// once into registers (L1 + 1 and L2 + 1 of them, m >= 0), and every index,
-// conjugation and sign of A_{l,-m} = (-1)^m conj A_{l,m} is resolved at
-// compile time; the 3j symbols come from the combination's coefficient block.
-template <int L1, int L2, int L3>
-__device__ __forceinline__ void ace3_group(const float2 (*sA)[kTile], int b1, int b2, int lane,
-                                           const float* __restrict__ cf, float (&pr)[9], float (&pim)[9]) {
-    float2 a1[L1 + 1], a2[L2 + 1];
-    static_for<0, L1 + 1>([&](auto mc) { a1[decltype(mc)::value] = sA[b1 + decltype(mc)::value][lane]; });
-    static_for<0, L2 + 1>([&](auto mc) { a2[decltype(mc)::value] = sA[b2 + decltype(mc)::value][lane]; });
-    static_for<0, 2 * L3 + 1>([&](auto ic) {
-        constexpr int m3 = decltype(ic)::value - L3;
-        // one slot's coefficients at a time (hoisting all of a group's loads
-        // ahead would hold up to 81 of them in registers)
-        __builtin_amdgcn_sched_barrier(0);
-        float xr = 0.f, xi = 0.f;
-        static_for<0, 2 * L1 + 1>([&](auto jc) {
-            constexpr int m1 = decltype(jc)::value - L1, m2 = -m1 - m3;
-            if constexpr (m2 >= -L2 && m2 <= L2) {
-                constexpr int k = ace3_k(L1, L2, L3, m3, m1);
-                constexpr int am1 = m1 < 0 ? -m1 : m1, am2 = m2 < 0 ? -m2 : m2;
-                constexpr bool neg = ((m1 < 0 && (am1 & 1)) != (m2 < 0 && (am2 & 1)));
-                const float c = neg ? -cf[k] : cf[k];
-                const float ax = a1[am1].x, ay = m1 < 0 ? -a1[am1].y : a1[am1].y;
-                const float bx = a2[am2].x, by = m2 < 0 ? -a2[am2].y : a2[am2].y;
-                xr = fmaf(c, ax * bx - ay * by, xr);
-                xi = fmaf(c, ax * by + ay * bx, xi);
-            }
-        });
-        pr[m3 + 4] = xr;
-        pim[m3 + 4] = xi;
-    });
-}
-
-__host__ __device__ constexpr bool ace3_combo_valid(int c) {
-    const int l1 = c / 25, l2 = (c / 5) % 5, l3 = c % 5;
-    return l3 >= (l1 > l2 ? l1 - l2 : l2 - l1) && l3 <= l1 + l2 && (l1 + l2 + l3) % 2 == 0;
-}
-
-// Ranks 1-3 of one tile from its projected A (no register-heavy projection
-// here, so many blocks share a CU).  STAGE: point-major output through LDS;
-// the descriptor-major form stores directly and keeps the LDS for more blocks.
-template <bool STAGE>
-__global__ __launch_bounds__(64 * kAce3Waves) void k_ace(const float2* __restrict__ Ag, int nmax, int lmax,
-                                                        int64_t n_pts, const int* __restrict__ groups,
-                                                        int n_groups, const float* __restrict__ coef,
-                                                        int n_desc,
-                                                        float* __restrict__ out, int64_t ps, int64_t ds) {
-    __shared__ float2 sA[kAceN * kAceLm][kTile];
-    // point-major output: each wave gathers a pair's (contiguous) columns for
-    // the tile's 64 points here, then writes them as row segments, several
-    // rows per store instruction, instead of 64 values a row apart per store
-    __shared__ float sO[STAGE ? kAce3Waves : 1][STAGE ? kAceMaxPairCols : 1][kTile + 1];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t idx = (int64_t)blockIdx.x * kTile + lane;
-    const bool valid = idx < n_pts;
-    constexpr bool stage = STAGE;
-    ace_load_tile(Ag, sA);
-    __syncthreads();
-
-    float* o = out + (valid ? idx : 0) * ps;       // descriptor d at o[d * ds]
-    const int n12 = nmax + (lmax + 1) * nmax * (nmax + 1) / 2;
-    int d = 0;
-    if (wave == 0) {
-    for (int n = 0; n < nmax; ++n, ++d)
-        if (valid) o[d * ds] = sA[n * kAceLm][lane].x;
-    for (int l = 0; l <= lmax; ++l)
-        for (int n1 = 0; n1 < nmax; ++n1)
-            for (int n2 = n1; n2 < nmax; ++n2, ++d) {
-                // sum_m (-1)^m A_{n1 l m} A_{n2 l -m} = A_{n1 l 0} A_{n2 l 0} + 2 sum_{m>0} Re(A_{n1 l m} conj(A_{n2 l m}))
-                const int e0 = l * (l + 1) / 2;
-                const float2 a0 = sA[n1 * kAceLm + e0][lane], b0 = sA[n2 * kAceLm + e0][lane];
-                float s = a0.x * b0.x + a0.y * b0.y;
-                for (int m = 1; m <= l; ++m) {
-                    const float2 a = sA[n1 * kAceLm + e0 + m][lane], b = sA[n2 * kAceLm + e0 + m][lane];
-                    s = fmaf(2.f, a.x * b.x + a.y * b.y, s);
-                }
-                if (valid) o[d * ds] = s;
-            }
+// 3j symbol (l1 l2 l3; m1 m2 m3) by Racah's sum, at compile time.
+__host__ __device__ constexpr double ace_3j(int l1, int l2, int l3, int m1, int m2, int m3) {
+    if (m1 + m2 + m3 != 0) return 0.0;
+    double sum = 0.0;
+    for (int k = 0; k <= l1 + l2 - l3; ++k) {
+        const int a = l3 - l2 + k + m1, b = l3 - l1 + k - m2, c = l1 - k - m1, d = l2 - k + m2;
+        if (a < 0 || b < 0 || c < 0 || d < 0) continue;
+        sum += ((k & 1) ? -1.0 : 1.0) / (ace_fact(k) * ace_fact(l1 + l2 - l3 - k) * ace_fact(a) * ace_fact(b) *
+                                         ace_fact(c) * ace_fact(d));
     }
-    // rank 3 by groups (p1, p2, l3): P(m3) once, then every n3 of the group
-    // the next group's header is loaded while the current group is formed
-    // (a wave past the last group re-reads group 0, unused)
-    // (its outputs come with it: no load between the group and its LDS reads)
-    auto header = [&](int gi, int (&h)[kAceGroupInts]) {
-        const int* gr = groups + kAceGroupInts * (gi < n_groups ? gi : 0);
-#pragma unroll
-        for (int i = 0; i < kAceGroupInts; ++i) h[i] = gr[i];
-    };
-    int nxt[kAceGroupInts] = {};
-    if (n_groups > 0) header(wave, nxt);
-    for (int gi = wave; gi < n_groups; gi += kAce3Waves) {
-        int h[kAceGroupInts];
-#pragma unroll
-        for (int i = 0; i < kAceGroupInts; ++i) h[i] = nxt[i];
-        header(gi + kAce3Waves, nxt);
-        const float* cf = coef + __builtin_amdgcn_readfirstlane(h[0]);
-        const int l3 = __builtin_amdgcn_readfirstlane(h[1]);
-        const int oc = __builtin_amdgcn_readfirstlane(h[2]);
-        const int combo = __builtin_amdgcn_readfirstlane(h[3]);
-        const int b1 = __builtin_amdgcn_readfirstlane(h[4]), b2 = __builtin_amdgcn_readfirstlane(h[5]);
-        const int col0 = __builtin_amdgcn_readfirstlane(h[10]), pw = __builtin_amdgcn_readfirstlane(h[11]);
-        float pr[9], pim[9];
-        static_for<0, 125>([&](auto cc) {
-            constexpr int C = decltype(cc)::value;
-            if constexpr (ace3_combo_valid(C)) {
-                if (combo == C) ace3_group<C / 25, (C / 5) % 5, C % 5>(sA, b1, b2, lane, cf, pr, pim);
-            }
-        });
-        // every n3 of the group, by code specialised for l3: the A reads of
-        // an output issue together, with no branch per m3 between them
-        static_for<0, kAceMaxL + 1>([&](auto lc) {
-            constexpr int L3 = decltype(lc)::value;
-            if (l3 != L3) return;
-            static_for<0, kAceN>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                if (k >= oc) return;
-                const int ok = __builtin_amdgcn_readfirstlane(h[6 + k]);
-                const int base3 = ok & 127;
-                float2 c[L3 + 1];
-#pragma unroll
-                for (int am = 0; am <= L3; ++am) c[am] = sA[base3 + am][lane];
-                float v = 0.f;
-                static_for<4 - L3, 5 + L3>([&](auto sc) {
-                    constexpr int slot = decltype(sc)::value;
-                    constexpr int m3 = slot - 4, am = m3 < 0 ? -m3 : m3;
-                    // A_{l3,m3} = A_{l3,|m3|} for m3 >= 0, (-1)^|m3| conj(A_{l3,|m3|}) below
-                    constexpr float sg = (m3 < 0 && (am & 1)) ? -1.f : 1.f;
-                    const float cy = m3 < 0 ? -c[am].y : c[am].y;
-                    v = fmaf(sg, pr[slot] * c[am].x - pim[slot] * cy, v);    // Re(P A)
-                });
-                if constexpr (stage) sO[wave][(ok >> 7) - col0][lane] = v;
-                else if (valid) o[(n12 + (ok >> 7)) * ds] = v;
+    const double delta = ace_fact(l1 + l2 - l3) * ace_fact(l1 - l2 + l3) * ace_fact(l2 + l3 - l1) /
+                         ace_fact(l1 + l2 + l3 + 1);
+    const double root = ace_sqrt(delta * ace_fact(l1 + m1) * ace_fact(l1 - m1) * ace_fact(l2 + m2) *
+                                 ace_fact(l2 - m2) * ace_fact(l3 + m3) * ace_fact(l3 - m3));
+    return (((l1 - l2 - m3) & 1) ? -1.0 : 1.0) * root * sum;
+}
+
+// The l3 that couple with (l1, l2) at an even sum, up to lmax: l = |l1-l2| + 2 i.
+struct AceL3 {
+    int lo, n, reals;      // first l3, how many, real numbers of their A (2 l3 + 1 each)
+};
+__host__ __device__ constexpr AceL3 ace_l3(int l1, int l2, int lmax) {
+    AceL3 r{l1 > l2 ? l1 - l2 : l2 - l1, 0, 0};
+    for (int l = r.lo; l <= l1 + l2 && l <= lmax; l += 2) {
+        ++r.n;
+        r.reals += 2 * l + 1;
+    }
+    return r;
+}
+// Position of (l3, M >= 0)'s real part among them (the imaginary part of M > 0 behind it)
+__host__ __device__ constexpr int ace_l3_re(int lo, int l3, int M) {
+    int o = 0;
+    for (int l = lo; l < l3; l += 2) o += 2 * l + 1;
+    return o + (M ? 2 * M - 1 : 0);
+}
+
+// Where a lane's values of one tile go.  PT points per tile; the 64 / PT lane
+// groups of a wave work on different pairs.  Point-major (PT = 16): whole rows in
+// LDS, written at the end as one contiguous piece (segments of a row written when
+// their pair was done left partial lines: 53 million write requests for 11
+// million lines' worth at 300,007 points); a value that the lane's pair does not
+// have goes to a spare word, which costs less than a branch around each.
+// Descriptor-major (PT = 64): stored at once, one plane per column.
+template <int PT>
+struct AceOut {
+    static constexpr bool kRows = PT < kTile;
+    float* to;             // the lane's point: its row in LDS, or its element of plane 0
+    float* spare;          // kAceMaxPairCols words per lane, a word apart between lanes (rows only)
+    int64_t ds;            // plane stride
+    bool valid;
+    // value c of a pair whose own values begin at c = first, in column col0
+    __device__ __forceinline__ void put(int col0, int c, int first, float v) const {
+        if constexpr (kRows) (c >= first ? to + (col0 - first) : spare)[c] = v;
+        else if (valid && c >= first) to[(col0 - first + c) * ds] = v;
+    }
+};
+
+// A wave's place in its list of rounds: the kind of the round and the lane's pair.
+template <int PT>
+struct AceRounds {
+    const int* r;          // this round (LDS)
+    const int* end;
+    int group;             // the lane's group
+    __device__ __forceinline__ bool more() const { return r < end; }
+    __device__ __forceinline__ void next() { r += ace_round_ints(kTile / PT); }
+    __device__ __forceinline__ int kind() const { return __builtin_amdgcn_readfirstlane(r[0]) & 255; }
+    __device__ __forceinline__ int first_n3() const { return __builtin_amdgcn_readfirstlane(r[0]) >> 8; }
+    __device__ __forceinline__ int pair() const {
+        if constexpr (PT == kTile) return __builtin_amdgcn_readfirstlane(r[1]);
+        else return r[1 + group];
+    }
+};
+
+// Rank 3 of the pairs (n1 l1), (n2 l2), l1 <= l2, of the rounds of one kind, code
+// specialised for (l1, l2).  For an even l-sum the terms of M and -M are conjugates, so
+//   B = P(0) A_{l3,0} + sum_{M>=1} 2 (-1)^M Re[P(M) conj A_{l3,M}],
+//   P(M) = sum_m1 (l1 l2 l3; m1, M - m1, -M) A1(m1) A2(M - m1);
+// a product of the pair is formed once for every l3, A of the third factor stays
+// in registers over the rounds, and every index, sign and 3j symbol is a constant.
+template <int PT, int L1, int L2, int LMAX>
+__device__ __forceinline__ void ace3_rounds(const float2* a, const AceOut<PT>& o, AceRounds<PT>& rounds, int nmax) {
+    constexpr AceL3 S = ace_l3(L1, L2, LMAX);
+    float a3[kAceN][S.reals];
+    static_for<0, kAceN>([&](auto nc) {
+        constexpr int n3 = decltype(nc)::value;
+        static_for<0, S.n>([&](auto ic) {
+            constexpr int l = S.lo + 2 * decltype(ic)::value;
+            static_for<0, l + 1>([&](auto mc) {
+                constexpr int M = decltype(mc)::value, e = ace_l3_re(S.lo, l, M);
+                const float2 v = a[(n3 * kAceLm + l * (l + 1) / 2 + M) * PT];
+                a3[n3][e] = v.x;
+                if constexpr (M > 0) a3[n3][e + 1] = v.y;
             });
         });
-        if (stage && (pw >> 8)) {                     // the pair's last group: write its columns
-            const int ncol = pw & 255;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int rows = kTile / ncol, r_l = lane / ncol, c_l = lane - r_l * ncol;
-            const int64_t t0 = (int64_t)blockIdx.x * kTile;
-            for (int r0 = 0; r0 < kTile; r0 += rows) {
-                const int r = r0 + r_l;
-                if (r_l < rows && r < kTile && t0 + r < n_pts)
-                    out[(t0 + r) * ps + (n12 + col0 + c_l)] = sO[wave][c_l][r];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    });
+#pragma clang loop unroll(disable)
+    do {
+        const int pr = rounds.pair(), n3_lo = rounds.first_n3();
+        const float2* s1 = a + (pr & 3) * (kAceLm * PT);
+        const float2* s2 = a + ((pr >> 2) & 3) * (kAceLm * PT);
+        float2 a1[L1 + 1], a2[L2 + 1];
+        static_for<0, L1 + 1>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            a1[m] = s1[(L1 * (L1 + 1) / 2 + m) * PT];
+        });
+        static_for<0, L2 + 1>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            a2[m] = s2[(L2 * (L2 + 1) / 2 + m) * PT];
+        });
+        float p[S.reals];
+        static_for<0, S.reals>([&](auto ec) { p[decltype(ec)::value] = 0.f; });
+        static_for<0, (L1 < L2 ? L1 : L2) + 1>([&](auto mc) {             // M = 0: m1 = m, m2 = -m and their conjugates
+            constexpr int m = decltype(mc)::value;
+            const float x = m ? fmaf(a1[m].x, a2[m].x, a1[m].y * a2[m].y) : a1[0].x * a2[0].x;
+            static_for<0, S.n>([&](auto ic) {
+                constexpr int l = S.lo + 2 * decltype(ic)::value, e = ace_l3_re(S.lo, l, 0);
+                constexpr float c = (float)(ace_3j(L1, L2, l, m, -m, 0) * (m == 0 ? 1.0 : (m & 1) ? -2.0 : 2.0));
+                p[e] = fmaf(c, x, p[e]);
+            });
+        });
+        static_for<1, S.lo + 2 * (S.n - 1) + 1>([&](auto Mc) {
+            constexpr int M = decltype(Mc)::value;
+            static_for<0, 2 * L1 + 1>([&](auto jc) {
+                constexpr int m1 = decltype(jc)::value - L1, m2 = M - m1;
+                if constexpr (m2 >= -L2 && m2 <= L2) {
+                    constexpr int am1 = m1 < 0 ? -m1 : m1, am2 = m2 < 0 ? -m2 : m2;
+                    // A_{l,-m} = (-1)^m conj A_{l,m}
+                    constexpr bool neg = ((m1 < 0 && (am1 & 1)) != (m2 < 0 && (am2 & 1))) != ((M & 1) != 0);
+                    const float ax = a1[am1].x, ay = m1 < 0 ? -a1[am1].y : a1[am1].y;
+                    const float bx = a2[am2].x, by = m2 < 0 ? -a2[am2].y : a2[am2].y;
+                    float xr, xi;
+                    if constexpr (am1 == 0) { xr = ax * bx; xi = ax * by; }
+                    else if constexpr (am2 == 0) { xr = ax * bx; xi = ay * bx; }
+                    else { xr = fmaf(ax, bx, -ay * by); xi = fmaf(ax, by, ay * bx); }
+                    static_for<0, S.n>([&](auto ic) {
+                        constexpr int l = S.lo + 2 * decltype(ic)::value;
+                        if constexpr (l >= M) {
+                            constexpr int e = ace_l3_re(S.lo, l, M);
+                            constexpr float c = (float)(ace_3j(L1, L2, l, m1, m2, -M) * (neg ? -2.0 : 2.0));
+                            p[e] = fmaf(c, xr, p[e]);
+                            p[e + 1] = fmaf(c, xi, p[e + 1]);
+                        }
+                    });
+                }
+            });
+        });
+        // the pair's columns are (n3, l3) in order, from its later key on
+        const int first = (pr >> 4) & 15, col0 = pr >> 8;
+        static_for<0, kAceN>([&](auto nc) {
+            constexpr int n3 = decltype(nc)::value;
+            if (n3 < n3_lo || n3 >= nmax) return;
+            static_for<0, S.n>([&](auto ic) {
+                constexpr int i = decltype(ic)::value, l = S.lo + 2 * i, e0 = ace_l3_re(S.lo, l, 0);
+                float v = p[e0] * a3[n3][e0];
+#pragma unroll
+                for (int e = 1; e < 2 * l + 1; ++e) v = fmaf(p[e0 + e], a3[n3][e0 + e], v);
+                o.put(col0, n3 * S.n + i, first, v);
+            });
+        });
+        rounds.next();
+    } while (rounds.more() && rounds.kind() == L1 * (kAceL + 1) + L2);
+}
+
+// Rank 2 of one l: sum_m (-1)^m A_{n1 l m} A_{n2 l -m}
+//   = A_{n1 l 0} A_{n2 l 0} + 2 sum_{m>0} Re(A_{n1 l m} conj(A_{n2 l m})).
+template <int PT, int L>
+__device__ __forceinline__ void ace2_round(const float2* a, const AceOut<PT>& o, int pr) {
+    const float2* s1 = a + ((pr & 3) * kAceLm + L * (L + 1) / 2) * PT;
+    const float2* s2 = a + (((pr >> 2) & 3) * kAceLm + L * (L + 1) / 2) * PT;
+    float s = 0.f;
+    static_for<1, L + 1>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        const float2 x = s1[m * PT], y = s2[m * PT];
+        s = fmaf(x.x, y.x, fmaf(x.y, y.y, s));
+    });
+    o.put(pr >> 8, 0, (pr >> 4) & 15, fmaf(2.f, s, s1[0].x * s2[0].x));
+}
+
+// Ranks 1-3 of one tile from its projected A.  Bound by the VALU (17,000 of its
+// instructions per 64 points in rank 3 at nmax = lmax = 4, if every lane group has
+// a pair) beside the 2.4 KB of output per point.  Rounds of up to 64 / PT pairs of
+// one (l1, l2) are dealt to the waves by their cost.  One product of a pair for
+// all its l3, M >= 0 only, constant 3j symbols and whole rows written, where every
+// (p1, p2, l3) formed its own products for every m3 from a table of symbols and
+// wrote segments of rows: 745 -> 335 us per 300,007 points, point-major.
+template <int PT, int LMAX>
+__global__ __launch_bounds__(64 * kAce3Waves, 4) void k_ace(const float2* __restrict__ Ag, int nmax, int64_t n_pts,
+                                                           const int* __restrict__ plan, int plan_ints, int n_desc,
+                                                           float* __restrict__ out, int64_t ds) {
+    extern __shared__ float4 ace_lds[];
+    float2* sA = reinterpret_cast<float2*>(ace_lds);                       // [kAceAPerPoint][PT]
+    int* sPlan = reinterpret_cast<int*>(sA + kAceAPerPoint * PT);
+    // PT rows (point-major), as they lie in memory, and the spare words
+    float* sO = reinterpret_cast<float*>(sPlan + (plan_ints + 3) / 4 * 4);
+    const int lane = threadIdx.x & 63, pt = lane % PT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t p0 = (int64_t)blockIdx.x * PT;
+    {
+        // the block's points of a 64-point tile of A
+        const float2* src = Ag + p0 / kTile * (kAceAPerPoint * kTile) + p0 % kTile;
+        for (int e = threadIdx.x; e < kAceAPerPoint * PT; e += blockDim.x) sA[e] = src[e / PT * kTile + e % PT];
+        for (int e = threadIdx.x; e < plan_ints; e += blockDim.x) sPlan[e] = plan[e];
+    }
+    __syncthreads();
+    AceOut<PT> o;
+    o.ds = ds;
+    o.valid = p0 + pt < n_pts;
+    if constexpr (o.kRows) {
+        o.to = sO + pt * n_desc;
+        o.spare = sO + PT * n_desc + lane;
+    } else {
+        o.to = out + p0 + pt;
+    }
+    const float2* a = sA + pt;
+    AceRounds<PT> rounds;
+    rounds.group = lane / PT;
+    rounds.r = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave]);
+    rounds.end = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave + 1]);
+    while (rounds.more()) {
+        const int kind = rounds.kind();
+        if (kind >= kAceRank2) {
+            const int pr = rounds.pair();
+            static_for<0, LMAX + 1>([&](auto lc) {
+                constexpr int L = decltype(lc)::value;
+                if (kind == kAceRank2 + L) ace2_round<PT, L>(a, o, pr);
+            });
+            if (kind == kAceRank1) o.put(pr >> 8, 0, (pr >> 4) & 15, a[(pr & 3) * (kAceLm * PT)].x);
+            rounds.next();
+        } else {
+            static_for<0, LMAX + 1>([&](auto c1) {
+                static_for<decltype(c1)::value, LMAX + 1>([&](auto c2) {
+                    constexpr int L1 = decltype(c1)::value, L2 = decltype(c2)::value;
+                    if (kind == L1 * (kAceL + 1) + L2) ace3_rounds<PT, L1, L2, LMAX>(a, o, rounds, nmax);
+                });
+            });
         }
+    }
+    if constexpr (o.kRows) {
+        __syncthreads();
+        const int n = (int)(n_pts - p0 < PT ? n_pts - p0 : PT) * n_desc;
+        float* to = out + p0 * n_desc;
+        int done = 0;
+        if ((reinterpret_cast<uintptr_t>(to) & 15) == 0) {
+            done = n & ~3;
+            for (int i = threadIdx.x; i < n / 4; i += blockDim.x)
+                reinterpret_cast<float4*>(to)[i] = reinterpret_cast<const float4*>(sO)[i];
+        }
+        for (int i = done + threadIdx.x; i < n; i += blockDim.x) to[i] = sO[i];
     }
 }
 
@@ -603,19 +684,35 @@ hipError_t launch_planes_to_rows(hipStream_t s, const float* in, int64_t ld, int
     return hipGetLastError();
 }
 
-hipError_t launch_ace(hipStream_t s, const float2* Ag, int nmax, int lmax, int64_t n_pts, const int* groups,
-                      int n_groups, const float* coef, int n_desc, float* out, int64_t ps,
-                      int64_t ds) {
-    if (n_pts <= 0) return hipSuccess;
-    if (nmax < 1 || nmax > kAceN || lmax < 0 || lmax > kAceL) return hipErrorInvalidValue;
-    const int64_t n_tiles = (n_pts + kTile - 1) / kTile;
-    if (ds == 1)
-        hipLaunchKernelGGL(k_ace<true>, dim3((unsigned)n_tiles), dim3(64 * kAce3Waves), 0, s, Ag, nmax, lmax, n_pts,
-                           groups, n_groups, coef, n_desc, out, ps, ds);
-    else
-        hipLaunchKernelGGL(k_ace<false>, dim3((unsigned)n_tiles), dim3(64 * kAce3Waves), 0, s, Ag, nmax, lmax, n_pts,
-                           groups, n_groups, coef, n_desc, out, ps, ds);
+template <int PT, int LMAX>
+static hipError_t ace_run(hipStream_t s, const float2* Ag, int nmax, int64_t n_pts, const int* plan, int plan_ints,
+                          int n_desc, float* out, int64_t ds) {
+    const size_t lds = sizeof(float2) * kAceAPerPoint * PT + sizeof(int) * ((plan_ints + 3) / 4 * 4) +
+                       (PT < kTile ? sizeof(float) * (PT * n_desc + 64 + kAceMaxPairCols) : 0);
+    hipLaunchKernelGGL((k_ace<PT, LMAX>), dim3((unsigned)((n_pts + PT - 1) / PT)), dim3(64 * kAce3Waves), lds, s, Ag,
+                       nmax, n_pts, plan, plan_ints, n_desc, out, ds);
     return hipGetLastError();
+}
+
+template <int PT>
+static hipError_t ace_lmax(hipStream_t s, const float2* Ag, int nmax, int lmax, int64_t n_pts, const int* plan,
+                           int plan_ints, int n_desc, float* out, int64_t ds) {
+    switch (lmax) {
+    case 0: return ace_run<PT, 0>(s, Ag, nmax, n_pts, plan, plan_ints, n_desc, out, ds);
+    case 1: return ace_run<PT, 1>(s, Ag, nmax, n_pts, plan, plan_ints, n_desc, out, ds);
+    case 2: return ace_run<PT, 2>(s, Ag, nmax, n_pts, plan, plan_ints, n_desc, out, ds);
+    case 3: return ace_run<PT, 3>(s, Ag, nmax, n_pts, plan, plan_ints, n_desc, out, ds);
+    case 4: return ace_run<PT, 4>(s, Ag, nmax, n_pts, plan, plan_ints, n_desc, out, ds);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_ace(hipStream_t s, const float2* Ag, int nmax, int lmax, int64_t n_pts, const int* plan,
+                      int plan_ints, bool rows, int n_desc, float* out, int64_t ds) {
+    if (n_pts <= 0) return hipSuccess;
+    if (nmax < 1 || nmax > kAceN) return hipErrorInvalidValue;
+    return rows ? ace_lmax<kAceRowPoints>(s, Ag, nmax, lmax, n_pts, plan, plan_ints, n_desc, out, ds)
+                : ace_lmax<kTile>(s, Ag, nmax, lmax, n_pts, plan, plan_ints, n_desc, out, ds);
 }
 
 }  // namespace mala

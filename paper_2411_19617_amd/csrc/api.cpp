@@ -103,13 +103,9 @@ struct Ace4Tables {
     int4* descs = nullptr;
 };
 
-struct AceTables {
-    bool ready = false;
-    int n3 = 0, n_groups = 0;
-    int* groups = nullptr;            // point-major plan
-    int* groups_dm = nullptr;         // descriptor-major order
-    int n_groups_dm = 0;
-    float* coef = nullptr;
+struct AceTables {                    // point-major, descriptor-major
+    int* plan[2] = {nullptr, nullptr};
+    int plan_ints[2] = {0, 0};
 };
 
 }  // namespace
@@ -598,11 +594,9 @@ mala_status mala_destroy(mala_ctx* c) {
     if (c->err) (void)hipFree(c->err);
     if (c->li_coef) (void)hipFree(c->li_coef);
     for (auto& row : c->ace)
-        for (auto& a : row) {
-            if (a.groups) (void)hipFree(a.groups);
-            if (a.groups_dm) (void)hipFree(a.groups_dm);
-            if (a.coef) (void)hipFree(a.coef);
-        }
+        for (auto& a : row)
+            for (int* p : a.plan)
+                if (p) (void)hipFree(p);
     for (auto& row : c->ace4)
         for (auto& a : row) {
             if (a.l_units) (void)hipFree(a.l_units);
@@ -917,26 +911,24 @@ mala_status mala_ace_descriptors(mala_ctx* c, const double* positions, int32_t n
     if (!out) return fail(MALA_E_INVALID_ARG, "out is NULL");
     DeviceGuard g(c->device);
     AceTables& t = c->ace[nmax][lmax];
-    if (!t.ready) {
-        std::vector<int> groups, groups_dm;
-        std::vector<float> coef;
-        t.n3 = build_ace_tables(nmax, lmax, groups, groups_dm, coef);
-        if (t.n3 < 0) return fail(MALA_E_UNSUPPORTED, "grid ACE: a pair's outputs exceed the staging columns");
-        t.n_groups = (int)(groups.size() / kAceGroupInts);
-        t.n_groups_dm = (int)(groups_dm.size() / kAceGroupInts);
-        c->n_allocs += 3;
-        HIP_TRY(hipMalloc(&t.groups, sizeof(int) * (groups.size() ? groups.size() : 1)));
-        HIP_TRY(hipMalloc(&t.groups_dm, sizeof(int) * (groups_dm.size() ? groups_dm.size() : 1)));
-        HIP_TRY(hipMalloc(&t.coef, sizeof(float) * (coef.size() ? coef.size() : 1)));
-        HIP_TRY(hipMemcpy(t.groups, groups.data(), sizeof(int) * groups.size(), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(t.groups_dm, groups_dm.data(), sizeof(int) * groups_dm.size(), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(t.coef, coef.data(), sizeof(float) * coef.size(), hipMemcpyHostToDevice));
-        t.ready = true;
+    const bool rows = layout == MALA_LAYOUT_POINT_MAJOR;
+    int*& plan_d = t.plan[rows ? 0 : 1];
+    int& plan_ints = t.plan_ints[rows ? 0 : 1];
+    if (!plan_d) {
+        std::vector<int> plan;
+        build_ace_plan(nmax, lmax, rows ? kTile / kAceRowPoints : 1, plan);
+        plan_ints = (int)plan.size();
+        ++c->n_allocs;
+        int* d = nullptr;
+        HIP_TRY(hipMalloc(&d, sizeof(int) * plan.size()));
+        const hipError_t e = hipMemcpy(d, plan.data(), sizeof(int) * plan.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) (void)hipFree(d);
+        HIP_TRY(e);
+        plan_d = d;
     }
-    const int n_desc = ace_count_ranks12(nmax, lmax) + t.n3;
+    const int n_desc = mala_ace_count(nmax, lmax);
     // point-major [point][descriptor] or descriptor-major [descriptor][point]
-    const int64_t ps = layout == MALA_LAYOUT_POINT_MAJOR ? n_desc : 1;
-    const int64_t ds = layout == MALA_LAYOUT_POINT_MAJOR ? 1 : pt_end - pt_begin;
+    const int64_t ps = rows ? n_desc : 1, ds = pt_end - pt_begin;
     if ((st = upload_positions(c, positions, n_atoms))) return st;
     BinState bs{};
     if ((st = bin_atoms(c, n_atoms, cg, rcut, &bs))) return st;
@@ -948,9 +940,7 @@ mala_status mala_ace_descriptors(mala_ctx* c, const double* positions, int32_t n
         HIP_TRY(staged(c, MALA_STAGE_ACE, n, [&] {
             hipError_t e = launch_ace_proj(c->stream, bs, cg->N, rcut, pt_begin + off, n, c->aceA.p, c->err);
             if (e != hipSuccess) return e;
-            const bool pm = ds == 1;              // staged point-major rows, else plain stores
-            return launch_ace(c->stream, c->aceA.p, nmax, lmax, n, pm ? t.groups : t.groups_dm,
-                              pm ? t.n_groups : t.n_groups_dm, t.coef, n_desc, out + off * ps, ps, ds);
+            return launch_ace(c->stream, c->aceA.p, nmax, lmax, n, plan_d, plan_ints, rows, n_desc, out + off * ps, ds);
         }));
     }
     return MALA_OK;

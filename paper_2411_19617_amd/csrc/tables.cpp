@@ -202,156 +202,98 @@ int ace_count_rank3(int nmax, int lmax) {
     return nd;
 }
 
-// Rank-3 grid ACE tables.  The descriptors (multisets of three (n, l)
-// pairs, key p = n (lmax+1) + l, p1 <= p2 <= p3, l1+l2+l3 even and triangle,
-// in that order) are grouped by (p1, p2, l3).  A group's partial sums
-//   P(m3) = sum_m1 (l1 l2 l3; m1, -m1-m3, m3) A_{n1 l1 m1} A_{n2 l2 -m1-m3}
-// are formed once and every descriptor of the group is
-//   B = sum_m3 P(m3) A_{n3 l3 m3}.
-// A is stored for m >= 0 only (A_{l,-m} = (-1)^m conj(A_{l,m})) at n*15 +
-// l(l+1)/2 + |m|.  The kernel evaluates a group with code specialised for
-// its (l1, l2, l3), so the 3j symbols of each such combination form one block
-// of coefficients shared by all groups of that combination, in the order
-// m3 = -l3..l3, m1 = -l1..l1 with |m1 + m3| <= l2 (zeros included).  Per group:
-// groups[8g..8g+7] = {offset of its coefficient block, l3, first output,
-// output count, l1*25 + l2*5 + l3, storage base of (n1, l1), of (n2, l2), 0};
-// outputs pack the storage base n3*15 + l3(l3+1)/2 (bits 0-6) and the
-// descriptor's rank-3 position (bits 7 and up).  The 3j symbol comes from the
-// coupled states of couple(): (l1 l2 l3; m1 m2 m3) = (-1)^(l1-l2-m3)
-// <l1 m1 l2 m2 | l3 -m3> / sqrt(2 l3 + 1).
-int build_ace_tables(int nmax, int lmax, std::vector<int>& groups, std::vector<int>& groups_dm,
-                     std::vector<float>& coef) {
-    groups.clear();
-    groups_dm.clear();
-    coef.clear();
-    std::vector<Coupling> cache(25 * 25);
-    std::vector<bool> have(cache.size(), false);
-    auto three_j = [&](int l1, int l2, int l3, int m1, int m2, int m3) {
-        const int J1 = 2 * l1, J2 = 2 * l2, J = 2 * l3;
-        const int key = J1 * 25 + J2;
-        if (!have[key]) {
-            cache[key] = couple(J1, J2);
-            have[key] = true;
-        }
-        const Coupling& c = cache[key];
-        const int D = (J1 + J2 - J) / 2;
-        const int ma = l3 - m3, ma1 = l1 + m1, ma2 = l2 + m2;     // <l1 m1 l2 m2 | l3, -m3>
-        const double cg = c.vec[D][ma][pidx(J2, ma1, ma2)];
-        const int ph = l1 - l2 - m3;
-        return ((ph % 2 + 2) % 2 ? -1.0 : 1.0) * cg / sqrt(2.0 * l3 + 1.0);
-    };
-    const int np = nmax * (lmax + 1);
-    // rank-3 position of every descriptor, in the output order
-    std::vector<int> pos_of(np * np * np, -1);
-    int nd = 0;
-    for (int p1 = 0; p1 < np; ++p1)
-        for (int p2 = p1; p2 < np; ++p2)
-            for (int p3 = p2; p3 < np; ++p3) {
-                const int l1 = p1 % (lmax + 1), l2 = p2 % (lmax + 1), l3 = p3 % (lmax + 1);
-                if (l3 < abs(l1 - l2) || l3 > l1 + l2 || (l1 + l2 + l3) % 2) continue;
-                pos_of[(p1 * np + p2) * np + p3] = nd++;
-            }
-    std::vector<int> block_of(125, -1);
-    struct Pair {
-        std::vector<std::array<int, kAceGroupInts>> groups;
-        int col0 = -1, ncol = 0;
-        long cost = 0;
-    };
-    std::vector<Pair> pairs;
+// Plan of ranks 1-3 (layout in ace.h).  Rank-3 columns follow the order
+// p1 <= p2 <= p3 of the keys p = n (lmax+1) + l.  The pairs of one (l1, l2), those
+// whose later key has the largest n first so that a round's outputs start at as
+// high an n3 as they can, fill rounds; runs of rounds go to the waves by cost
+// (VALU instructions), longest first to the least loaded.
+void build_ace_plan(int nmax, int lmax, int groups, std::vector<int>& plan) {
+    const int nl = lmax + 1, np = nmax * nl;
+    std::vector<int> col(np * np, 0);                // first column of (p1, p2)
+    int next = ace_count_ranks12(nmax, lmax);
     for (int p1 = 0; p1 < np; ++p1)
         for (int p2 = p1; p2 < np; ++p2) {
-            Pair pr;
-            for (int l3 = 0; l3 <= lmax; ++l3) {
-                const int n1 = p1 / (lmax + 1), l1 = p1 % (lmax + 1), n2 = p2 / (lmax + 1), l2 = p2 % (lmax + 1);
-                if (l3 < abs(l1 - l2) || l3 > l1 + l2 || (l1 + l2 + l3) % 2) continue;
-                std::vector<int> outs;
-                for (int n3 = 0; n3 < nmax; ++n3) {
-                    const int p3 = n3 * (lmax + 1) + l3;
-                    if (p3 < p2) continue;
-                    outs.push_back((n3 * 15 + l3 * (l3 + 1) / 2) | (pos_of[(p1 * np + p2) * np + p3] << 7));
-                }
-                if (outs.empty()) continue;
-                const int combo = l1 * 25 + l2 * 5 + l3;
-                int terms = 0;                   // structural terms (m3, m1) of the combination
-                for (int m3 = -l3; m3 <= l3; ++m3)
-                    for (int m1 = -l1; m1 <= l1; ++m1)
-                        terms += abs(m1 + m3) <= l2;
-                if (block_of[combo] < 0) {
-                    block_of[combo] = (int)coef.size();
-                    for (int m3 = -l3; m3 <= l3; ++m3)
-                        for (int m1 = -l1; m1 <= l1; ++m1) {
-                            const int m2 = -m1 - m3;
-                            if (abs(m2) > l2) continue;
-                            coef.push_back((float)three_j(l1, l2, l3, m1, m2, m3));
-                        }
-                }
-                // header: coefficient block, l3, output count, combination, the
-                // two A row bases, the outputs (one per n3 <= nmax <= 4), then
-                // the pair's columns (filled below)
-                std::array<int, kAceGroupInts> g{};
-                g[0] = block_of[combo];
-                g[1] = l3;
-                g[2] = (int)outs.size();
-                g[3] = combo;
-                g[4] = n1 * 15 + l1 * (l1 + 1) / 2;
-                g[5] = n2 * 15 + l2 * (l2 + 1) / 2;
-                for (size_t i = 0; i < outs.size(); ++i) {
-                    g[6 + i] = outs[i];
-                    const int pos = outs[i] >> 7;
-                    if (pr.col0 < 0 || pos < pr.col0) pr.col0 = pos;
-                    ++pr.ncol;
-                }
-                pr.cost += terms + (long)outs.size() * (2 * l3 + 1);
-                pr.groups.push_back(g);
+            col[p1 * np + p2] = next;
+            const int l1 = p1 % nl, l2 = p2 % nl;
+            for (int p3 = p2; p3 < np; ++p3) {
+                const int l3 = p3 % nl;
+                next += l3 >= abs(l1 - l2) && l3 <= l1 + l2 && (l1 + l2 + l3) % 2 == 0;
             }
-            if (pr.groups.empty()) continue;
-            // the kernel stages a pair's outputs by column - col0: they must be
-            // exactly the columns col0 .. col0 + ncol - 1
-            std::vector<int> cols;
-            for (const auto& g : pr.groups)
-                for (int i = 0; i < g[2]; ++i) cols.push_back(g[6 + i] >> 7);
-            std::sort(cols.begin(), cols.end());
-            for (size_t i = 0; i < cols.size(); ++i)
-                if (cols[i] != pr.col0 + (int)i) return -1;
-            if (pr.ncol > kAceMaxPairCols) return -1;
-            for (const auto& g : pr.groups)                     // (p1, p2, l3) order
-                for (int i = 0; i < kAceGroupInts; ++i) groups_dm.push_back(g[i]);
-            pairs.push_back(pr);
         }
-    // whole pairs to the waves, longest first to the least loaded (LPT)
-    std::vector<int> order(pairs.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return pairs[a].cost > pairs[b].cost; });
+    struct Run { long cost; std::vector<int> rounds; };
+    struct Pair { int n1, n2, later, first, col; };  // later: n of the later key
+    std::vector<Run> runs;
+    // one run: the pairs in rounds; set up once, `each` per round, `third` per n3 a round forms
+    auto add = [&](int kind, const std::vector<Pair>& pairs, long setup, long each, long third) {
+        Run r{setup, {}};
+        for (size_t i = 0; i < pairs.size(); i += groups) {
+            int lo = nmax;
+            std::vector<int> entry(groups, 15 << 4);
+            for (size_t g = 0; g < (size_t)groups && i + g < pairs.size(); ++g) {
+                const Pair& p = pairs[i + g];
+                lo = std::min(lo, p.later);
+                entry[g] = p.n1 | p.n2 << 2 | p.first << 4 | p.col << 8;
+            }
+            r.rounds.push_back(kind | lo << 8);
+            r.rounds.insert(r.rounds.end(), entry.begin(), entry.end());
+            r.cost += each + third * (nmax - lo);
+        }
+        if (!r.rounds.empty()) runs.push_back(r);
+    };
+    std::vector<Pair> pairs;
+    for (int n = 0; n < nmax; ++n) pairs.push_back({n, 0, 0, 0, n});
+    add(kAceRank1, pairs, 10, 15, 0);
+    for (int l = 0; l <= lmax; ++l) {
+        pairs.clear();
+        int c = nmax + l * nmax * (nmax + 1) / 2;
+        for (int n1 = 0; n1 < nmax; ++n1)
+            for (int n2 = n1; n2 < nmax; ++n2) pairs.push_back({n1, n2, 0, 0, c++});
+        add(kAceRank2 + l, pairs, 10, 20 + 4 * l, 0);
+    }
+    for (int l1 = 0; l1 <= lmax; ++l1)
+        for (int l2 = l1; l2 <= lmax; ++l2) {
+            long each = 30, third = 0, reads = 0;
+            int below1 = 0, below2 = 0, n_l3 = 0;    // of the l3: below l1, below l2, all
+            for (int l3 = l2 - l1; l3 <= l1 + l2 && l3 <= lmax; l3 += 2) {
+                below1 += l3 < l1;
+                below2 += l3 < l2;
+                ++n_l3;
+            }
+            for (int M = 0; M <= l1 + l2; ++M) {
+                int terms = 0, nl3 = 0;
+                for (int m = -l1; m <= l1; ++m) terms += abs(M - m) <= l2;
+                for (int l3 = l2 - l1; l3 <= l1 + l2 && l3 <= lmax; l3 += 2) nl3 += l3 >= M;
+                if (nl3 == 0) continue;
+                each += M ? terms * (4 + 2 * nl3) : (terms + 1) / 2 * (2 + nl3);
+                third += nl3 * (M ? 2 : 1);
+                reads += nl3;
+            }
+            third += 3 * n_l3;
+            pairs.clear();
+            for (int later = nmax - 1; later >= 0; --later)
+                for (int n = 0; n <= later; ++n) {
+                    // (n l1) (later l2), and, other than for one l, (n l2) (later l1) with n < later
+                    const int f2 = later * n_l3 + below2, f1 = later * n_l3 + below1;
+                    if (f2 < nmax * n_l3) pairs.push_back({n, later, later, f2, col[(n * nl + l1) * np + later * nl + l2]});
+                    if (l1 < l2 && n < later && f1 < nmax * n_l3)
+                        pairs.push_back({later, n, later, f1, col[(n * nl + l2) * np + later * nl + l1]});
+                }
+            add(l1 * (kAceMaxL + 1) + l2, pairs, 60 + 8 * reads, each, third);
+        }
+    std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.cost > b.cost; });
     std::vector<long> load(kAce3Waves, 0);
-    std::vector<std::vector<int>> wave_pairs(kAce3Waves);
-    for (int i : order) {
+    std::vector<std::vector<int>> lists(kAce3Waves);
+    for (const Run& x : runs) {
         const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-        load[w] += pairs[i].cost;
-        wave_pairs[w].push_back(i);
+        load[w] += x.cost;
+        lists[w].insert(lists[w].end(), x.rounds.begin(), x.rounds.end());
     }
-    std::vector<std::vector<std::array<int, kAceGroupInts>>> lists(kAce3Waves);
-    size_t longest = 0;
+    plan.assign(kAce3Waves + 1, 0);
     for (int w = 0; w < kAce3Waves; ++w) {
-        std::sort(wave_pairs[w].begin(), wave_pairs[w].end());
-        for (int i : wave_pairs[w]) {
-            const Pair& pr = pairs[i];
-            for (size_t k = 0; k < pr.groups.size(); ++k) {
-                std::array<int, kAceGroupInts> g = pr.groups[k];
-                g[10] = pr.col0;
-                g[11] = pr.ncol | ((k + 1 == pr.groups.size() ? 1 : 0) << 8);
-                lists[w].push_back(g);
-            }
-        }
-        longest = std::max(longest, lists[w].size());
+        plan[w] = (int)plan.size();
+        plan.insert(plan.end(), lists[w].begin(), lists[w].end());
     }
-    std::array<int, kAceGroupInts> empty{};
-    empty[3] = -1;
-    for (size_t k = 0; k < longest; ++k)
-        for (int w = 0; w < kAce3Waves; ++w) {
-            const std::array<int, kAceGroupInts>& g = k < lists[w].size() ? lists[w][k] : empty;
-            for (int i = 0; i < kAceGroupInts; ++i) groups.push_back(g[i]);
-        }
-    return nd;
+    plan[kAce3Waves] = (int)plan.size();
 }
 
 // Rank-4 grid ACE (Eq. ace_grid with four factors, one intermediate
