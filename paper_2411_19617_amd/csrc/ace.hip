@@ -297,8 +297,9 @@ struct AceRounds {
     const int* r;          // this round (LDS)
     const int* end;
     int group;             // the lane's group
+    int ints;              // of a round
     __device__ __forceinline__ bool more() const { return r < end; }
-    __device__ __forceinline__ void next() { r += ace_round_ints(kTile / PT); }
+    __device__ __forceinline__ void next() { r += ints; }
     __device__ __forceinline__ int kind() const { return __builtin_amdgcn_readfirstlane(r[0]) & 255; }
     __device__ __forceinline__ int first_n3() const { return __builtin_amdgcn_readfirstlane(r[0]) >> 8; }
     __device__ __forceinline__ int pair() const {
@@ -412,6 +413,17 @@ __device__ __forceinline__ void ace2_round(const float2* a, const AceOut<PT>& o,
     o.put(pr >> 8, 0, (pr >> 4) & 15, fmaf(2.f, s, s1[0].x * s2[0].x));
 }
 
+// A block's rows, n floats, from LDS (whole block).
+__device__ __forceinline__ void ace_write_rows(const float* from, int n, float* __restrict__ to) {
+    int done = 0;
+    if ((reinterpret_cast<uintptr_t>(to) & 15) == 0) {
+        done = n & ~3;
+        for (int i = threadIdx.x; i < n / 4; i += blockDim.x)
+            reinterpret_cast<float4*>(to)[i] = reinterpret_cast<const float4*>(from)[i];
+    }
+    for (int i = done + threadIdx.x; i < n; i += blockDim.x) to[i] = from[i];
+}
+
 // Ranks 1-3 of one tile from its projected A.  Bound by the VALU (17,000 of its
 // instructions per 64 points in rank 3 at nmax = lmax = 4, if every lane group has
 // a pair) beside the 2.4 KB of output per point.  Rounds of up to 64 / PT pairs of
@@ -450,6 +462,7 @@ __global__ __launch_bounds__(64 * kAce3Waves, 4) void k_ace(const float2* __rest
     const float2* a = sA + pt;
     AceRounds<PT> rounds;
     rounds.group = lane / PT;
+    rounds.ints = kTile / PT + 1;
     rounds.r = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave]);
     rounds.end = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave + 1]);
     while (rounds.more()) {
@@ -473,15 +486,7 @@ __global__ __launch_bounds__(64 * kAce3Waves, 4) void k_ace(const float2* __rest
     }
     if constexpr (o.kRows) {
         __syncthreads();
-        const int n = (int)(n_pts - p0 < PT ? n_pts - p0 : PT) * n_desc;
-        float* to = out + p0 * n_desc;
-        int done = 0;
-        if ((reinterpret_cast<uintptr_t>(to) & 15) == 0) {
-            done = n & ~3;
-            for (int i = threadIdx.x; i < n / 4; i += blockDim.x)
-                reinterpret_cast<float4*>(to)[i] = reinterpret_cast<const float4*>(sO)[i];
-        }
-        for (int i = done + threadIdx.x; i < n; i += blockDim.x) to[i] = sO[i];
+        ace_write_rows(sO, (int)(n_pts - p0 < PT ? n_pts - p0 : PT) * n_desc, out + p0 * n_desc);
     }
 }
 
@@ -533,7 +538,7 @@ __host__ __device__ constexpr bool ace4_combo_valid(int c) {
     return L >= (l1 > l2 ? l1 - l2 : l2 - l1) && L <= l1 + l2;
 }
 
-// Rank 4 (one intermediate coupling L).  Sixteen waves per 64-point tile
+// Rank 4 (one intermediate coupling L), descriptor-major.  Sixteen waves per 64-point tile
 // (the projected A of the tile in LDS), in phases of one or more L: the
 // coupled pairs P_a(M) = sum_m1 <l1 m1 l2 m2|L M> A_p1 A_p2 (M = 0..L) the
 // descriptors of the phase need are formed into LDS (every wave takes every
@@ -549,7 +554,7 @@ __global__ __launch_bounds__(64 * kAce4Waves) void k_ace4(const float2* __restri
                                                           const float* __restrict__ coef,
                                                           const int* __restrict__ l_descs,
                                                           const int4* __restrict__ descs, int n4,
-                                                          float* __restrict__ out, int64_t ps, int64_t ds) {
+                                                          float* __restrict__ out, int64_t ds) {
     __shared__ float2 sA[kAceN * kAceLm][kTile];
     __shared__ int4 sD[kAce4MaxDescsL];     // this phase's descriptor entries
     extern __shared__ float2 sP[];          // [slots][kTile]
@@ -562,7 +567,7 @@ __global__ __launch_bounds__(64 * kAce4Waves) void k_ace4(const float2* __restri
     ace_load_tile(Ag, sA);
     __syncthreads();
 
-    float* o = out + (tl.valid ? tl.idx : 0) * ps;    // descriptor k at o[k * ds]
+    float* o = out + (tl.valid ? tl.idx : 0);         // descriptor k at o[k * ds]
     for (int ph = 0; ph < n_phases; ++ph) {
         // this phase's descriptor entries into LDS, read back as broadcasts:
         // a scalar load per descriptor would hold every LDS wait of the loop
@@ -620,30 +625,143 @@ __global__ __launch_bounds__(64 * kAce4Waves) void k_ace4(const float2* __restri
     }
 }
 
-// Point-major rows from descriptor planes: out[p * n_cols + k] = in[k * ld + p]
-// for p < n_rows, k < n_cols, through a 64 x 64 LDS block (both sides
-// coalesced); neighbouring blocks take neighbouring row tiles, so the reads
-// of one plane stay together (one block per row tile walking every column
-// block, or column blocks as neighbours, measured slower).
-// Rank 4 writes its planes this way: the columns of one L are spread over
-// the whole row, so its direct point-major stores put every lane's value in
-// a line of its own.
-__global__ __launch_bounds__(256) void k_planes_to_rows(const float* __restrict__ in, int64_t ld, int64_t n_rows,
-                                                        int n_cols, float* __restrict__ out) {
-    __shared__ float sT[64][kTile + 1];
-    const int64_t p0 = (int64_t)blockIdx.x * kTile;
-    const int c0 = blockIdx.y * 64;
-    const int rows = (int)(n_rows - p0 < kTile ? n_rows - p0 : kTile);
-    const int cols = n_cols - c0 < 64 ? n_cols - c0 : 64;
-    for (int e = threadIdx.x; e < 64 * kTile; e += blockDim.x) {
-        const int c = e / kTile, r = e % kTile;
-        if (c < cols && r < rows) sT[c][r] = in[(int64_t)(c0 + c) * ld + p0 + r];
+// Clebsch-Gordan coefficient <l1 m1 l2 m2 | L M> at compile time.
+__host__ __device__ constexpr double ace_cg(int l1, int m1, int l2, int m2, int L, int M) {
+    return (((l1 - l2 + M) & 1) ? -1.0 : 1.0) * ace_sqrt(2 * L + 1) * ace_3j(l1, l2, L, m1, m2, -M);
+}
+
+// P_a(M) of the pairs (n1 l1), (n2 l2), l1 <= l2, of the rounds of one kind, for
+// every L their descriptors need (the others go to spare slots): a product of the
+// pair is formed once for all L.  a, pairs: the lane's point.
+template <int L1, int L2>
+__device__ __forceinline__ void ace4_pair_rounds(const float2* a, float2* pairs, AceRounds<kAce4RowPoints>& rounds) {
+    constexpr int PT = kAce4RowPoints, LO = L2 - L1, HI = L1 + L2;
+#pragma clang loop unroll(disable)
+    do {
+        const int* e = rounds.r + 1 + rounds.group * kAce4PairInts;
+        const int pr = e[0];
+        float2 a1[L1 + 1], a2[L2 + 1];
+        static_for<0, L1 + 1>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            a1[m] = a[((pr & 3) * kAceLm + L1 * (L1 + 1) / 2 + m) * PT];
+        });
+        static_for<0, L2 + 1>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            a2[m] = a[((pr >> 2) * kAceLm + L2 * (L2 + 1) / 2 + m) * PT];
+        });
+        float2* to[HI - LO + 1];
+        static_for<0, HI - LO + 1>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            to[i] = pairs + ((e[1 + i / 3] >> (10 * (i % 3))) & 1023) * PT;
+        });
+        static_for<0, HI + 1>([&](auto Mc) {
+            constexpr int M = decltype(Mc)::value, L0 = M > LO ? M : LO;
+            float xr[HI + 1], xi[HI + 1];
+            static_for<L0, HI + 1>([&](auto Lc) { xr[decltype(Lc)::value] = xi[decltype(Lc)::value] = 0.f; });
+            static_for<0, 2 * L1 + 1>([&](auto jc) {
+                constexpr int m1 = decltype(jc)::value - L1, m2 = M - m1;
+                if constexpr (m2 >= -L2 && m2 <= L2) {
+                    constexpr int am1 = m1 < 0 ? -m1 : m1, am2 = m2 < 0 ? -m2 : m2;
+                    constexpr bool neg = (m1 < 0 && (am1 & 1)) != (m2 < 0 && (am2 & 1));
+                    const float ax = a1[am1].x, ay = m1 < 0 ? -a1[am1].y : a1[am1].y;
+                    const float bx = a2[am2].x, by = m2 < 0 ? -a2[am2].y : a2[am2].y;
+                    float pr_, pi_;
+                    if constexpr (am1 == 0) { pr_ = ax * bx; pi_ = ax * by; }
+                    else if constexpr (am2 == 0) { pr_ = ax * bx; pi_ = ay * bx; }
+                    else { pr_ = fmaf(ax, bx, -ay * by); pi_ = fmaf(ax, by, ay * bx); }
+                    static_for<L0, HI + 1>([&](auto Lc) {
+                        constexpr int L = decltype(Lc)::value;
+                        constexpr double cg = ace_cg(L1, m1, L2, m2, L, M);
+                        if constexpr (cg > 1e-12 || cg < -1e-12) {
+                            constexpr float c = (float)(neg ? -cg : cg);
+                            xr[L] = fmaf(c, pr_, xr[L]);
+                            xi[L] = fmaf(c, pi_, xi[L]);
+                        }
+                    });
+                }
+            });
+            static_for<L0, HI + 1>([&](auto Lc) {
+                constexpr int L = decltype(Lc)::value;
+                to[L - LO][M * PT] = make_float2(xr[L], xi[L]);
+            });
+        });
+        rounds.next();
+    } while (rounds.more() && rounds.kind() == L1 * (kAce4MaxL + 1) + L2);
+}
+
+// Rank 4, point-major: blocks of kAce4RowPoints points with every coupled pair and
+// the whole rows in LDS, so that the pairs are formed and the descriptors
+// evaluated in one pass each and the rows leave as one contiguous piece.  The
+// lane groups of the waves take contiguous shares of the descriptors of one L
+// (sorted by their first pair, whose P_a stays in registers).  Bound by the VALU
+// and the LDS reads of P_b beside 4 n4 bytes of output per point.  Writing planes
+// (in phases of the L that fit) and transposing them moved every value three
+// times: 660 -> 345 us per 150,001 points at nmax4 = lmax4 = 3.  Blocks of 8
+// points leave room for two on a CU (79 KB each).
+__global__ __launch_bounds__(64 * kAce4RowWaves) void k_ace4_rows(const float2* __restrict__ Ag, int64_t n_pts,
+                                                                  const int* __restrict__ plan, int plan_ints,
+                                                                  int n_slots, int n4, float* __restrict__ out) {
+    constexpr int PT = kAce4RowPoints, G = kTile / PT;
+    extern __shared__ float4 ace_lds[];
+    float2* sA = reinterpret_cast<float2*>(ace_lds);                       // [kAce4ARows][PT]
+    float2* sP = sA + kAce4ARows * PT;                                     // [n_slots][PT]
+    float* sO = reinterpret_cast<float*>(sP + n_slots * PT);               // [PT][n4], spare words
+    int* sPlan = reinterpret_cast<int*>(sO + PT * n4 + 64);
+    const int lane = threadIdx.x & 63, pt = lane % PT, group = lane / PT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t p0 = (int64_t)blockIdx.x * PT;
+    {
+        const float2* src = Ag + p0 / kTile * (kAceAPerPoint * kTile) + p0 % kTile;
+        for (int e = threadIdx.x; e < kAce4ARows * PT; e += blockDim.x) sA[e] = src[e / PT * kTile + e % PT];
+        for (int e = threadIdx.x; e < plan_ints; e += blockDim.x) sPlan[e] = plan[e];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < kTile * 64; e += blockDim.x) {
-        const int r = e / 64, c = e % 64;
-        if (c < cols && r < rows) out[(p0 + r) * n_cols + c0 + c] = sT[c][r];
+    AceRounds<PT> rounds;
+    rounds.group = group;
+    rounds.ints = 1 + G * kAce4PairInts;
+    rounds.r = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave]);
+    rounds.end = sPlan + __builtin_amdgcn_readfirstlane(sPlan[wave + 1]);
+    while (rounds.more()) {
+        const int kind = rounds.kind();
+        static_for<0, kAce4MaxL + 1>([&](auto c1) {
+            static_for<decltype(c1)::value, kAce4MaxL + 1>([&](auto c2) {
+                constexpr int L1 = decltype(c1)::value, L2 = decltype(c2)::value;
+                if (kind == L1 * (kAce4MaxL + 1) + L2) ace4_pair_rounds<L1, L2>(sA + pt, sP + pt, rounds);
+            });
+        });
     }
+    __syncthreads();
+    float* row = sO + pt * n4;
+    float* spare = sO + PT * n4 + lane;
+    const float2* pairs = sP + pt;
+    static_for<0, 2 * kAce4MaxL + 1>([&](auto lc) {
+        constexpr int L = decltype(lc)::value;
+        const int d0 = __builtin_amdgcn_readfirstlane(sPlan[kAce4RowWaves + 1 + L]);
+        const int d1 = __builtin_amdgcn_readfirstlane(sPlan[kAce4RowWaves + 2 + L]);
+        const int share = (d1 - d0 + kAce4RowWaves * G - 1) / (kAce4RowWaves * G);
+        const int first = d0 + (wave * G + group) * share;
+        constexpr float f = (float)(1.0 / ace_sqrt(2 * L + 1));
+        int cached = -1;
+        float2 pa[L + 1];
+#pragma clang loop unroll(disable)
+        for (int k = 0; k < share; ++k) {
+            const int d = first + k, q = sPlan[d < d1 ? d : d1 - 1];
+            const int sa = q & 1023, sb = (q >> 10) & 1023;
+            if (sa != cached) {
+                static_for<0, L + 1>([&](auto mc) { pa[decltype(mc)::value] = pairs[(sa + decltype(mc)::value) * PT]; });
+                cached = sa;
+            }
+            float2 b[L + 1];
+            static_for<0, L + 1>([&](auto mc) { b[decltype(mc)::value] = pairs[(sb + decltype(mc)::value) * PT]; });
+            float acc = 0.f;
+#pragma unroll
+            for (int M = 1; M <= L; ++M) acc = fmaf(pa[M].x, b[M].x, fmaf(pa[M].y, b[M].y, acc));
+            const float v = fmaf(2.f, acc, pa[0].x * b[0].x + pa[0].y * b[0].y) * (q < 0 ? -f : f);
+            *(d < d1 ? row + ((q >> 20) & 1023) : spare) = v;
+        }
+    });
+    __syncthreads();
+    ace_write_rows(sO, (int)(n_pts - p0 < PT ? n_pts - p0 : PT) * n4, out + p0 * n4);
 }
 
 hipError_t launch_ace_proj(hipStream_t s, const BinState& bins, const int N[3], double rcut, int64_t pt_begin,
@@ -657,7 +775,7 @@ hipError_t launch_ace_proj(hipStream_t s, const BinState& bins, const int N[3], 
 
 hipError_t launch_ace4(hipStream_t s, const float2* Ag, int lmax4, int n_phases, int64_t n_pts, const int* l_units,
                        const int4* units, const float* coef, const int* l_descs, const int4* descs, int max_slots,
-                       int n4, float* out, int64_t ps, int64_t ds) {
+                       int n4, float* out, int64_t ds) {
     if (n_pts <= 0 || n4 <= 0) return hipSuccess;
     if (lmax4 < 0 || lmax4 > kAce4MaxL) return hipErrorInvalidValue;
     const size_t lds = sizeof(float2) * (size_t)max_slots * kTile;
@@ -671,16 +789,25 @@ hipError_t launch_ace4(hipStream_t s, const float2* Ag, int lmax4, int n_phases,
     if (lds > kAce4LdsBudget) return hipErrorInvalidValue;
     const int64_t n_tiles = (n_pts + kTile - 1) / kTile;
     hipLaunchKernelGGL(k_ace4, dim3((unsigned)n_tiles), dim3(64 * kAce4Waves), lds, s, Ag, n_phases, n_pts, l_units,
-                       units, coef, l_descs, descs, n4, out, ps, ds);
+                       units, coef, l_descs, descs, n4, out, ds);
     return hipGetLastError();
 }
 
-hipError_t launch_planes_to_rows(hipStream_t s, const float* in, int64_t ld, int64_t n_rows, int n_cols, float* out) {
-    if (n_rows <= 0 || n_cols <= 0) return hipSuccess;
-    if (ld < n_rows) return hipErrorInvalidValue;
-    const int64_t row_tiles = (n_rows + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_planes_to_rows, dim3((unsigned)row_tiles, (unsigned)((n_cols + 63) / 64)), dim3(256), 0, s,
-                       in, ld, n_rows, n_cols, out);
+hipError_t launch_ace4_rows(hipStream_t s, const float2* Ag, int64_t n_pts, const int* plan, int plan_ints, int n_slots,
+                            int n4, float* out) {
+    if (n_pts <= 0 || n4 <= 0) return hipSuccess;
+    constexpr int PT = kAce4RowPoints;
+    const size_t lds = ace4_rows_lds(plan_ints, n_slots, n4);
+    if (lds > kAce4RowsLds) return hipErrorInvalidValue;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ace4_rows),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAce4RowsLds);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    hipLaunchKernelGGL(k_ace4_rows, dim3((unsigned)((n_pts + PT - 1) / PT)), dim3(64 * kAce4RowWaves), lds, s, Ag, n_pts,
+                       plan, plan_ints, n_slots, n4, out);
     return hipGetLastError();
 }
 

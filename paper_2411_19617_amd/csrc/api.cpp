@@ -94,7 +94,9 @@ constexpr int kPredictChunk = 1 << 21;
 constexpr double kWindowMargin = 0.3;     // eV around the E_F estimate kept in the stored LDOS window
 
 struct Ace4Tables {
-    bool ready = false;
+    int* rows_plan = nullptr;            // point-major
+    int rows_ints = 0, n_slots = 0, n_rows = 0;
+    bool ready = false;                  // descriptor-major
     int n4 = 0, max_slots = 0, n_phases = 0;
     int* l_units = nullptr;           // unit and descriptor offsets per phase
     int4* units = nullptr;
@@ -122,7 +124,6 @@ struct mala_ctx {
     DevBuf<float2> u;
     DevBuf<float2> yadj;                 // dL/du of the descriptor adjoint, laid out like u
     DevBuf<float2> aceA;                 // projected grid ACE basis of one chunk [tile][60][64]
-    DevBuf<float> ace4S;                 // rank-4 descriptor planes of one point-major chunk
     DevBuf<float> Bbuf;
     DevBuf<double> partials, est_partials;
     DevBuf<double> fermi_w;
@@ -513,7 +514,6 @@ void ctx_trim(mala_ctx* c) {
     release(c->u);
     release(c->yadj);
     release(c->aceA);
-    release(c->ace4S);
     release(c->Bbuf);
     release(c->window);
     release(c->prefix);
@@ -582,7 +582,6 @@ mala_status mala_destroy(mala_ctx* c) {
     release(c->u);
     release(c->yadj);
     release(c->aceA);
-    release(c->ace4S);
     release(c->Bbuf);
     release(c->partials);
     release(c->est_partials);
@@ -599,6 +598,7 @@ mala_status mala_destroy(mala_ctx* c) {
                 if (p) (void)hipFree(p);
     for (auto& row : c->ace4)
         for (auto& a : row) {
+            if (a.rows_plan) (void)hipFree(a.rows_plan);
             if (a.l_units) (void)hipFree(a.l_units);
             if (a.units) (void)hipFree(a.units);
             if (a.coef) (void)hipFree(a.coef);
@@ -977,7 +977,21 @@ mala_status mala_ace4_descriptors(mala_ctx* c, const double* positions, int32_t 
     if (!out) return fail(MALA_E_INVALID_ARG, "out is NULL");
     DeviceGuard g(c->device);
     Ace4Tables& t = c->ace4[nmax4][lmax4];
-    if (!t.ready) {
+    const bool pm = layout == MALA_LAYOUT_POINT_MAJOR;
+    if (pm && !t.rows_plan) {
+        std::vector<int> plan;
+        build_ace4_rows_plan(nmax4, lmax4, plan, t.n_slots);
+        t.rows_ints = (int)plan.size();
+        t.n_rows = mala_ace4_count(nmax4, lmax4);
+        ++c->n_allocs;
+        int* d = nullptr;
+        HIP_TRY(hipMalloc(&d, sizeof(int) * plan.size()));
+        const hipError_t e = hipMemcpy(d, plan.data(), sizeof(int) * plan.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) (void)hipFree(d);
+        HIP_TRY(e);
+        t.rows_plan = d;
+    }
+    if (!pm && !t.ready) {
         std::vector<int> l_units, l_descs;
         std::vector<int4> units, descs;
         std::vector<float> coef;
@@ -1005,24 +1019,18 @@ mala_status mala_ace4_descriptors(mala_ctx* c, const double* positions, int32_t 
     BinState bs{};
     if ((st = bin_atoms(c, n_atoms, cg, rcut, &bs))) return st;
     const int64_t total = pt_end - pt_begin;
-    const bool pm = layout == MALA_LAYOUT_POINT_MAJOR;
-    // point-major: descriptor planes of each chunk into ace4S, then rows
-    const int64_t chunk_max = pm ? kAce4RowChunk : kChunk;
-    const int64_t chunk = total < chunk_max ? total : chunk_max;
+    const int64_t chunk = total < kChunk ? total : kChunk;
     HIP_TRY(ensure(c->n_allocs, c->aceA, (size_t)((chunk + kTile - 1) / kTile) * kAceAPerPoint * kTile));
-    if (pm) HIP_TRY(ensure(c->n_allocs, c->ace4S, (size_t)chunk * t.n4));
     for (int64_t off = 0; off < total; off += chunk) {
         const int64_t n = (total - off) < chunk ? (total - off) : chunk;
         HIP_TRY(staged(c, MALA_STAGE_ACE4, n, [&] {
             hipError_t e = launch_ace_proj(c->stream, bs, cg->N, rcut, pt_begin + off, n, c->aceA.p, c->err);
             if (e != hipSuccess) return e;
-            if (!pm)
-                return launch_ace4(c->stream, c->aceA.p, lmax4, t.n_phases, n, t.l_units, t.units, t.coef, t.l_descs, t.descs,
-                                   t.max_slots, t.n4, out + off, 1, total);
-            e = launch_ace4(c->stream, c->aceA.p, lmax4, t.n_phases, n, t.l_units, t.units, t.coef, t.l_descs, t.descs,
-                            t.max_slots, t.n4, c->ace4S.p, 1, chunk);
-            if (e != hipSuccess) return e;
-            return launch_planes_to_rows(c->stream, c->ace4S.p, chunk, n, t.n4, out + off * t.n4);
+            if (pm)
+                return launch_ace4_rows(c->stream, c->aceA.p, n, t.rows_plan, t.rows_ints, t.n_slots, t.n_rows,
+                                        out + off * t.n_rows);
+            return launch_ace4(c->stream, c->aceA.p, lmax4, t.n_phases, n, t.l_units, t.units, t.coef, t.l_descs, t.descs,
+                               t.max_slots, t.n4, out + off, total);
         }));
     }
     return MALA_OK;

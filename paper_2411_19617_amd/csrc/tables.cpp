@@ -498,6 +498,96 @@ int build_ace4_tables(int nmax4, int lmax4, std::vector<int>& l_units, std::vect
     return n4;
 }
 
+// Plan of the point-major rank-4 kernel (layout in ace.h).  The pair (p1, p2) with
+// l1 > l2 is formed as (p2, p1): <l2 m2 l1 m1|L M> = (-1)^(l1+l2-L) <l1 m1 l2 m2|L M>
+// goes into the descriptors' signs.
+void build_ace4_rows_plan(int nmax4, int lmax4, std::vector<int>& plan, int& n_slots) {
+    constexpr int G = kTile / kAce4RowPoints, W = kAce4RowWaves;
+    std::vector<int> set;
+    const int n4 = ace4_descriptor_set(nmax4, lmax4, set);
+    const int nl = lmax4 + 1, np = nmax4 * nl, nL = 2 * kAce4MaxL + 1;
+    std::vector<int> slot((size_t)np * np * nL, -1);
+    n_slots = 0;
+    struct Desc { int L, sa, sb, out, neg; };
+    std::vector<Desc> descs;
+    for (int k = 0; k < n4; ++k) {
+        const int* d = &set[5 * k];
+        const int L = d[4];
+        int s[2], neg = (d[2] % nl + d[3] % nl) & 1;             // (-1)^(l3+l4-L) (-1)^L
+        for (int h = 0; h < 2; ++h) {
+            const int pa = d[2 * h], pb = d[2 * h + 1], la = pa % nl, lb = pb % nl;
+            int& at = slot[((size_t)pa * np + pb) * nL + L];
+            if (at < 0) {
+                at = n_slots;
+                n_slots += L + 1;
+            }
+            s[h] = at;
+            if (la > lb) neg ^= (la + lb - L) & 1;
+        }
+        descs.push_back({L, s[0], s[1], k, neg});
+    }
+    const int spare = n_slots;
+    n_slots += nL;
+    std::stable_sort(descs.begin(), descs.end(), [](const Desc& x, const Desc& y) {
+        return x.L != y.L ? x.L < y.L : x.sa < y.sa;
+    });
+    // rounds of pairs of one (l1, l2), dealt by cost, longest first to the least loaded
+    std::vector<std::pair<long, std::vector<int>>> rounds;
+    for (int l1 = 0; l1 <= lmax4; ++l1)
+        for (int l2 = l1; l2 <= lmax4; ++l2) {
+            long cost = 30;
+            for (int M = 0; M <= l1 + l2; ++M)
+                for (int m = -l1; m <= l1; ++m)
+                    if (abs(M - m) <= l2) cost += 4 + 2 * (l1 + l2 - std::max(M, l2 - l1) + 1);
+            std::vector<std::array<int, kAce4PairInts>> pairs;
+            for (int pa = 0; pa < np; ++pa)
+                for (int pb = pa; pb < np; ++pb) {
+                    const int la = pa % nl, lb = pb % nl;
+                    if (std::min(la, lb) != l1 || std::max(la, lb) != l2) continue;
+                    std::array<int, kAce4PairInts> e{};
+                    e[0] = la <= lb ? pa / nl | pb / nl << 2 : pb / nl | pa / nl << 2;
+                    bool used = false;
+                    for (int i = 0; i <= 2 * l1; ++i) {
+                        const int at = slot[((size_t)pa * np + pb) * nL + l2 - l1 + i];
+                        used = used || at >= 0;
+                        e[1 + i / 3] |= (at < 0 ? spare : at) << (10 * (i % 3));
+                    }
+                    if (used) pairs.push_back(e);
+                }
+            std::array<int, kAce4PairInts> none{};
+            for (int i = 0; i <= 2 * l1; ++i) none[1 + i / 3] |= spare << (10 * (i % 3));
+            for (size_t i = 0; i < pairs.size(); i += G) {
+                std::vector<int> r(1, l1 * (kAce4MaxL + 1) + l2);
+                for (size_t g = 0; g < (size_t)G; ++g) {
+                    const auto& e = i + g < pairs.size() ? pairs[i + g] : none;
+                    r.insert(r.end(), e.begin(), e.end());
+                }
+                rounds.push_back({cost, r});
+            }
+        }
+    std::stable_sort(rounds.begin(), rounds.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+    std::vector<long> load(W, 0);
+    std::vector<std::vector<int>> lists(W);
+    for (const auto& x : rounds) {
+        const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        load[w] += x.first;
+        lists[w].insert(lists[w].end(), x.second.begin(), x.second.end());
+    }
+    plan.assign(W + 1 + nL + 1, 0);
+    for (int w = 0; w < W; ++w) {
+        plan[w] = (int)plan.size();
+        plan.insert(plan.end(), lists[w].begin(), lists[w].end());
+    }
+    plan[W] = (int)plan.size();
+    const int d0 = (int)plan.size();
+    for (int L = 0, k = 0; L <= nL; ++L) {
+        while (k < n4 && descs[k].L < L) ++k;
+        plan[W + 1 + L] = d0 + k;
+    }
+    for (const Desc& d : descs)
+        plan.push_back((int)((unsigned)d.sa | (unsigned)d.sb << 10 | (unsigned)d.out << 20 | (unsigned)d.neg << 31));
+}
+
 // Longest-processing-time assignment of triples to the waves of a block.
 // wave_triples[w*stride] = count, followed by the triple indices.
 void plan_zb_waves(int twojmax, int n_waves, int* wave_triples, int stride) {
