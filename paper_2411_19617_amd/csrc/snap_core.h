@@ -1,7 +1,6 @@
 // Compile-time helpers of the bispectrum kernels (Sec. 3.2.2, Eq. SNAPExpansion,
 // Eq. snap_dim) shared by the descriptor kernels and their adjoint: exact
-// constants, the chain layout of the U recursion, the wave groups of the
-// chains, and the (row, row) pairs of the Z contraction.
+// constants and the (row, row) pairs of the Z contraction.
 #pragma once
 #include "mala_internal.h"
 
@@ -12,51 +11,6 @@ __host__ __device__ constexpr double ce_sqrt(double x) {
     double r = x > 1.0 ? x : 1.0;
     for (int i = 0; i < 64; ++i) r = 0.5 * (r + x / r);
     return r;
-}
-
-// ------------------------------------------------------------------ chains
-// Chain q: rows k = 0..min(q, TJ-q) at level J = q + k, row index ma = k.
-__host__ __device__ constexpr int chain_rows(int tj, int q) { return (q < tj - q ? q : tj - q) + 1; }
-__host__ __device__ constexpr int chain_len(int tj, int q) {
-    int n = 0;
-    for (int k = 0; k < chain_rows(tj, q); ++k) n += q + k + 1;
-    return n;
-}
-// Chains are split over four waves at twojmax 8 and 10 (operation counts
-// balanced to within 4%, at most 75 complex accumulators per wave, and
-// power tables small enough that every wave keeps its share in VGPRs with
-// two waves per SIMD); one wave below that.
-__host__ __device__ constexpr int n_groups(int tj) { return tj >= 8 ? 4 : 1; }
-__host__ __device__ constexpr bool in_group(int tj, int g, int q) {
-    if (tj == 10) return g == 0 ? (q == 0 || q == 5 || q == 10)
-                       : g == 1 ? (q == 1 || q == 2 || q == 3 || q == 4)
-                       : g == 2 ? (q == 6 || q == 9)
-                                : (q == 7 || q == 8);
-    if (tj == 8) return g == 0 ? (q <= 3) : g == 1 ? (q == 4) : g == 2 ? (q == 5 || q == 8) : (q == 6 || q == 7);
-    return g == 0;
-}
-__host__ __device__ constexpr int group_size(int tj, int g) {
-    int n = 0;
-    for (int q = 0; q <= tj; ++q)
-        if (in_group(tj, g, q)) n += chain_len(tj, q);
-    return n;
-}
-__host__ __device__ constexpr int group_qmax(int tj, int g) {
-    int m = 0;
-    for (int q = 0; q <= tj; ++q)
-        if (in_group(tj, g, q)) m = q;
-    return m;
-}
-__host__ __device__ constexpr int chain_slot(int tj, int g, int q) {
-    int n = 0;
-    for (int p = 0; p < q; ++p)
-        if (in_group(tj, g, p)) n += chain_len(tj, p);
-    return n;
-}
-__host__ __device__ constexpr int row_slot(int q, int k) {
-    int n = 0;
-    for (int i = 0; i < k; ++i) n += q + i + 1;
-    return n;
 }
 
 __host__ __device__ constexpr double ce_binom(int n, int k) {

@@ -168,34 +168,11 @@ __device__ __forceinline__ PointFrame point_frame(const TileBoxes& tb, int n0, d
     return f;
 }
 
-// Wave 0's per-point neighbour lists: the indices of the candidates within
-// rc of the lane's point, in candidate order, at most kMaxNbr (more sets
-// kErrNbr in *err); invalid lanes get empty lists.
-__device__ __forceinline__ void build_neighbour_lists(const float4* cand, int ncand, const PointFrame& f, float rc,
-                                                      bool valid, int lane, unsigned short (*nbr)[kTile],
-                                                      int* nnbr, int* err) {
-    int cnt = 0;
-    const int split = f.n0 < ncand ? f.n0 : ncand;
-    auto scan = [&](int c0, int c1, float3 p) {
-        for (int c = c0; c < c1; ++c) {
-            const float4 q = cand[c];
-            const float dx = q.x - p.x, dy = q.y - p.y, dz = q.z - p.z;
-            if (dx * dx + dy * dy + dz * dz < rc * rc) {
-                if (cnt < kMaxNbr) nbr[cnt][lane] = (unsigned short)c;
-                ++cnt;
-            }
-        }
-    };
-    scan(0, split, f.p0);
-    scan(split, ncand, f.p1);
-    if (cnt > kMaxNbr) atomicOr(err, kErrNbr);
-    nnbr[lane] = valid ? (cnt < kMaxNbr ? cnt : kMaxNbr) : 0;
-}
-
-// The same lists by all NW waves of the block (called by all of them): wave w
+// Per-point neighbour lists by all NW waves of the block (called by all of them):
+// the indices of the candidates within rc of the lane's point, in candidate order,
+// at most kMaxNbr (more sets kErrNbr in *err); invalid lanes get empty lists.  Wave w
 // takes the w-th part of the candidates, marks each point's hits in bit masks,
-// and writes the marked indices behind those of the waves before it, so the
-// order is the same.  Most candidates miss (about 300 for 50 neighbours on a row
+// and writes the marked indices behind those of the waves before it.  Most candidates miss (about 300 for 50 neighbours on a row
 // of 64 points): a marked candidate costs one pass over the few bits set, where
 // a second scan for the writes cost as much as the first (k_ace_proj 160 ->
 // 142 us per 300,007 points).
