@@ -234,8 +234,10 @@ mala_status ensure_tables(mala_ctx* c, int tj) {
     int n = build_cg_table(tj, tab.data(), off.data(), (int)tab.size());
     if (n < 0) return fail(MALA_E_UNSUPPORTED, "Clebsch-Gordan table too large");
     t.zb_waves = 12;      // three waves per SIMD share the LDS tile
-    std::vector<int> waves(t.zb_waves * kMaxZbStride, 0);
+    // the plan of one block per tile, then that of two
+    std::vector<int> waves(3 * t.zb_waves * kMaxZbStride, 0);
     plan_zb_waves(tj, t.zb_waves, waves.data(), kMaxZbStride);
+    plan_zb_waves(tj, 2 * t.zb_waves, waves.data() + t.zb_waves * kMaxZbStride, kMaxZbStride);
     c->n_allocs += 3;
     HIP_TRY(hipMalloc(&t.cg, sizeof(float) * (n > 0 ? n : 1)));
     HIP_TRY(hipMalloc(&t.cg_off, sizeof(int) * off.size()));

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(768) void k_zb(const float2* __restrict__ u, int64_
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t idx = tile * kTile + lane;
     const bool valid = idx < n_pts;
-    const int* list = wave_triples + wave * stride;
+    const int* list = wave_triples + (blockIdx.y * (blockDim.x >> 6) + wave) * stride;
     const int cnt = __builtin_amdgcn_readfirstlane(list[0]);
     for (int i = 0; i < cnt; ++i) {
         const int t = __builtin_amdgcn_readfirstlane(list[1 + i]);
@@ -230,8 +230,17 @@ static hipError_t zb_tj(hipStream_t s, int64_t n_pts, const float2* u_scratch, f
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL(k_zb<TJ>, dim3((unsigned)n_tiles), dim3(64 * zb_waves), lds, s, u_scratch, n_pts, B_out,
-                       cg_table, cg_offsets, wave_triples, kMaxZbStride);
+    // Two blocks per tile, half of the triples each, where that shortens the last
+    // round of blocks over the chip.  From twojmax 8 on a block fills a CU (its LDS):
+    // 125 tiles 38.7 -> 24.9 us at twojmax 8 and 110 -> 68 at 10, 300 tiles 75 -> 63
+    // and 224 -> 187.  A split costs a second load of the tile and, the longest
+    // triples being whole, some balance, so it has to save an eighth of the rounds
+    // (880 tiles: 147 -> 138, 431 -> 412).  Below twojmax 8 it gave nothing.
+    constexpr int64_t kCus = 256;
+    const int64_t whole = 2 * ((n_tiles + kCus - 1) / kCus), halves = (2 * n_tiles + kCus - 1) / kCus;
+    const bool split = TJ >= 8 && 8 * halves <= 7 * whole;
+    hipLaunchKernelGGL(k_zb<TJ>, dim3((unsigned)n_tiles, split ? 2 : 1), dim3(64 * zb_waves), lds, s, u_scratch, n_pts,
+                       B_out, cg_table, cg_offsets, wave_triples + (split ? zb_waves * kMaxZbStride : 0), kMaxZbStride);
     return hipGetLastError();
 }
 

@@ -265,6 +265,7 @@ hipError_t launch_bin(hipStream_t s, const double* pos_dev, int n_atoms, const d
 
 hipError_t launch_ui(hipStream_t s, int twojmax, const BinState& bins, const int N[3], double rcut,
                      int64_t pt_begin, int64_t n_pts, float2* u_scratch, int* err_flag);
+// wave_triples: the lists of zb_waves waves, then those of 2 zb_waves (two blocks per tile)
 hipError_t launch_zb(hipStream_t s, int twojmax, int64_t n_pts, const float2* u_scratch, float* B_out,
                      const float* cg_table, const int* cg_offsets, const int* wave_triples, int zb_waves);
 hipError_t launch_gauss(hipStream_t s, const BinState& bins, const int N[3], double sigma, double cutoff,
