@@ -32,7 +32,8 @@ import mala_synth  # noqa: E402
 
 METRIC = "grid points/s (bispectrum+MLP+LDOS reduce); p50/p99 snapshot latency"
 PEAK_FP32_VALU_TFLOPS = 157.3     # 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2 (packed) x 2.4 GHz
-PEAK_MFMA_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}   # dense matrix peaks
+# dense matrix peaks; an FP32 network product is three FP16 ones (two planes per operand)
+PEAK_MFMA_TFLOPS = {"fp32": 2500.0 / 3.0, "bf16": 2500.0}
 WORKLOADS = {
     "paper_solid": (mala_synth.paper_solid, mala_synth.paper_net),
     "paper_solid_200": (lambda: mala_synth.paper_solid(grid=200), mala_synth.paper_net),
@@ -287,7 +288,7 @@ def stats_summary(prof_dir, bench_json, out_name, command):
             zb = float(r["AverageNs"]) / 1e6
     lines += ["", "The metric's step runs the cell list, `k_ui`, `k_zb`, `k_mlp` and `k_fermi` "
               "(and `k_density_window`); `k_gauss`, `k_mlp_vjp`, `k_yi`, `k_dedr`, `k_ace_proj`, `k_ace`, `k_ace4` and "
-              "`k_planes_to_rows` come "
+              "`k_ace4_rows` come "
               "from the lines outside the metric (Gaussian descriptors, both VJPs, grid ACE) when they are run."]
     if b is None:
         with open(os.path.join(ROOT, "profiles", out_name), "w") as fo:
@@ -342,8 +343,7 @@ def probe_kernels():
     print("probe done", flush=True)
 
 
-COUNTER_KERNELS = ["mala::k_ui<", "mala::k_zb<", "mala::k_mlp<0", "mala::k_mlp<1", "mala::k_ace4", "mala::k_ace",
-                   "mala::k_planes_to_rows",
+COUNTER_KERNELS = ["mala::k_ui<", "mala::k_zb<", "mala::k_mlp<2", "mala::k_mlp<1", "mala::k_ace4", "mala::k_ace",
                    "mala::k_mlp_vjp", "mala::k_yi", "mala::k_dedr"]
 
 
