@@ -67,17 +67,14 @@ __device__ __forceinline__ AceTile ace_tile(const BinState& bins, int Nx, int Ny
     AceTile t;
     t.idx = tile * kTile + lane;
     t.valid = t.idx < n_pts;
-    const int64_t p = pt_begin + (t.valid ? t.idx : tile * kTile);
-    const int64_t pk = p % Nz, pj = (p / Nz) % Ny, pi = p / ((int64_t)Ny * Nz);
-    const double rx = (double)pi * bins.L[0] / Nx, ry = (double)pj * bins.L[1] / Ny,
-                 rz = (double)pk * bins.L[2] / Nz;
-    const int64_t p0 = pt_begin + tile * kTile;
-    const TileBoxes boxes = tile_boxes(p, p0, Ny, Nz, rx, ry, rz);
+    const TilePoint pt = tile_point(bins, Nx, Ny, Nz, pt_begin + tile * kTile,
+                                    (int)min((int64_t)kTile, n_pts - tile * kTile), lane);
+    const TileBoxes& boxes = pt.boxes;
     int n0;
     const int base = gather_candidates(bins, boxes, rcut, cand, kMaxCand, scan_tmp, &n0);
     if (base > kMaxCand && threadIdx.x == 0) atomicOr(err, kErrCand);
     t.ncand = base < kMaxCand ? base : kMaxCand;
-    t.frame = point_frame(boxes, n0, rx, ry, rz);
+    t.frame = point_frame(boxes, n0, pt.x, pt.y, pt.z);
     return t;
 }
 

@@ -21,19 +21,16 @@ __global__ __launch_bounds__(64) void k_gauss(BinState bins, int Nx, int Ny, int
     const int64_t tile = blockIdx.x;
     const int64_t idx = tile * kTile + lane;
     const bool valid = idx < n_pts;
-    const int64_t p = pt_begin + (valid ? idx : tile * kTile);
-    const int64_t pk = p % Nz, pj = (p / Nz) % Ny, pi = p / ((int64_t)Ny * Nz);
-    const double rx = (double)pi * bins.L[0] / Nx, ry = (double)pj * bins.L[1] / Ny,
-                 rz = (double)pk * bins.L[2] / Nz;
-    const int64_t p0 = pt_begin + tile * kTile;
-    const TileBoxes boxes = tile_boxes(p, p0, Ny, Nz, rx, ry, rz);
+    const TilePoint pt = tile_point(bins, Nx, Ny, Nz, pt_begin + tile * kTile,
+                                    (int)min((int64_t)kTile, n_pts - tile * kTile), lane);
+    const TileBoxes& boxes = pt.boxes;
     int n0;
     const int base = gather_candidates(bins, boxes, cutoff, cand, kMaxCand, scan_tmp, &n0);
     if (base > kMaxCand && lane == 0) atomicOr(err, kErrCand);
     const int ncand = base < kMaxCand ? base : kMaxCand;
     __syncthreads();
 
-    const PointFrame frame = point_frame(boxes, n0, rx, ry, rz);
+    const PointFrame frame = point_frame(boxes, n0, pt.x, pt.y, pt.z);
     const float rc2 = (float)(cutoff * cutoff);
     float acc = 0.f;
     auto scan = [&](int c0, int c1, float3 o) {

@@ -144,13 +144,9 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
     const int64_t tile = blockIdx.x;
     const int64_t idx = tile * kTile + lane;
     const bool valid = idx < n_pts;
-    const int64_t p = pt_begin + (valid ? idx : tile * kTile);
-    const int64_t pk = p % Nz, pj = (p / Nz) % Ny, pi = p / ((int64_t)Ny * Nz);
-    const double rx = (double)pi * bins.L[0] / Nx, ry = (double)pj * bins.L[1] / Ny,
-                 rz = (double)pk * bins.L[2] / Nz;
-    const int64_t p0 = pt_begin + tile * kTile;
-    // bounding boxes of the tile's points
-    const TileBoxes boxes = tile_boxes(p, p0, Ny, Nz, rx, ry, rz);
+    const TilePoint pt = tile_point(bins, Nx, Ny, Nz, pt_begin + tile * kTile,
+                                    (int)min((int64_t)kTile, n_pts - tile * kTile), lane);
+    const TileBoxes& boxes = pt.boxes;
 
     // ---- candidate atom images within rcut of the boxes, in a fixed order
     int n0;
@@ -160,7 +156,7 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
     __syncthreads();
 
     // ---- per-point neighbour lists, in candidate order, by all waves
-    const PointFrame frame = point_frame(boxes, n0, rx, ry, rz);
+    const PointFrame frame = point_frame(boxes, n0, pt.x, pt.y, pt.z);
     const float rcf = (float)rcut;
     const int my_n = build_neighbour_lists_block<NG>(cand, ncand, frame, rcf, valid, lane, wave, nbr, nnbr, err);
     const int n_iter = wave_max_int(my_n);            // the same in every wave
