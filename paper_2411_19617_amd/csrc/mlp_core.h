@@ -229,6 +229,9 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
 
 // The wave's item: one unit tile times one point tile.  Three products per
 // step cover little of a weight read, so six steps of weights are in flight.
+// The sum runs in the order of mm: whether a unit tile is an item depends on the
+// point tiles of a block and with them on the number of points of the call, and
+// a point's values must not.
 template <int P, int NT, int RS>
 __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh, const ActTile<P, NT, RS>& in, int lane) {
     constexpr int D = 6, PS = ActTile<P, NT, RS>::kPlane;
@@ -236,15 +239,15 @@ __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh,
     const unsigned short* row = in.p + (16 * sh.it_n + (lane & 15)) * RS;
     uint4 a[D][P];
     static_for<0, D>([&](auto dc) { fetch_tile<P>(W, sh.it_mt, T, min((int)decltype(dc)::value, KL), lane, a[decltype(dc)::value]); });
-    f4 t[P == 2 ? 3 : 1] = {};            // one chain per product: they do not wait for each other
+    f4 t = {};
     auto step = [&](int s, uint4 (&w)[P]) {
         uint4 b[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) b[p] = *reinterpret_cast<const uint4*>(row + p * PS + 32 * s + 8 * g);
-        t[0] = mfma32<P>(w[0], b[0], t[0]);
+        t = mfma32<P>(w[0], b[0], t);
         if constexpr (P == 2) {
-            t[1] = mfma32<P>(w[0], b[P - 1], t[1]);
-            t[2] = mfma32<P>(w[P - 1], b[0], t[2]);
+            t = mfma32<P>(w[0], b[P - 1], t);
+            t = mfma32<P>(w[P - 1], b[0], t);
         }
         fetch_tile<P>(W, sh.it_mt, T, min(s + D, KL), lane, w);
     };
@@ -259,11 +262,10 @@ __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh,
             uint2 bt[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) bt[p] = *reinterpret_cast<const uint2*>(row + p * PS + 32 * KS + 4 * g);
-            half_products<P>(a[i], bt, t[0]);
+            half_products<P>(a[i], bt, t);
         }
     });
-    if constexpr (P == 2) return t[0] + (t[1] + t[2]);
-    else return t[0];
+    return t;
 }
 
 // acc = W in for the wave's share of a layer.
