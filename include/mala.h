@@ -55,8 +55,16 @@ typedef int32_t mala_status;
 #define MALA_E_BUSY (-6)         /* serving: result not ready yet              */
 #define MALA_E_CAPACITY (-7)     /* a fixed per-tile capacity was exceeded      */
 
-#define MALA_PREC_FP32 0         /* network in FP32 on MFMA                    */
-#define MALA_PREC_BF16 1         /* network in BF16 on MFMA, FP32 accumulate    */
+/* Arithmetic of the network.  FP32: weights and activations in FP32, each split
+ * into two 16-bit halves for the matrix unit (22 bits and a sign, the products
+ * accumulated in FP32): the error against 64 bits is no larger than with FP32
+ * products, also where inputs, units or outputs of a layer differ by many decades
+ * and the neighbouring layer makes up for it.  Only a value more than 2^27 smaller
+ * than another input of the same layer and point has fewer bits, if no scaling of
+ * single units brings the two together.  BF16: weights and activations in
+ * BF16, accumulated in FP32.                                                 */
+#define MALA_PREC_FP32 0
+#define MALA_PREC_BF16 1
 
 /* Thread-local message of the last failing call on this thread ("" if none). */
 const char* mala_last_error(void);

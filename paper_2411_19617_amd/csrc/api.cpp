@@ -699,6 +699,62 @@ mala_status mala_profile_read(mala_ctx* c, double* ms, int64_t* launches, int64_
 }
 
 // ---------------------------------------------------------------- weights
+}  // extern "C"
+
+namespace {
+
+// The same network with its magnitudes evened out by powers of two, which are
+// exact: every input and hidden unit may be scaled by a positive factor that the
+// next layer's column takes back (sigma is positively homogeneous), every output by
+// one that its scaler takes back.  The FP16 planes of FP32 weights hold a value
+// relative to the largest of its layer (weights) or of its point (activations), so
+// that units of very different size in one layer, which FP32 does not mind, would
+// lose bits there: hidden units spread over eight decades gave 3e-5 of error
+// where FP32 has 5e-7.  Columns of the first layer, then every layer's rows (with
+// the bias, which must not come to dominate a point) are brought to the binade of
+// the layer's largest one, by at most 2^60, which leaves FP32 its range.
+void even_out(std::vector<double>& rstd, std::vector<double>* W, std::vector<double>* b, std::vector<double>& out_scale) {
+    constexpr int kMost = 60;
+    auto larger = [](double m, double v) { return fabs(v) > m && isfinite(v) ? fabs(v) : m; };
+    // factors that raise magnitudes to the binade of the largest, and zeros
+    // as far as they go if `all`; at most so far that hold[i] / factor stays a normal FP32 number
+    auto raise = [&](const std::vector<double>& m, bool all, const std::vector<double>* hold) {
+        const double top = *std::max_element(m.begin(), m.end());
+        std::vector<double> f(m.size());
+        for (size_t i = 0; i < m.size(); ++i) {
+            int d = m[i] > 0.0 ? std::min(ilogb(top) - ilogb(m[i]), kMost) : all ? kMost : 0;
+            if (hold && (*hold)[i] != 0.0 && isfinite((*hold)[i])) d = std::min(d, std::max(0, ilogb((*hold)[i]) + 100));
+            f[i] = ldexp(1.0, d);
+        }
+        return f;
+    };
+    for (int l = 0; l < 3; ++l)                      // what FP32 holds of them
+        for (double& v : W[l]) v = (float)v;
+    std::vector<double> col(rstd.size(), 0.0);
+    for (size_t i = 0; i < W[0].size(); ++i) col[i % col.size()] = larger(col[i % col.size()], W[0][i]);
+    col = raise(col, true, &rstd);                    // an input that nothing reads: out of the way
+    for (size_t k = 0; k < col.size(); ++k) rstd[k] /= col[k];
+    for (int l = 0; l < 3; ++l) {
+        const size_t fin = col.size(), fout = b[l].size();
+        std::vector<double> row(fout, 0.0);
+        for (size_t i = 0; i < fout; ++i) {
+            for (size_t k = 0; k < fin; ++k) row[i] = larger(row[i], W[l][i * fin + k] *= col[k]);
+            if (l < 2) row[i] = larger(row[i], b[l][i]);
+        }
+        row = raise(row, false, l == 2 ? &out_scale : nullptr);
+        for (size_t i = 0; i < fout; ++i) {
+            for (size_t k = 0; k < fin; ++k) W[l][i * fin + k] *= row[i];
+            b[l][i] *= row[i];
+            row[i] = 1.0 / row[i];
+            if (l == 2) out_scale[i] *= row[i];
+        }
+        col.swap(row);
+    }
+}
+
+}  // namespace
+
+extern "C" {
 mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32_t precision,
                               mala_weights** out) {
     if (!c || !blob || !out) return fail(MALA_E_INVALID_ARG, "NULL argument");
@@ -729,12 +785,14 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     const int n_in = wid[0], h1 = wid[1], h2 = wid[2], n_out = wid[3];
     if (n_in > kMlpMaxIn || h1 > kMlpMaxHidden || h2 > kMlpMaxHidden || n_out > kMlpMaxOut)
         return fail(MALA_E_UNSUPPORTED, "layer width beyond the library's limits");
-    std::vector<double> mean(n_in), sd(n_in), W1((size_t)h1 * n_in), b1(h1), W2((size_t)h2 * h1), b2(h2),
-        W3((size_t)n_out * h2), b3(n_out), osc(n_out), osh(n_out);
-    bool ok = take(mean.data(), 8 * n_in) && take(sd.data(), 8 * n_in) && take(W1.data(), 8 * W1.size()) &&
-              take(b1.data(), 8 * h1) && take(W2.data(), 8 * W2.size()) && take(b2.data(), 8 * h2) &&
-              take(W3.data(), 8 * W3.size()) && take(b3.data(), 8 * n_out) && take(osc.data(), 8 * n_out) &&
-              take(osh.data(), 8 * n_out);
+    std::vector<double> mean(n_in), sd(n_in), osc(n_out), osh(n_out), W[3], bias[3];
+    bool ok = take(mean.data(), 8 * n_in) && take(sd.data(), 8 * n_in);
+    for (int l = 0; l < 3; ++l) {
+        W[l].resize((size_t)wid[l + 1] * wid[l]);
+        bias[l].resize(wid[l + 1]);
+        ok = ok && take(W[l].data(), 8 * W[l].size()) && take(bias[l].data(), 8 * bias[l].size());
+    }
+    ok = ok && take(osc.data(), 8 * n_out) && take(osh.data(), 8 * n_out);
     if (!ok) return fail(MALA_E_INVALID_ARG, "truncated blob");
     for (double v : sd)
         if (!(v > 0.0) || !isfinite(v)) return fail(MALA_E_INVALID_ARG, "input std must be positive");
@@ -744,29 +802,31 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
     const int in_t = ceil_div(n_in, 16), in_pad = 16 * in_t;
     const int h1t = ceil_div(h1, 16), h2t = ceil_div(h2, 16), ot = ceil_div(n_out, 16);
-    // FP32 weights are split into two FP16 planes, v = hi + lo, after a
-    // power-of-two scale that brings the layer's largest weight to [2^14, 2^15)
+    std::vector<double> rstd(n_in);
+    for (int i = 0; i < n_in; ++i) rstd[i] = 1.0 / sd[i];
+    if (!bf) even_out(rstd, W, bias, osc);
+    // FP32 weights are split into two FP16 planes after a power-of-two scale that
+    // brings the layer's largest weight to [2^14, 2^15)
     auto scale_exponent = [](const std::vector<double>& W) {
         float m = 0.f;
         for (double v : W)
             if (isfinite((float)v)) m = std::max(m, fabsf((float)v));
         return m > 0.f ? std::min(14 - ilogbf(m), 100) : 0;
     };
-    const int we[3] = {bf ? 0 : scale_exponent(W1), bf ? 0 : scale_exponent(W2), bf ? 0 : scale_exponent(W3)};
+    const int we[3] = {bf ? 0 : scale_exponent(W[0]), bf ? 0 : scale_exponent(W[1]), bf ? 0 : scale_exponent(W[2])};
     // every FP32 array in one upload, each on 256 bytes and zero-padded to its
     // length on the device: the layers' weights (packed there), biases, scalers
     std::vector<float> f32;
-    auto add = [&](const std::vector<double>& v, size_t n, auto&& value) {
+    auto add = [&](const std::vector<double>& v, size_t n) {
         const size_t at = (f32.size() + 63) / 64 * 64;
         f32.resize(at + n, 0.f);
-        for (size_t i = 0; i < v.size() && i < n; ++i) f32[at + i] = value(v[i]);
+        for (size_t i = 0; i < v.size() && i < n; ++i) f32[at + i] = (float)v[i];
         return at;
     };
-    auto as_float = [](double v) { return (float)v; };
-    const size_t off_w[3] = {add(W1, W1.size(), as_float), add(W2, W2.size(), as_float), add(W3, W3.size(), as_float)};
-    const size_t off_b[3] = {add(b1, 16 * h1t, as_float), add(b2, 16 * h2t, as_float), add(b3, 16 * ot, as_float)};
-    const size_t off_mean = add(mean, n_in, as_float), off_rstd = add(sd, n_in, [](double v) { return (float)(1.0 / v); });
-    const size_t off_sc = add(osc, kMlpMaxOut, as_float), off_sh = add(osh, kMlpMaxOut, as_float);
+    const size_t off_w[3] = {add(W[0], W[0].size()), add(W[1], W[1].size()), add(W[2], W[2].size())};
+    const size_t off_b[3] = {add(bias[0], 16 * h1t), add(bias[1], 16 * h2t), add(bias[2], 16 * ot)};
+    const size_t off_mean = add(mean, n_in), off_rstd = add(rstd, n_in);
+    const size_t off_sc = add(osc, kMlpMaxOut), off_sh = add(osh, kMlpMaxOut);
 
     // packed A operands of every layer, and of the transposes (for the network's
     // vector-Jacobian product, FP32 only: their K runs over the padded output

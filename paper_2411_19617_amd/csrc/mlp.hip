@@ -313,10 +313,10 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
     if (planes == 1) {                                  // BF16, round to nearest even
         const unsigned x = (unsigned)__float_as_int(v);
         h = (unsigned short)((x + 0x7FFFu + ((x >> 16) & 1u)) >> 16);
-    } else {                                            // v scale = hi + lo
+    } else {                                            // v scale = hi + lo / 2^kLoBits
         const float x = v * scale;
         const _Float16 hi = (_Float16)x;
-        h = bits_as<unsigned short>(pl == 0 ? hi : (_Float16)(x - (float)hi));
+        h = bits_as<unsigned short>(pl == 0 ? hi : (_Float16)((x - (float)hi) * (float)(1 << kLoBits)));
     }
     out[i] = h;
 }

@@ -6,22 +6,28 @@
 // M dimension, the points of the block's tile the N dimension.
 //
 // FP32 weights run as two FP16 planes per operand on the 16-bit matrix unit:
-// x = hi + lo with hi = fp16(x), lo = fp16(x - hi), after a power-of-two scale
-// that puts the largest value near 2^14 (per layer for the weights, per point
-// for the activations, taken from the values themselves, so nothing overflows
-// and only values 2^-28 below the largest lose bits).  hi + lo keeps x to at
-// most one unit of the last FP32 place (exactly for three values in four), the
-// products hi hi + hi lo + lo hi are accumulated in FP32, and lo lo (2^-24 of
-// the product) is dropped.  Against the 16x16x4 FP32 instruction that is
+// x = hi + lo / 2^11 with hi = fp16(x), lo = fp16(2^11 (x - hi)), after a
+// power-of-two scale that puts the largest value near 2^14 (per layer for the
+// weights, per point for the activations, taken from the values themselves, so
+// nothing overflows).  hi + lo / 2^11 keeps x to at most one unit of the last FP32
+// place (exactly for three values in four) from the largest value down to 2^-27 of
+// it; below that a bit is lost per binade (as lo = fp16(x - hi) it was from 2^-16 on).
+// FP32 has its precision at any size, so the loader first evens out the network's
+// inputs, units and outputs (even_out in api.cpp): what is left below 2^-27 of
+// the largest then counts only beside values that no unit adds to it.  The products
+// hi hi and hi lo + lo hi are accumulated in FP32, in a sum each, and lo lo (2^-24
+// of the product) is dropped.  Against the 16x16x4 FP32 instruction that is
 // three 16x16x32 instructions of 16 cycles per 32 units instead of eight of
-// 32, and fewer FP32 roundings of the running sum (three per 32 units).  Error
+// 32, and fewer FP32 roundings of the running sum (one per 32 units).  Error
 // against 64 bits of the plain network output (2-norm, x ~ N(0, 1)): 2.6e-7
-// with that instruction and 2.4e-7 here at 55-64-64-250, 5.5e-7 and 3.8e-7 at
-// 91-400-400-250, 6.1e-7 and 4.0e-7 at 128-512-512-256.  Time at 91-400-400-250:
-// 4.12 -> 1.46 ms per 729,000 points with the LDOS stored, 14.6 -> 4.8 us per
-// 1,000 points for the vector-Jacobian product.  What bounds it now: the
-// products are 0.65 ms of the 1.46 at the 1.9 GHz the card holds under them,
-// the epilogues (activation, scales, LDS writes) as much, and the weights
+// with that instruction and 1.9e-7 here at 55-64-64-250, 5.5e-7 and 2.5e-7 at
+// 91-400-400-250, 6.1e-7 and 2.6e-7 at 128-512-512-256; the same with units
+// spread over 14 decades, and 3.8e-7 and 2.6e-7 with two halves of a network 1e8
+// apart.  The sum of its own for the small products costs 1 to 2%.
+// Time at 91-400-400-250: 4.12 -> 1.46 ms per 729,000 points with the LDOS stored,
+// 14.6 -> 4.9 us per 1,000 points for the vector-Jacobian product.  What bounds it
+// now: the products are 0.65 ms of the 1.46 at the 1.9 GHz the card holds under
+// them, the epilogues (activation, scales, LDS writes) as much, and the weights
 // from L2 most of the rest.
 // BF16 weights use one plane, rounded once, without scales.
 #pragma once
@@ -36,6 +42,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 
+constexpr int kLoBits = 11;        // binary places by which the second plane is raised (FP32 weights)
 constexpr int kWaves = 8;          // waves of a network block (two per SIMD, one block per CU)
 
 // sigma(x) = slope x for x < 0, else x.  For 0 < slope <= 1 that is the larger of
@@ -123,13 +130,19 @@ struct Acc {
 
 // Half a step: the first 8 bytes of the weight operand, 16 units.
 template <int P>
-__device__ __forceinline__ void half_products(const uint4 (&w)[P], const uint2 (&b)[P], f4& c) {
+__device__ __forceinline__ void half_products(const uint4 (&w)[P], const uint2 (&b)[P], f4& c, f4& cl) {
     auto lo = [](const uint4& v) { return make_uint2(v.x, v.y); };
     c = mfma16<P>(lo(w[0]), b[0], c);
     if constexpr (P == 2) {
-        c = mfma16<P>(lo(w[0]), b[P - 1], c);
-        c = mfma16<P>(lo(w[P - 1]), b[0], c);
+        cl = mfma16<P>(lo(w[0]), b[P - 1], cl);
+        cl = mfma16<P>(lo(w[P - 1]), b[0], cl);
     }
+}
+
+// The sum of hi hi and that of the two cross products, 2^kLoBits larger.
+__device__ __forceinline__ f4 join_planes(f4 c, f4 cl) {
+    constexpr float f = 1.f / (float)(1 << kLoBits);
+    return f4{fmaf(cl[0], f, c[0]), fmaf(cl[1], f, c[1]), fmaf(cl[2], f, c[2]), fmaf(cl[3], f, c[3])};
 }
 
 // t[m][n] = the wave's unit tile m times point tile n over T unit tiles of
@@ -147,6 +160,7 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
     const int KS = T >> 1, KL = w_steps(T) - 1, g = lane >> 4;
     const unsigned short* row = in.p + (lane & 15) * RS;
     uint4 a[2][H0][P], b[2][P];
+    f4 tl[P == 2 ? M : 1][NT];            // the cross products of the planes
     auto fetch = [&](int s, auto hc, uint4 (&d)[H0][P]) {
         constexpr int h = decltype(hc)::value;
 #pragma unroll
@@ -163,7 +177,10 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
     constexpr std::integral_constant<int, NC - 1> clast{};
     fetch(0, c0, a[0]);
     static_for<0, M>([&](auto mc) {
-        static_for<0, NT>([&](auto nc) { t[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f}; });
+        static_for<0, NT>([&](auto nc) {
+            t[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (P == 2) tl[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f};
+        });
     });
     if (KS > 0) fetch_b(0, 0, b[0]);
     // step s, the I-th of the loop body: its first chunk lies in a[I * NC % 2],
@@ -185,9 +202,9 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
                 for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][0], bc[0], t[h * H0 + m][n]);
                 if constexpr (P == 2) {
 #pragma unroll
-                    for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][0], bc[P - 1], t[h * H0 + m][n]);
+                    for (int m = 0; m < MH; ++m) tl[h * H0 + m][n] = mfma32<P>(ac[m][0], bc[P - 1], tl[h * H0 + m][n]);
 #pragma unroll
-                    for (int m = 0; m < MH; ++m) t[h * H0 + m][n] = mfma32<P>(ac[m][P - 1], bc[0], t[h * H0 + m][n]);
+                    for (int m = 0; m < MH; ++m) tl[h * H0 + m][n] = mfma32<P>(ac[m][P - 1], bc[0], tl[h * H0 + m][n]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -203,7 +220,7 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
             for (int p = 0; p < P; ++p) bt[p] = *reinterpret_cast<const uint2*>(row + n * 16 * RS + p * PS + 32 * KS + 4 * g);
             static_for<0, M>([&](auto mc) {
                 constexpr int m = decltype(mc)::value;
-                half_products<P>(a[m / H0][m % H0], bt, t[m][n]);
+                half_products<P>(a[m / H0][m % H0], bt, t[m][n], tl[P == 2 ? m : 0][n]);
             });
         });
     };
@@ -225,6 +242,13 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
         }
     }
     if (T & 1) tail();
+    if constexpr (P == 2)
+        static_for<0, M>([&](auto mc) {
+            static_for<0, NT>([&](auto nc) {
+                constexpr int m = decltype(mc)::value, n = decltype(nc)::value;
+                t[m][n] = join_planes(t[m][n], tl[m][n]);
+            });
+        });
 }
 
 // The wave's item: one unit tile times one point tile.  Three products per
@@ -239,15 +263,15 @@ __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh,
     const unsigned short* row = in.p + (16 * sh.it_n + (lane & 15)) * RS;
     uint4 a[D][P];
     static_for<0, D>([&](auto dc) { fetch_tile<P>(W, sh.it_mt, T, min((int)decltype(dc)::value, KL), lane, a[decltype(dc)::value]); });
-    f4 t = {};
+    f4 t = {}, tl = {};
     auto step = [&](int s, uint4 (&w)[P]) {
         uint4 b[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) b[p] = *reinterpret_cast<const uint4*>(row + p * PS + 32 * s + 8 * g);
         t = mfma32<P>(w[0], b[0], t);
         if constexpr (P == 2) {
-            t = mfma32<P>(w[0], b[P - 1], t);
-            t = mfma32<P>(w[P - 1], b[0], t);
+            tl = mfma32<P>(w[0], b[P - 1], tl);
+            tl = mfma32<P>(w[P - 1], b[0], tl);
         }
         fetch_tile<P>(W, sh.it_mt, T, min(s + D, KL), lane, w);
     };
@@ -262,10 +286,11 @@ __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh,
             uint2 bt[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) bt[p] = *reinterpret_cast<const uint2*>(row + p * PS + 32 * KS + 4 * g);
-            half_products<P>(a[i], bt, t);
+            half_products<P>(a[i], bt, t, tl);
         }
     });
-    return t;
+    if constexpr (P == 2) return join_planes(t, tl);
+    else return t;
 }
 
 // acc = W in for the wave's share of a layer.
@@ -295,13 +320,15 @@ __device__ __forceinline__ float max_abs4(float mx, f4 v) {
     return fmaxf(fmaxf(fabsf(v[2]), fabsf(v[3])), mx);
 }
 
-// hi = fp16(v scale), lo = fp16(v scale - hi) of two values, each half one
-// mixed-precision FMA that rounds once (v scale is exact: a power of two).
+// hi = fp16(v scale), lo = fp16(2^kLoBits (v scale - hi)) of two values, each
+// half one mixed-precision FMA that rounds once (v scale is exact: a power of two).
 __device__ __forceinline__ void split2(float v0, float v1, float scale, unsigned& hi, unsigned& lo) {
+    constexpr float f = (float)(1 << kLoBits);
+    const float s0 = v0 * (scale * f), s1 = v1 * (scale * f);
     asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(v0), "v"(scale));
     asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(v1), "v"(scale));
-    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(v0), "v"(scale), "v"(hi));
-    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(v1), "v"(scale), "v"(hi));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "s"(-f), "v"(s0));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "s"(-f), "v"(s1));
 }
 
 // Four consecutive units of one point into the tile (scale: FP32 weights only).
