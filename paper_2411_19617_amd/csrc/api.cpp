@@ -703,6 +703,20 @@ mala_status mala_profile_read(mala_ctx* c, double* ms, int64_t* launches, int64_
 
 namespace {
 
+// |v| as an integer that orders like it, 0 for what is not finite, and the binary
+// exponent of one that is not 0.
+inline int magnitude(float v) {
+    int i;
+    memcpy(&i, &v, 4);
+    i &= 0x7fffffff;
+    return i < 0x7f800000 ? i : 0;
+}
+inline int exponent(int i) {
+    float v;
+    memcpy(&v, &i, 4);
+    return ilogbf(v);
+}
+
 // The same network with its magnitudes evened out by powers of two, which are
 // exact: every input and hidden unit may be scaled by a positive factor that the
 // next layer's column takes back (sigma is positively homogeneous), every output by
@@ -713,39 +727,45 @@ namespace {
 // where FP32 has 5e-7.  Columns of the first layer, then every layer's rows (with
 // the bias, which must not come to dominate a point) are brought to the binade of
 // the layer's largest one, by at most 2^60, which leaves FP32 its range.
-void even_out(std::vector<double>& rstd, std::vector<double>* W, std::vector<double>* b, std::vector<double>& out_scale) {
+// Two passes over each weight, on FP32 bits so that they run in vector registers.
+void even_out(const int (&n)[4], float* rstd, float* const (&W)[3], float* const (&b)[3], float* out_scale) {
     constexpr int kMost = 60;
-    auto larger = [](double m, double v) { return fabs(v) > m && isfinite(v) ? fabs(v) : m; };
-    // factors that raise magnitudes to the binade of the largest, and zeros
-    // as far as they go if `all`; at most so far that hold[i] / factor stays a normal FP32 number
-    auto raise = [&](const std::vector<double>& m, bool all, const std::vector<double>* hold) {
-        const double top = *std::max_element(m.begin(), m.end());
-        std::vector<double> f(m.size());
+    // factors that raise magnitudes to the binade of the largest (zeros, if `all`, as
+    // far as any), at most so far that hold[i] / factor stays a normal number
+    auto raise = [&](const std::vector<int>& m, bool all, const float* hold) {
+        const int top = exponent(std::max(*std::max_element(m.begin(), m.end()), 1));
+        std::vector<float> f(m.size());
         for (size_t i = 0; i < m.size(); ++i) {
-            int d = m[i] > 0.0 ? std::min(ilogb(top) - ilogb(m[i]), kMost) : all ? kMost : 0;
-            if (hold && (*hold)[i] != 0.0 && isfinite((*hold)[i])) d = std::min(d, std::max(0, ilogb((*hold)[i]) + 100));
-            f[i] = ldexp(1.0, d);
+            int d = m[i] ? std::min(top - exponent(m[i]), kMost) : all ? kMost : 0;
+            if (hold && magnitude(hold[i])) d = std::min(d, std::max(0, ilogbf(hold[i]) + 100));
+            f[i] = ldexpf(1.f, d);
         }
         return f;
     };
-    for (int l = 0; l < 3; ++l)                      // what FP32 holds of them
-        for (double& v : W[l]) v = (float)v;
-    std::vector<double> col(rstd.size(), 0.0);
-    for (size_t i = 0; i < W[0].size(); ++i) col[i % col.size()] = larger(col[i % col.size()], W[0][i]);
-    col = raise(col, true, &rstd);                    // an input that nothing reads: out of the way
-    for (size_t k = 0; k < col.size(); ++k) rstd[k] /= col[k];
+    std::vector<int> m(n[0], 0);
+    for (int i = 0; i < n[1]; ++i)
+        for (int k = 0; k < n[0]; ++k) m[k] = std::max(m[k], magnitude(W[0][(size_t)i * n[0] + k]));
+    std::vector<float> col = raise(m, true, rstd);   // an input that nothing reads: out of the way
+    for (int k = 0; k < n[0]; ++k) rstd[k] /= col[k];
     for (int l = 0; l < 3; ++l) {
-        const size_t fin = col.size(), fout = b[l].size();
-        std::vector<double> row(fout, 0.0);
-        for (size_t i = 0; i < fout; ++i) {
-            for (size_t k = 0; k < fin; ++k) row[i] = larger(row[i], W[l][i * fin + k] *= col[k]);
-            if (l < 2) row[i] = larger(row[i], b[l][i]);
+        const int fin = n[l], fout = n[l + 1];
+        m.assign(fout, 0);
+        for (int i = 0; i < fout; ++i) {
+            float* w = W[l] + (size_t)i * fin;
+            int r = l < 2 ? magnitude(b[l][i]) : 0;
+            for (int k = 0; k < fin; ++k) {
+                w[k] *= col[k];
+                r = std::max(r, magnitude(w[k]));
+            }
+            m[i] = r;
         }
-        row = raise(row, false, l == 2 ? &out_scale : nullptr);
-        for (size_t i = 0; i < fout; ++i) {
-            for (size_t k = 0; k < fin; ++k) W[l][i * fin + k] *= row[i];
-            b[l][i] *= row[i];
-            row[i] = 1.0 / row[i];
+        std::vector<float> row = raise(m, false, l == 2 ? out_scale : nullptr);
+        for (int i = 0; i < fout; ++i) {
+            float* w = W[l] + (size_t)i * fin;
+            const float f = row[i];
+            for (int k = 0; k < fin; ++k) w[k] *= f;
+            b[l][i] *= f;
+            row[i] = 1.f / f;
             if (l == 2) out_scale[i] *= row[i];
         }
         col.swap(row);
@@ -804,16 +824,6 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     const int h1t = ceil_div(h1, 16), h2t = ceil_div(h2, 16), ot = ceil_div(n_out, 16);
     std::vector<double> rstd(n_in);
     for (int i = 0; i < n_in; ++i) rstd[i] = 1.0 / sd[i];
-    if (!bf) even_out(rstd, W, bias, osc);
-    // FP32 weights are split into two FP16 planes after a power-of-two scale that
-    // brings the layer's largest weight to [2^14, 2^15)
-    auto scale_exponent = [](const std::vector<double>& W) {
-        float m = 0.f;
-        for (double v : W)
-            if (isfinite((float)v)) m = std::max(m, fabsf((float)v));
-        return m > 0.f ? std::min(14 - ilogbf(m), 100) : 0;
-    };
-    const int we[3] = {bf ? 0 : scale_exponent(W[0]), bf ? 0 : scale_exponent(W[1]), bf ? 0 : scale_exponent(W[2])};
     // every FP32 array in one upload, each on 256 bytes and zero-padded to its
     // length on the device: the layers' weights (packed there), biases, scalers
     std::vector<float> f32;
@@ -827,6 +837,19 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     const size_t off_b[3] = {add(bias[0], 16 * h1t), add(bias[1], 16 * h2t), add(bias[2], 16 * ot)};
     const size_t off_mean = add(mean, n_in), off_rstd = add(rstd, n_in);
     const size_t off_sc = add(osc, kMlpMaxOut), off_sh = add(osh, kMlpMaxOut);
+    // FP32 weights are split into two FP16 planes after a power-of-two scale that
+    // brings the layer's largest weight to [2^14, 2^15)
+    int we[3] = {0, 0, 0};
+    if (!bf) {
+        float* const p = f32.data();
+        even_out({n_in, h1, h2, n_out}, p + off_rstd, {p + off_w[0], p + off_w[1], p + off_w[2]},
+                 {p + off_b[0], p + off_b[1], p + off_b[2]}, p + off_sc);
+        for (int l = 0; l < 3; ++l) {
+            int m = 0;
+            for (size_t i = 0; i < W[l].size(); ++i) m = std::max(m, magnitude(p[off_w[l] + i]));
+            we[l] = m ? std::min(14 - exponent(m), 100) : 0;
+        }
+    }
 
     // packed A operands of every layer, and of the transposes (for the network's
     // vector-Jacobian product, FP32 only: their K runs over the padded output
