@@ -892,7 +892,10 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     a.in_pad = in_pad; a.h1_tiles = h1t; a.h2_tiles = h2t; a.out_tiles = ot;
     a.slope = (float)slope;
     a.out_act = out_act ? 1 : 0;
-    for (int l = 0; l < 3; ++l) a.wexp[l] = we[l];
+    for (int l = 0; l < 3; ++l) {
+        a.wexp[l] = we[l];
+        a.Wf[l] = fd + off_w[l];
+    }
     a.W1 = packed_ptr[0];
     a.W2 = packed_ptr[1];
     a.W3 = packed_ptr[2];

@@ -281,6 +281,7 @@ struct MlpArgs {
     const void* W1;              // packed A operands: BF16, or two FP16 planes for FP32 weights
     const void* W2;
     const void* W3;
+    const float* Wf[3];          // FP32 weights: [out][in], as packed but for the scale (BF16: unused)
     const float* b1;             // padded biases (zeros in the padding)
     const float* b2;
     const float* b3;

@@ -194,6 +194,23 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
                 for (int q = 4 * n4 + threadIdx.x; q < nf; q += kWaves * 64) g_out[q] = out[q];
             });
         }
+        if constexpr (MODE == kModeLdos && P == 2) {
+            unsigned long long again = infinite_points(s_max, 3, rows, lane);
+            if (again) {
+                PlainPoint& q = *reinterpret_cast<PlainPoint*>(smem);
+                __syncthreads();                     // the rows in LDS are out
+                for (; again; again &= again - 1) {
+                    const int64_t p = p0 + __ffsll(again) - 1;
+                    const int t = plain_thread();
+                    plain_hidden(a, B + p * row_stride * n_in, q, t);
+                    plain_layer(a.Wf[2], a.b3, a.n_out, a.n_h2, q.h2, t, [&](int e, float y) {
+                        if (a.out_act) y = leaky<false>(y, a.slope);
+                        o.ldos[p * a.n_out + e] = (float)((double)a.out_scale[e] * (double)y + (double)a.out_shift[e]);
+                    });
+                    __syncthreads();
+                }
+            }
+        }
         if constexpr (WINDOW || DENSITY) {
             double* s_part = reinterpret_cast<double*>(smem);      // [wave][point], over the activation tile
             __syncthreads();

@@ -431,7 +431,7 @@ __device__ __forceinline__ float unscale(const unsigned* s_max, int point, int w
 // Standardised descriptor rows of a tile into LDS: wave w takes rows w R ..
 // w R + R - 1, lane = columns lane and lane + 64, at most twelve rows'
 // reads in flight.  A row past the last valid point repeats that point (its
-// results are not used), a pad column the last one with mean and 1/std zero.
+// results are not used), a pad column the last one.
 template <int P, int NT, int RS>
 __device__ __forceinline__ void stage_rows(const float* __restrict__ B, int64_t p0, int rows, int row_stride, int n_in,
                                            int in_pad, const float (&mu)[2], const float (&rstd)[2],
@@ -450,7 +450,9 @@ __device__ __forceinline__ void stage_rows(const float* __restrict__ B, int64_t 
 #pragma unroll
         for (int q = 0; q < C; ++q) {
             const int p = wave * R + q0 + q;
-            const float x0 = (v[q][0] - mu[0]) * rstd[0], x1 = (v[q][1] - mu[1]) * rstd[1];
+            // a pad column is zero also where the last one is infinite
+            const float x0 = lane < n_in ? (v[q][0] - mu[0]) * rstd[0] : 0.f;
+            const float x1 = lane + 64 < n_in ? (v[q][1] - mu[1]) * rstd[1] : 0.f;
             unsigned short* d = t.p + p * RS + lane;
             if constexpr (P == 2) {
                 const unsigned mx = wave_max_u32(max((unsigned)__float_as_int(x0) & 0x7fffffffu, (unsigned)__float_as_int(x1) & 0x7fffffffu));
@@ -471,6 +473,53 @@ __device__ __forceinline__ void stage_rows(const float* __restrict__ B, int64_t 
             }
         }
     }
+}
+
+// The FP16 planes of an infinity are infinity and NaN, and its product with the second
+// plane of a weight has any sign, so a point with an infinite input or activation
+// comes out of the matrix unit as NaN where FP32 has an infinity: its units' signs,
+// and with them the gradient, would be lost.  Such points are done again, one at a
+// time by the whole block, in plain FP32.  The tile's points that need it (NaN
+// without an infinity does not): s_max holds the largest magnitude of each of the
+// layers' inputs.
+template <int NP>
+__device__ __forceinline__ unsigned long long infinite_points(const unsigned (*s_max)[NP], int layers, int rows, int lane) {
+    static_assert(NP <= 64, "one lane per point");
+    bool inf = false;
+    for (int l = 0; l < layers; ++l) inf = inf || s_max[l][lane % NP] == 0x7f800000u;
+    return __ballot(inf && lane < rows);
+}
+
+// Units of one layer of one point from LDS: f(unit, W in + b).  t: the thread, in a
+// register of its own, or the addresses formed from it stay in registers all along.
+template <typename F>
+__device__ __forceinline__ void plain_layer(const float* __restrict__ W, const float* __restrict__ b, int n_out, int n_in,
+                                            const float* in, int t, F&& f) {
+    for (int u = t; u < n_out; u += kWaves * 64) {
+        float z = b[u];
+#pragma clang loop unroll(disable)
+        for (int k = 0; k < n_in; ++k) z = fmaf(W[(unsigned)(u * n_in + k)], in[k], z);
+        f(u, z);
+    }
+}
+__device__ __forceinline__ int plain_thread() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// Inputs and hidden activations of one point in plain FP32 (LDS of PlainPoint;
+// a barrier has passed since the last write).
+struct PlainPoint {
+    float x[kMlpMaxIn], h1[kMlpMaxHidden], h2[kMlpMaxHidden], d[kMlpMaxOut];
+};
+__device__ __forceinline__ void plain_hidden(const MlpArgs& a, const float* __restrict__ row, PlainPoint& q, int t) {
+    for (int k = t; k < a.n_in; k += kWaves * 64) q.x[k] = (row[k] - a.in_mean[k]) * a.in_rstd[k];
+    __syncthreads();
+    plain_layer(a.Wf[0], a.b1, a.n_h1, a.n_in, q.x, t, [&](int u, float z) { q.h1[u] = leaky<false>(z, a.slope); });
+    __syncthreads();
+    plain_layer(a.Wf[1], a.b2, a.n_h2, a.n_h1, q.h1, t, [&](int u, float z) { q.h2[u] = leaky<false>(z, a.slope); });
+    __syncthreads();
 }
 
 }  // namespace mala

@@ -133,7 +133,32 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
                 }
             }
         }
+        unsigned long long again = infinite_points(s_max, 6, rows, lane);
         __syncthreads();                       // every wave has read the activation tile
+        for (; again; again &= again - 1) {
+            PlainPoint& q = *reinterpret_cast<PlainPoint*>(smem);
+            const int64_t p = p0 + __ffsll(again) - 1;
+            const int t = plain_thread();
+            plain_hidden(a, B + p * n_in, q, t);
+            plain_layer(a.Wf[2], a.b3, n_out, a.n_h2, q.h2, t, [&](int e, float y) {
+                q.d[e] = v[p * n_out + e] * a.out_scale[e] * (a.out_act && !(y > 0.f) ? slope : 1.f);
+            });
+            // delta over the units of `h` in place, from the delta of the layer W leads to
+            auto back = [&](const float* W, int fout, const float* delta, int n, auto&& f) {
+                __syncthreads();
+                for (int u = t; u < n; u += kWaves * 64) {
+                    float z = 0.f;
+#pragma clang loop unroll(disable)
+                    for (int i = 0; i < fout; ++i) z = fmaf(W[(unsigned)(i * n + u)], delta[i], z);
+                    f(u, z);
+                }
+            };
+            auto through = [&](float* h) { return [=](int u, float z) { h[u] = z * (h[u] > 0.f ? 1.f : slope); }; };
+            back(a.Wf[2], n_out, q.d, a.n_h2, through(q.h2));
+            back(a.Wf[1], a.n_h2, q.h2, a.n_h1, through(q.h1));
+            back(a.Wf[0], a.n_h1, q.h1, n_in, [&](int k, float z) { g_out[p * n_in + k] = z * a.in_rstd[k]; });
+            __syncthreads();
+        }
     }
 }
 
