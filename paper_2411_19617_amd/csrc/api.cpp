@@ -1000,20 +1000,23 @@ mala_status mala_ace_descriptors(mala_ctx* c, const double* positions, int32_t n
     DeviceGuard g(c->device);
     AceTables& t = c->ace[nmax][lmax];
     const bool rows = layout == MALA_LAYOUT_POINT_MAJOR;
-    int*& plan_d = t.plan[rows ? 0 : 1];
-    int& plan_ints = t.plan_ints[rows ? 0 : 1];
-    if (!plan_d) {
+    // both layouts' plans at the first use of a size: a later call in either one
+    // allocates nothing and can be captured
+    for (int dm = 0; dm < 2; ++dm) {
+        if (t.plan[dm]) continue;
         std::vector<int> plan;
-        build_ace_plan(nmax, lmax, rows ? kTile / kAceRowPoints : 1, plan);
-        plan_ints = (int)plan.size();
+        build_ace_plan(nmax, lmax, dm ? 1 : kTile / kAceRowPoints, plan);
+        t.plan_ints[dm] = (int)plan.size();
         ++c->n_allocs;
         int* d = nullptr;
         HIP_TRY(hipMalloc(&d, sizeof(int) * plan.size()));
         const hipError_t e = hipMemcpy(d, plan.data(), sizeof(int) * plan.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) (void)hipFree(d);
         HIP_TRY(e);
-        plan_d = d;
+        t.plan[dm] = d;
     }
+    const int* plan_d = t.plan[rows ? 0 : 1];
+    const int plan_ints = t.plan_ints[rows ? 0 : 1];
     const int n_desc = mala_ace_count(nmax, lmax);
     // point-major [point][descriptor] or descriptor-major [descriptor][point]
     const int64_t ps = rows ? n_desc : 1, ds = pt_end - pt_begin;
@@ -1066,7 +1069,8 @@ mala_status mala_ace4_descriptors(mala_ctx* c, const double* positions, int32_t 
     DeviceGuard g(c->device);
     Ace4Tables& t = c->ace4[nmax4][lmax4];
     const bool pm = layout == MALA_LAYOUT_POINT_MAJOR;
-    if (pm && !t.rows_plan) {
+    // both layouts' tables at the first use of a size, as for ranks 1-3
+    if (!t.rows_plan) {
         std::vector<int> plan;
         build_ace4_rows_plan(nmax4, lmax4, plan, t.n_slots);
         t.rows_ints = (int)plan.size();
@@ -1079,7 +1083,7 @@ mala_status mala_ace4_descriptors(mala_ctx* c, const double* positions, int32_t 
         HIP_TRY(e);
         t.rows_plan = d;
     }
-    if (!pm && !t.ready) {
+    if (!t.ready) {
         std::vector<int> l_units, l_descs;
         std::vector<int4> units, descs;
         std::vector<float> coef;
