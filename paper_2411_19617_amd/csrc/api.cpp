@@ -837,6 +837,7 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     const size_t off_b[3] = {add(bias[0], 16 * h1t), add(bias[1], 16 * h2t), add(bias[2], 16 * ot)};
     const size_t off_mean = add(mean, n_in), off_rstd = add(rstd, n_in);
     const size_t off_sc = add(osc, kMlpMaxOut), off_sh = add(osh, kMlpMaxOut);
+    const size_t off_plain = add({}, sizeof(MlpPlain) / sizeof(float));
     // FP32 weights are split into two FP16 planes after a power-of-two scale that
     // brings the layer's largest weight to [2^14, 2^15)
     int we[3] = {0, 0, 0};
@@ -873,6 +874,9 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     if (e == hipSuccess) w->allocs.push_back(fd);
     if (e == hipSuccess) e = hipMalloc(&pd, sizeof(uint16_t) * packed);
     if (e == hipSuccess) w->allocs.push_back(pd);
+    const MlpPlain plain{{fd + off_w[0], fd + off_w[1], fd + off_w[2]}, {fd + off_b[0], fd + off_b[1], fd + off_b[2]},
+                         fd + off_mean, fd + off_rstd, fd + off_sc, fd + off_sh, {n_in, h1, h2, n_out}, (float)slope, out_act ? 1 : 0};
+    memcpy(&f32[off_plain], &plain, sizeof(plain));
     if (e == hipSuccess) e = hipMemcpy(fd, f32.data(), sizeof(float) * f32.size(), hipMemcpyHostToDevice);
     const void* packed_ptr[6] = {};
     for (int i = 0; i < n_packs && e == hipSuccess; ++i) {
@@ -892,10 +896,8 @@ mala_status mala_weights_load(mala_ctx* c, const void* blob, size_t bytes, int32
     a.in_pad = in_pad; a.h1_tiles = h1t; a.h2_tiles = h2t; a.out_tiles = ot;
     a.slope = (float)slope;
     a.out_act = out_act ? 1 : 0;
-    for (int l = 0; l < 3; ++l) {
-        a.wexp[l] = we[l];
-        a.Wf[l] = fd + off_w[l];
-    }
+    for (int l = 0; l < 3; ++l) a.wexp[l] = we[l];
+    a.plain = reinterpret_cast<const MlpPlain*>(fd + off_plain);
     a.W1 = packed_ptr[0];
     a.W2 = packed_ptr[1];
     a.W3 = packed_ptr[2];
@@ -1158,7 +1160,10 @@ mala_status mala_ldos_infer(mala_ctx* c, const mala_weights* w, const float* B, 
     MlpOut o;
     o.ldos = ldos_out;
     HIP_TRY(staged(c, MALA_STAGE_MLP_LDOS, n_pts,
-                   [&] { return launch_mlp(c->stream, w->args, kModeLdos, B, n_pts, 1, mlp_blocks(n_pts), o); }));
+                   [&] {
+                       const int nb = mlp_blocks(n_pts, mlp_rows_small(w->args) ? 2 : 1);
+                       return launch_mlp(c->stream, w->args, kModeLdos, B, n_pts, 1, nb, o);
+                   }));
     return MALA_OK;
 }
 

@@ -271,6 +271,14 @@ hipError_t launch_zb(hipStream_t s, int twojmax, int64_t n_pts, const float2* u_
 hipError_t launch_gauss(hipStream_t s, const BinState& bins, const int N[3], double sigma, double cutoff,
                         int64_t pt_begin, int64_t n_pts, float* out, int* err_flag);
 
+// The network as FP32 arrays, weights [out][in].  In device memory: few points need
+// it, and its pointers as kernel arguments would hold scalar registers all along.
+struct MlpPlain {
+    const float *W[3], *b[3], *in_mean, *in_rstd, *out_scale, *out_shift;
+    int n[4];                    // widths
+    float slope;
+    int out_act;
+};
 struct MlpArgs {
     int precision;               // 0 fp32, 1 bf16
     int n_in, n_h1, n_h2, n_out; // logical widths
@@ -281,7 +289,7 @@ struct MlpArgs {
     const void* W1;              // packed A operands: BF16, or two FP16 planes for FP32 weights
     const void* W2;
     const void* W3;
-    const float* Wf[3];          // FP32 weights: [out][in], as packed but for the scale (BF16: unused)
+    const MlpPlain* plain;       // device (FP32 weights only)
     const float* b1;             // padded biases (zeros in the padding)
     const float* b2;
     const float* b3;
@@ -326,10 +334,16 @@ struct MlpOut {
 size_t packed_weight_elems(int mtiles, int kt, int planes);
 hipError_t launch_pack_weights(hipStream_t s, const float* W, int fout, int fin, bool transposed, int mtiles, int kt,
                                int planes, int wexp, void* out);
-int mlp_blocks(int64_t n_pts);
+int mlp_blocks(int64_t n_pts, int per_cu = 1);
 int mlp_point_tiles(const MlpArgs& a, int64_t n_pts, int n_blocks);
-// Rows of 400 units hold the widest layer of the network (else rows of 528).
-constexpr int kRowWide = 400, kRowMax = 528;
+// Rows of the activation tile, in units: 528 hold any layer; 400, the widest that
+// three unit tiles per wave and one left over reach (more accumulators per wave
+// spill), and 144 where no layer has more than 128 units, one unit tile per wave: its
+// registers and LDS leave room for two blocks on a CU, which such layers need, as
+// a tile is mostly latency (16-16-16-16, 100,003 points, FP32: 50 us with rows of
+// 400, 35 with these).
+constexpr int kRowSmall = 144, kRowWide = 400, kRowMax = 528;
+inline bool mlp_rows_small(const MlpArgs& a) { return std::max({a.h1_tiles, a.h2_tiles, a.out_tiles}) <= 8; }
 inline bool mlp_rows_wide(const MlpArgs& a) { return 16 * std::max(a.h1_tiles, a.h2_tiles) <= kRowWide; }
 bool mlp_vjp_supported(const MlpArgs& a);
 hipError_t launch_mlp_vjp(hipStream_t s, const MlpArgs& a, const float* B, const float* v, int64_t n_pts,

@@ -23,9 +23,9 @@
 namespace mala {
 
 template <int P, int MODE, int NT, int MT, int RS>
-__global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* __restrict__ B, int64_t n_pts,
+__global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp(MlpArgs a, const float* __restrict__ B, int64_t n_pts,
                                                         int row_stride, MlpOut o) {
-    constexpr int NP = 16 * NT, OT = kMlpMaxOut / 16 / kWaves;      // output tiles of a wave, at most
+    constexpr int NP = 16 * NT, OT = out_unit_tiles(MT);      // output tiles of a wave, at most
     constexpr bool WINDOW = MODE == kModeDosWindow, DENSITY = MODE == kModeDensity;
     constexpr bool DOS = MODE == kModeDos || WINDOW;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
     const float rstd[2] = {lane0 < n_in ? a.in_rstd[lane0] : 0.f, lane0 + 64 < n_in ? a.in_rstd[lane0 + 64] : 0.f};
     const bool fast_act = a.slope > 0.f && a.slope <= 1.f;
     // the stored LDOS goes out through the activation tile, SP points at a time
-    constexpr int SP = ActTile<P, NT, RS>::kBytes / (sizeof(float) * kMlpMaxOut) >= NP ? NP : 16;
+    constexpr int SP = ActTile<P, NT, RS>::kBytes / (sizeof(float) * 16 * kWaves * OT) >= NP ? NP : 16;
     const bool wide = (reinterpret_cast<uintptr_t>(o.ldos) & 15) == 0;      // a tile's rows start on 16 bytes then
 
     for (int64_t it = it_begin; it < it_end; ++it) {
@@ -91,14 +91,16 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
 #pragma clang loop unroll(disable)
         for (int l = 0; l < 2; ++l) {
             const float* bias = l == 0 ? a.b1 : a.b2;
-            const Share<NT> sh(l == 0 ? a.h1_tiles : a.h2_tiles, wave, true);
-            layer_mm<P, NT, MT, RS, true>(l == 0 ? a.W1 : a.W2, l == 0 ? in_tiles : a.h1_tiles, sh, act, wave, lane, acc);
+            const Share<NT> sh(l == 0 ? a.h1_tiles : a.h2_tiles, wave, MT > 1);
+            f4 b0{};                                 // one unit tile per wave: its bias comes during the products
+            if (MT == 1 && sh.cnt > 0) b0 = bias4(bias, 16 * wave + 4 * g);
+            layer_mm<P, NT, MT, RS, (MT > 1)>(l == 0 ? a.W1 : a.W2, l == 0 ? in_tiles : a.h1_tiles, sh, act, wave, lane, acc);
             float c[NT];
 #pragma unroll
             for (int n = 0; n < NT; ++n) c[n] = unscale<P>(s_max[l], 16 * n + j, a.wexp[l]);
             auto out = [&](auto fast) {
                 layer_out<P, NT, MT, RS>(acc, sh, act, s_max[l + 1], wave, lane, [&](auto slot, int mt, int n, f4& v) {
-                    const f4 b = bias4(bias, 16 * mt + 4 * g);
+                    const f4 b = MT == 1 ? b0 : bias4(bias, 16 * mt + 4 * g);
                     float cn;
                     if constexpr (decltype(slot)::value < MT) cn = c[n];
                     else cn = unscale<P>(s_max[l], 16 * n + j, a.wexp[l]);
@@ -111,8 +113,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
             else out(std::false_type{});
         }
         Acc<NT, OT> acc3;
+        f4 out0[3] = {};
         {
             const Share<NT> sh(a.out_tiles, wave, false);
+            if (MT == 1 && sh.cnt > 0) {
+                const int e0 = 16 * wave + 4 * g;
+                out0[0] = bias4(a.b3, e0);
+                out0[1] = bias4(a.out_scale, e0);
+                out0[2] = bias4(a.out_shift, e0);
+            }
             layer_mm<P, NT, OT, RS, false>(a.W3, a.h2_tiles, sh, act, wave, lane, acc3);
         }
 
@@ -131,7 +140,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
             // in FP64, rounded once), so that the stored LDOS, the DOS, the
             // window, its prefix and a recomputed density all use identical numbers
             // (bias and scaler rows are zero-padded: energies past n_out give zero)
-            const f4 b = bias4(a.b3, e0), scf = bias4(a.out_scale, e0), shf = bias4(a.out_shift, e0);
+            const f4 b = MT == 1 ? out0[0] : bias4(a.b3, e0), scf = MT == 1 ? out0[1] : bias4(a.out_scale, e0),
+                     shf = MT == 1 ? out0[2] : bias4(a.out_shift, e0);
             float df[4][NT];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -202,10 +212,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp(MlpArgs a, const float* 
                 for (; again; again &= again - 1) {
                     const int64_t p = p0 + __ffsll(again) - 1;
                     const int t = plain_thread();
-                    plain_hidden(a, B + p * row_stride * n_in, q, t);
-                    plain_layer(a.Wf[2], a.b3, a.n_out, a.n_h2, q.h2, t, [&](int e, float y) {
-                        if (a.out_act) y = leaky<false>(y, a.slope);
-                        o.ldos[p * a.n_out + e] = (float)((double)a.out_scale[e] * (double)y + (double)a.out_shift[e]);
+                    const MlpPlain& w = *a.plain;
+                    plain_hidden(w, B + p * row_stride * w.n[0], q, t);
+                    plain_layer(w.W[2], w.b[2], w.n[3], w.n[2], q.h2, t, [&](int e, float y) {
+                        if (w.out_act) y = leaky<false>(y, w.slope);
+                        o.ldos[p * w.n[3] + e] = (float)((double)w.out_scale[e] * (double)y + (double)w.out_shift[e]);
                     });
                     __syncthreads();
                 }
@@ -284,7 +295,7 @@ int mlp_point_tiles(const MlpArgs& a, int64_t n_pts, int n_blocks) {
         return (double)((tiles + n_blocks - 1) / n_blocks) * (NT + 1.5);
     };
     int best = cost(4) <= cost(2) ? 4 : 2;
-    if (a.precision == 1 && mlp_rows_wide(a) && cost(6) <= cost(best)) best = 6;
+    if (a.precision == 1 && !mlp_rows_small(a) && mlp_rows_wide(a) && cost(6) <= cost(best)) best = 6;
     return best;
 }
 
@@ -292,6 +303,10 @@ template <int P, int MODE>
 static hipError_t launch_pm(hipStream_t s, const MlpArgs& a, const float* B, int64_t n_pts, int row_stride,
                             int n_blocks, const MlpOut& o) {
     const int nt = mlp_point_tiles(a, n_pts, n_blocks);
+    if (mlp_rows_small(a)) {
+        if (nt == 4) return launch_pmn<P, MODE, 4, 1, kRowSmall>(s, a, B, n_pts, row_stride, n_blocks, o);
+        return launch_pmn<P, MODE, 2, 1, kRowSmall>(s, a, B, n_pts, row_stride, n_blocks, o);
+    }
     if (mlp_rows_wide(a)) {
         if constexpr (P == 1)
             if (nt == 6) return launch_pmn<P, MODE, 6, 3, kRowWide>(s, a, B, n_pts, row_stride, n_blocks, o);
@@ -302,10 +317,10 @@ static hipError_t launch_pm(hipStream_t s, const MlpArgs& a, const float* B, int
     return launch_pmn<P, MODE, 2, 4, kRowMax>(s, a, B, n_pts, row_stride, n_blocks, o);
 }
 
-// One block per CU, fewer when there are not that many 32-point tiles.
-int mlp_blocks(int64_t n_pts) {
-    const int64_t it = (n_pts + 31) / 32;
-    return (int)(it < kMlpBlocks ? (it > 0 ? it : 1) : kMlpBlocks);
+// One block per CU, or per_cu, fewer when there are not that many 32-point tiles.
+int mlp_blocks(int64_t n_pts, int per_cu) {
+    const int64_t it = (n_pts + 31) / 32, most = (int64_t)kMlpBlocks * per_cu;
+    return (int)(it < most ? (it > 0 ? it : 1) : most);
 }
 
 // Weights W [fout][fin] (or, transposed, the layer with the widths swapped) as A

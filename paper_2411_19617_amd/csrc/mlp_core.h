@@ -78,6 +78,11 @@ __device__ __forceinline__ f4 mfma16(uint2 a, uint2 b, f4 c) {
     else return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bits_as<s4>(a), bits_as<s4>(b), c, 0, 0, 0);
 }
 
+// Unit tiles of the output layer a wave holds, and waves per SIMD, of a kernel whose waves
+// hold MT of a hidden layer.
+__host__ __device__ constexpr int out_unit_tiles(int MT) { return MT == 1 ? 1 : kMlpMaxOut / 16 / kWaves; }
+constexpr int waves_per_simd(int MT) { return MT == 1 ? 4 : 2; }
+
 // The activation tile of a block, [plane][point][unit], for NT point tiles and
 // layers of at most RS units.  The row stride RS (16-bit elements) is an odd
 // multiple of 8 dwords, which makes the 128-bit operand reads (16 points x 4
@@ -178,7 +183,6 @@ __device__ __forceinline__ void mm(const void* W, int T, const ActTile<P, NT, RS
     fetch(0, c0, a[0]);
     static_for<0, M>([&](auto mc) {
         static_for<0, NT>([&](auto nc) {
-            t[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f};
             if constexpr (P == 2) tl[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f};
         });
     });
@@ -297,6 +301,12 @@ __device__ __forceinline__ f4 mm_item(const void* W, int T, const Share<NT>& sh,
 template <int P, int NT, int MT, int RS, bool ITEMS>
 __device__ __forceinline__ void layer_mm(const void* W, int T, const Share<NT>& sh, const ActTile<P, NT, RS>& in,
                                          int wave, int lane, Acc<NT, MT>& acc) {
+    // every tile, also those this wave has none of: what they held before would
+    // stay live beside the products
+    static_for<0, MT>([&](auto mc) {
+        static_for<0, NT>([&](auto nc) { acc.t[decltype(mc)::value][decltype(nc)::value] = f4{0.f, 0.f, 0.f, 0.f}; });
+    });
+    if constexpr (ITEMS) acc.it = f4{0.f, 0.f, 0.f, 0.f};
     static_for<1, MT + 1>([&](auto mc) {
         if (sh.cnt == decltype(mc)::value) mm<P, NT, MT, RS, decltype(mc)::value>(W, T, in, wave, lane, acc.t);
     });
@@ -513,12 +523,13 @@ __device__ __forceinline__ int plain_thread() {
 struct PlainPoint {
     float x[kMlpMaxIn], h1[kMlpMaxHidden], h2[kMlpMaxHidden], d[kMlpMaxOut];
 };
-__device__ __forceinline__ void plain_hidden(const MlpArgs& a, const float* __restrict__ row, PlainPoint& q, int t) {
-    for (int k = t; k < a.n_in; k += kWaves * 64) q.x[k] = (row[k] - a.in_mean[k]) * a.in_rstd[k];
+__device__ __forceinline__ void plain_hidden(const MlpPlain& w, const float* __restrict__ row, PlainPoint& q,
+                                             int t) {
+    for (int k = t; k < w.n[0]; k += kWaves * 64) q.x[k] = (row[k] - w.in_mean[k]) * w.in_rstd[k];
     __syncthreads();
-    plain_layer(a.Wf[0], a.b1, a.n_h1, a.n_in, q.x, t, [&](int u, float z) { q.h1[u] = leaky<false>(z, a.slope); });
+    plain_layer(w.W[0], w.b[0], w.n[1], w.n[0], q.x, t, [&](int u, float z) { q.h1[u] = leaky<false>(z, w.slope); });
     __syncthreads();
-    plain_layer(a.Wf[1], a.b2, a.n_h2, a.n_h1, q.h1, t, [&](int u, float z) { q.h2[u] = leaky<false>(z, a.slope); });
+    plain_layer(w.W[1], w.b[1], w.n[2], w.n[1], q.h1, t, [&](int u, float z) { q.h2[u] = leaky<false>(z, w.slope); });
     __syncthreads();
 }
 

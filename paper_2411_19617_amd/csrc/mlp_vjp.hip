@@ -19,7 +19,7 @@
 namespace mala {
 
 template <int NT, int MT, int RS>
-__global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const float* __restrict__ B,
+__global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp_vjp(MlpArgs a, const float* __restrict__ B,
                                                             const float* __restrict__ v, int64_t n_pts,
                                                             float* __restrict__ g_out) {
     constexpr int NP = 16 * NT;
@@ -56,8 +56,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
         static_for<0, 2>([&](auto lc) {
             constexpr int l = decltype(lc)::value;
             const float* bias = l == 0 ? a.b1 : a.b2;
-            const Share<NT> sh(l == 0 ? a.h1_tiles : a.h2_tiles, wave, true);
-            layer_mm<2, NT, MT, RS, true>(l == 0 ? a.W1 : a.W2, l == 0 ? in_tiles : a.h1_tiles, sh, act, wave, lane, acc);
+            const Share<NT> sh(l == 0 ? a.h1_tiles : a.h2_tiles, wave, MT > 1);
+            f4 b0{};                           // one unit tile per wave: its bias comes during the products
+            if (MT == 1 && sh.cnt > 0) b0 = bias4(bias, 16 * wave + 4 * g);
+            layer_mm<2, NT, MT, RS, (MT > 1)>(l == 0 ? a.W1 : a.W2, l == 0 ? in_tiles : a.h1_tiles, sh, act, wave, lane, acc);
             float c[NT];
 #pragma unroll
             for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[l], 16 * n + j, a.wexp[l]);
@@ -65,7 +67,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
             for (int m = 0; m <= MT; ++m) mask[l][m] = 0;
             layer_out<2, NT, MT, RS>(acc, sh, act, s_max[l + 1], wave, lane, [&](auto slotc, int mt, int n, f4& z) {
                 constexpr int slot = decltype(slotc)::value;
-                const f4 b = bias4(bias, 16 * mt + 4 * g);
+                const f4 b = MT == 1 ? b0 : bias4(bias, 16 * mt + 4 * g);
                 float cn;
                 if constexpr (slot < MT) cn = c[n];
                 else cn = unscale<2>(s_max[l], 16 * n + j, a.wexp[l]);
@@ -81,18 +83,33 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
         // output layer and delta3 = s .* v .* sigma'(z3)
         {
             const Share<NT> sh(a.out_tiles, wave, false);
+            auto vector = [&](int n, int e) {
+                return v[(p0 + min(16 * n + j, rows - 1)) * n_out + min(e, n_out - 1)];
+            };
+            f4 b0{}, s0{}, v0[MT == 1 ? NT : 1] = {};      // as the hidden layers' bias
+            if constexpr (MT == 1)
+                if (sh.cnt > 0) {
+                    const int e0 = 16 * wave + 4 * g;
+                    b0 = bias4(a.b3, e0);
+                    s0 = bias4(a.out_scale, e0);
+#pragma unroll
+                    for (int n = 0; n < NT; ++n)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v0[n][r] = vector(n, e0 + r);
+                }
             layer_mm<2, NT, MT, RS, false>(a.W3, a.h2_tiles, sh, act, wave, lane, acc);
             float c[NT];
 #pragma unroll
             for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[2], 16 * n + j, a.wexp[2]);
             layer_out<2, NT, MT, RS>(acc, sh, act, s_max[3], wave, lane, [&](auto, int mt, int n, f4& z) {
-                const f4 b = bias4(a.b3, 16 * mt + 4 * g);
+                const f4 b = MT == 1 ? b0 : bias4(a.b3, 16 * mt + 4 * g);
                 const int pj = 16 * n + j;
-                const float* vp = v + (p0 + min(pj, rows - 1)) * n_out;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int e = 16 * mt + 4 * g + r;
-                    float x = vp[min(e, n_out - 1)] * a.out_scale[e];
+                    float x;
+                    if constexpr (MT == 1) x = v0[n][r] * s0[r];
+                    else x = vector(n, e) * a.out_scale[e];
                     if (a.out_act && !(fmaf(z[r], c[n], b[r]) > 0.f)) x *= slope;
                     z[r] = (pj < rows && e < n_out) ? x : 0.f;
                 }
@@ -101,9 +118,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
         // delta2 = (W3^T delta3) .* sigma'(z2), delta1 = (W2^T delta2) .* sigma'(z1)
         static_for<0, 2>([&](auto lc) {
             constexpr int l = decltype(lc)::value;
-            const Share<NT> sh(l == 0 ? a.h2_tiles : a.h1_tiles, wave, true);
+            const Share<NT> sh(l == 0 ? a.h2_tiles : a.h1_tiles, wave, MT > 1);
             const int we = a.wexp[l == 0 ? 2 : 1];
-            layer_mm<2, NT, MT, RS, true>(l == 0 ? a.W3T : a.W2T, l == 0 ? a.out_tiles : a.h2_tiles, sh, act, wave, lane, acc);
+            layer_mm<2, NT, MT, RS, (MT > 1)>(l == 0 ? a.W3T : a.W2T, l == 0 ? a.out_tiles : a.h2_tiles, sh, act, wave, lane, acc);
             float c[NT];
 #pragma unroll
             for (int n = 0; n < NT; ++n) c[n] = unscale<2>(s_max[3 + l], 16 * n + j, we);
@@ -139,9 +156,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
             PlainPoint& q = *reinterpret_cast<PlainPoint*>(smem);
             const int64_t p = p0 + __ffsll(again) - 1;
             const int t = plain_thread();
-            plain_hidden(a, B + p * n_in, q, t);
-            plain_layer(a.Wf[2], a.b3, n_out, a.n_h2, q.h2, t, [&](int e, float y) {
-                q.d[e] = v[p * n_out + e] * a.out_scale[e] * (a.out_act && !(y > 0.f) ? slope : 1.f);
+            const MlpPlain& w = *a.plain;
+            plain_hidden(w, B + p * w.n[0], q, t);
+            plain_layer(w.W[2], w.b[2], w.n[3], w.n[2], q.h2, t, [&](int e, float y) {
+                q.d[e] = v[p * w.n[3] + e] * w.out_scale[e] * (w.out_act && !(y > 0.f) ? w.slope : 1.f);
             });
             // delta over the units of `h` in place, from the delta of the layer W leads to
             auto back = [&](const float* W, int fout, const float* delta, int n, auto&& f) {
@@ -153,10 +171,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void k_mlp_vjp(MlpArgs a, const flo
                     f(u, z);
                 }
             };
-            auto through = [&](float* h) { return [=](int u, float z) { h[u] = z * (h[u] > 0.f ? 1.f : slope); }; };
-            back(a.Wf[2], n_out, q.d, a.n_h2, through(q.h2));
-            back(a.Wf[1], a.n_h2, q.h2, a.n_h1, through(q.h1));
-            back(a.Wf[0], a.n_h1, q.h1, n_in, [&](int k, float z) { g_out[p * n_in + k] = z * a.in_rstd[k]; });
+            auto through = [&](float* h) { return [h, slope = w.slope](int u, float z) { h[u] = z * (h[u] > 0.f ? 1.f : slope); }; };
+            back(w.W[2], w.n[3], q.d, w.n[2], through(q.h2));
+            back(w.W[1], w.n[2], q.h2, w.n[1], through(q.h1));
+            back(w.W[0], w.n[1], q.h1, w.n[0], [&](int k, float z) { g_out[p * w.n[0] + k] = z * w.in_rstd[k]; });
             __syncthreads();
         }
     }
@@ -186,7 +204,11 @@ hipError_t launch_mlp_vjp(hipStream_t s, const MlpArgs& a, const float* B, const
                           float* g_out) {
     if (n_pts <= 0) return hipSuccess;
     if (a.precision != 0 || !a.W1T || !a.W2T || !a.W3T || !mlp_vjp_supported(a)) return hipErrorInvalidValue;
-    const int nb = mlp_blocks(n_pts), nt = mlp_point_tiles(a, n_pts, nb);
+    const int nb = mlp_blocks(n_pts, mlp_rows_small(a) ? 2 : 1), nt = mlp_point_tiles(a, n_pts, nb);
+    if (mlp_rows_small(a)) {
+        if (nt == 4) return launch_vjp_n<4, 1, kRowSmall>(s, a, B, v, n_pts, g_out, nb);
+        return launch_vjp_n<2, 1, kRowSmall>(s, a, B, v, n_pts, g_out, nb);
+    }
     if (mlp_rows_wide(a)) {
         if (nt == 4) return launch_vjp_n<4, 3, kRowWide>(s, a, B, v, n_pts, g_out, nb);
         return launch_vjp_n<2, 3, kRowWide>(s, a, B, v, n_pts, g_out, nb);
