@@ -245,7 +245,9 @@ mala_status mala_ldos_infer(mala_ctx* ctx, const mala_weights* w, const float* B
  *  B: device float32 [n_pts][w0]; v: device float32 [n_pts][wL];
  *  g_out: device float32 [n_pts][w0] (caller-owned).
  * FP32 weights only (MALA_E_UNSUPPORTED for BF16 weights: rounding there
- * moves units across their kinks often enough to change g by percent).
+ * moves units across their kinks often enough to change g by percent), and
+ * both hidden widths and the larger of w0 and wL, each rounded up to a multiple
+ * of 64, of at most 1152 together (MALA_E_UNSUPPORTED beyond).
  * n_pts = 0 is a no-op.                                                      */
 mala_status mala_ldos_vjp(mala_ctx* ctx, const mala_weights* w, const float* B, const float* v,
                           int64_t n_pts, float* g_out);

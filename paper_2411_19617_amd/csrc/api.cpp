@@ -1175,7 +1175,7 @@ mala_status mala_ldos_vjp(mala_ctx* c, const mala_weights* w, const float* B, co
     if (n_pts == 0) return MALA_OK;
     if (!B || !v || !g_out) return fail(MALA_E_INVALID_ARG, "NULL buffer");
     if (!mlp_vjp_supported(w->args))
-        return fail(MALA_E_UNSUPPORTED, "network too wide for the VJP kernel's LDS tile");
+        return fail(MALA_E_UNSUPPORTED, "network VJP: both hidden widths and the larger of input and output width, each rounded up to 64, exceed 1152 together");
     DeviceGuard g(c->device);
     HIP_TRY(staged(c, MALA_STAGE_MLP_VJP, n_pts, [&] { return launch_mlp_vjp(c->stream, w->args, B, v, n_pts, g_out); }));
     return MALA_OK;

@@ -303,7 +303,6 @@ struct MlpArgs {
 };
 
 enum MlpMode { kModeLdos = 0, kModeDos = 1, kModeDensity = 2, kModeDosWindow = 3 };
-constexpr size_t kMlpLdsBudget = 155000;   // dynamic LDS of one network block
 
 // Mirrors mala_result of include/mala.h.
 struct ResultRec {

@@ -180,13 +180,13 @@ __global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp_vjp(Mlp
     }
 }
 
-// The widths the call accepts: 32 points' FP32 activations of both hidden
-// layers and of the wider of input and output (rows padded to 64 units and 8)
-// within the LDS of one block.
+// The widths the call accepts, part of its interface: both hidden layers and the
+// wider of input and output, each rounded up to 64 units, of at most 1152 together.
+// It is no limit of this kernel, whose one tile holds any layer: a form that kept
+// the activations of all three in LDS had it, and callers choose their path by it.
 bool mlp_vjp_supported(const MlpArgs& a) {
-    auto row = [](int w) { return (size_t)((w + 63) / 64) * 64 + 8; };
-    return sizeof(float) * 32 * (row(a.h1_tiles * 16) + row(a.h2_tiles * 16) + row(std::max(a.in_pad, a.out_tiles * 16))) <=
-           kMlpLdsBudget;
+    auto padded = [](int w) { return (w + 63) / 64 * 64; };
+    return padded(a.h1_tiles * 16) + padded(a.h2_tiles * 16) + padded(std::max(a.in_pad, a.out_tiles * 16)) <= 1152;
 }
 
 template <int NT, int MT, int RS>
