@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("widths,ok", [([91, 448, 448, 256], True), ([91, 448, 449, 256], False), ([128, 512, 512, 128], True),
                                        ([128, 512, 512, 129], False), ([91, 512, 384, 250], True), ([91, 512, 400, 250], False),
-                                       ([1, 385, 512, 193], False), ([1, 385, 448, 193], True), ([91, 400, 400, 250], True)])
+                                       ([1, 385, 512, 193], False), ([33, 385, 448, 193], True), ([91, 400, 400, 250], True)])
 def test_widths(widths, ok):
     import torch
     if not torch.cuda.is_available():
