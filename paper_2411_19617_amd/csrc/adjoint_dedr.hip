@@ -221,6 +221,8 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_dedr(BinState bins, int Nx
     constexpr float kpi = 3.14159265358979323846f;
     constexpr float kRfac0 = 0.99363f;
     const float kth = kRfac0 * kpi / rcf, kcut = kpi / rcf;     // per unit distance, formed once
+    // a loop per wave with the same count of barriers in each (nmax is the same in every
+    // wave; the hardware counts the waves that have reached one, wherever in the code)
     static_for<0, NG>([&](auto gc) {
         constexpr int G = decltype(gc)::value;
         if (wave != G) return;

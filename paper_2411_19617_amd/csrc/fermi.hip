@@ -273,7 +273,9 @@ __global__ __launch_bounds__(kFermiThreads) void k_fermi(const double* __restric
     if (e == 0 && (group == 1 || group == 2)) s_ends[group - 1] = n;
     __syncthreads();
     const double nlo = s_ends[0], nhi = s_ends[1];
-    if (group > 0) return;                     // whole waves: the rest is the first group's
+    // the rest is the first group's: whole waves end here, and a barrier counts only
+    // the waves that have not
+    if (group > 0) return;
     const bool ok = nlo <= n_target && n_target <= nhi;
     if (!ok) {
         if (e == 0) {
@@ -382,8 +384,7 @@ __global__ __launch_bounds__(kFermiThreads) void k_fermi(const double* __restric
 
 // n(p) = prefix(p) + sum over the stored window of w_e d_e(p), when the
 // window covers E_F +- 40 kT (outside it the Fermi weights equal the full
-// trapezoid weights or vanish to within e^-40).
-// n(p) = prefix(p) + sum over the window of w_e d_e(p).  A wave takes 64
+// trapezoid weights or vanish to within e^-40).  A wave takes 64
 // points at a time: their window rows are 64 W contiguous floats, read with
 // consecutive lanes into LDS (row stride W: coalesced, where one lane per row
 // strides W floats between the lanes of every load) and then summed by the

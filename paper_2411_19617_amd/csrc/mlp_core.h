@@ -25,7 +25,7 @@
 // spread over 14 decades, and 3.8e-7 and 2.6e-7 with two halves of a network 1e8
 // apart.  The sum of its own for the small products costs 1 to 2%.
 // Time at 91-400-400-250: 4.12 -> 1.46 ms per 729,000 points with the LDOS stored,
-// 14.6 -> 4.9 us per 1,000 points for the vector-Jacobian product.  What bounds it
+// 14.6 -> 5.0 to 5.3 us per 1,000 points for the vector-Jacobian product.  What bounds it
 // now: the products are 0.65 ms of the 1.46 at the 1.9 GHz the card holds under
 // them, the epilogues (activation, scales, LDS writes) as much, and the weights
 // from L2 most of the rest.
@@ -85,9 +85,12 @@ constexpr int waves_per_simd(int MT) { return MT == 1 ? 4 : 2; }
 
 // The activation tile of a block, [plane][point][unit], for NT point tiles and
 // layers of at most RS units.  The row stride RS (16-bit elements) is an odd
-// multiple of 8 dwords, which makes the 128-bit operand reads (16 points x 4
-// groups of 8 units) free of bank conflicts, and a constant, so that every
-// operand and output address is one register plus an immediate.
+// multiple of 8 dwords, chosen for the 128-bit operand reads (16 points x 4
+// groups of 8 units), which then spread over all banks, and a constant, so that
+// every operand and output address is one register plus an immediate.  The 8-byte
+// writes of a layer's output pay for it (points j and j + 8 share banks): 0.70 of
+// the conflicts that the counters show for FP32 weights (0.35 of the LDS cycles,
+// LDOS stored), the rows of the stored LDOS another 0.08.
 template <int P, int NT, int RS>
 struct ActTile {
     static constexpr int kPlane = 16 * NT * RS;

@@ -195,6 +195,9 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
         }
     };
     if (n_iter > 0) form(0);
+    // a loop per wave, each with code of its own: its barriers are met by every wave
+    // because n_iter is the same in all of them (the hardware counts the waves that
+    // have reached a barrier, wherever in the code)
     static_for<0, NG>([&](auto gc) {
         constexpr int G = decltype(gc)::value;
         if (wave != G) return;
