@@ -218,9 +218,7 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_dedr(BinState bins, int Nx
     const int nmax = wave_max_int(nn);                // the same in every wave
 
     const float2* yt = y_in + tile * NH * kTile + lane;
-    constexpr float kpi = 3.14159265358979323846f;
-    constexpr float kRfac0 = 0.99363f;
-    const float kth = kRfac0 * kpi / rcf, kcut = kpi / rcf;     // per unit distance, formed once
+    const PhaseFactors phase(rcut);
     // a loop per wave with the same count of barriers in each (nmax is the same in every
     // wave; the hardware counts the waves that have reached one, wherever in the code)
     static_for<0, NG>([&](auto gc) {
@@ -243,7 +241,7 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_dedr(BinState bins, int Nx
             const float r = on ? r2 * inv : 1.f;
             const float n[3] = {dx * inv, dy * inv, dz * inv};
             float sn, cs;
-            sincosf(kth * r, &sn, &cs);
+            sincosf(phase.angle(r), &sn, &cs);
             geo[G][lane] = on ? make_float4(cs, -n[2] * sn, -n[1] * sn, -n[0] * sn) : make_float4(1.f, 0.f, 0.f, 0.f);
             __syncthreads();
             const int cnt = min(NG, nmax - s0);
@@ -264,12 +262,12 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_dedr(BinState bins, int Nx
 #pragma unroll
                     for (int w = 1; w < NG; ++w) v[k] += part[G][w][k][lane];
                 }
-                const float x = kcut * r;
-                const float fc = 0.5f * (cosf(x) + 1.f), dfc = -0.5f * kcut * sinf(x);
+                const float x = phase.cutoff(r);
+                const float fc = 0.5f * (cosf(x) + 1.f), dfc = -0.5f * phase.cutoff(sinf(x));
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    // theta = kth r, n_i' = (delta_id - n_i n_d) / r
-                    const float dth = kth * n[d];
+                    // theta' = n_d theta0 / r, n_i' = (delta_id - n_i n_d) / r
+                    const float dth = phase.angle(n[d]);
                     const float dnx = ((d == 0 ? 1.f : 0.f) - n[0] * n[d]) * inv;
                     const float dny = ((d == 1 ? 1.f : 0.f) - n[1] * n[d]) * inv;
                     const float dnz = ((d == 2 ? 1.f : 0.f) - n[2] * n[d]) * inv;

@@ -29,7 +29,7 @@ constexpr int kIntegrateMaxParts = 512;
 // fixed scratch of mala_integrate_noalloc: the partial rows and the weights
 constexpr int kNoallocScratchDoubles = kIntegrateMaxParts * kMlpMaxOut + kMlpMaxOut;
 constexpr double kBoltzmannEv = 8.617333262e-5;
-constexpr float kRfac0 = 0.99363f;
+constexpr double kRfac0 = 0.99363;
 
 // Device-side error bits (OR-ed into a flag word in device memory).
 constexpr int kErrCand = 1;          // tile candidate list overflow

@@ -25,6 +25,24 @@ __host__ __device__ constexpr double ce_fact(int n) {
     return f;
 }
 
+// Angle theta0 and cutoff phase of a neighbour at distance r, from their factors per
+// unit distance, formed once (a quotient per neighbour is a full-precision division, a
+// dozen instructions), each in two floats: the rounding of one would turn every
+// neighbour the same way and add up where the others average out (descriptors
+// 3.1e-7 -> 2.8e-7 against 64 bits).
+struct PhaseFactors {
+    float th, th_lo, cut, cut_lo;
+    __device__ __forceinline__ explicit PhaseFactors(double rcut) {
+        const double c = 3.14159265358979323846 / rcut, t = kRfac0 * c;
+        th = (float)t;
+        th_lo = (float)(t - th);
+        cut = (float)c;
+        cut_lo = (float)(c - cut);
+    }
+    __device__ __forceinline__ float angle(float r) const { return fmaf(th, r, th_lo * r); }
+    __device__ __forceinline__ float cutoff(float r) const { return fmaf(cut, r, cut_lo * r); }
+};
+
 // x * (-1)^k for wave-uniform x and k, as a sign-bit flip on the scalar unit
 __device__ __forceinline__ float flip_odd(float x, int k) {
     return __int_as_float(__float_as_int(x) ^ (int)((unsigned)(k & 1) << 31));

@@ -162,10 +162,7 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
     const int n_iter = wave_max_int(my_n);            // the same in every wave
 
     // ---- expansion coefficients, this wave's group of sums
-    const float kpi = 3.14159265358979f;
-    // angle and cutoff phase per unit distance, formed once: a quotient
-    // per neighbour is a full-precision division (a dozen instructions)
-    const float kth = kRfac0 * kpi / rcf, kcut = kpi / rcf;
+    const PhaseFactors phase(rcut);
     auto form = [&](int s0) {                         // this wave's share of the chunk from s0
 #pragma unroll
         for (int q = 0; q < kUiChunk / NG; ++q) {
@@ -183,12 +180,12 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
                 const float inv = r2 > kMinR2 ? __builtin_amdgcn_rsqf(r2) : 0.f;
                 const float r = r2 * inv;
                 float sn, cs;
-                sincosf(kth * r, &sn, &cs);
+                sincosf(phase.angle(r), &sn, &cs);
                 ar = cs;
                 ai = -dz * inv * sn;
                 br = -dy * inv * sn;
                 bi = -dx * inv * sn;
-                fc = 0.5f * (cosf(kcut * r) + 1.f);
+                fc = 0.5f * (cosf(phase.cutoff(r)) + 1.f);
             }
             geo_ab[(s0 / kUiChunk) & 1][i][lane] = make_float4(ar, ai, br, bi);
             geo_fc[(s0 / kUiChunk) & 1][i][lane] = fc;
