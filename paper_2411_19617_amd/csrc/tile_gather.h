@@ -208,6 +208,13 @@ __device__ __forceinline__ int gather_candidates(const BinState& bins, const Til
 // denormal inputs, and the terms left out are below FP32 resolution.
 constexpr float kMinR2 = 1e-30f;
 
+// 1/r from r^2 > kMinR2: the hardware's reciprocal square root (about 1 ulp, off to one
+// side on the whole, which neighbours share) and a Newton step.
+__device__ __forceinline__ float inverse_distance(float r2) {
+    const float y = __builtin_amdgcn_rsqf(r2), h = r2 * y;
+    return fmaf(fmaf(-h, y, 1.f), 0.5f * y, y);
+}
+
 // A lane's point relative to the two origins its candidates are stored
 // against: candidate c is compared with at(c).
 struct PointFrame {

@@ -175,9 +175,7 @@ __global__ __launch_bounds__(64 * kUiWaves, 2) void k_ui(BinState bins, int Nx, 
                 const float3 o = frame.at(c);
                 const float dx = v.x - o.x, dy = v.y - o.y, dz = v.z - o.z;
                 const float r2 = dx * dx + dy * dy + dz * dz;
-                // 1/r and r from one hardware reciprocal square root (about
-                // 1 ulp; an atom on the point gives r = 0)
-                const float inv = r2 > kMinR2 ? __builtin_amdgcn_rsqf(r2) : 0.f;
+                const float inv = r2 > kMinR2 ? inverse_distance(r2) : 0.f;      // an atom on the point: r = 0
                 const float r = r2 * inv;
                 float sn, cs;
                 sincosf(phase.angle(r), &sn, &cs);
