@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp(MlpArgs
                     const int t = plain_thread();
                     const MlpPlain& w = *a.plain;
                     plain_hidden(w, B + p * row_stride * w.n[0], q, t);
-                    plain_layer(w.W[2], w.b[2], w.n[3], w.n[2], q.h2, t, [&](int e, float y) {
+                    plain_layer(w, 2, q.z2, t, [&](int e, float y) {
                         if (w.out_act) y = leaky<false>(y, w.slope);
                         o.ldos[p * w.n[3] + e] = (float)((double)w.out_scale[e] * (double)y + (double)w.out_shift[e]);
                     });

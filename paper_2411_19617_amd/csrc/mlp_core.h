@@ -503,15 +503,17 @@ __device__ __forceinline__ unsigned long long infinite_points(const unsigned (*s
     return __ballot(inf && lane < rows);
 }
 
-// Units of one layer of one point from LDS: f(unit, W in + b).  t: the thread, in a
-// register of its own, or the addresses formed from it stay in registers all along.
+// Units of layer l of one point: f(unit, W sigma(in) + b), in: the layer before in LDS
+// (z, or x for l = 0).  t: the thread, in a register of its own, or the addresses
+// formed from it stay in registers all along.
 template <typename F>
-__device__ __forceinline__ void plain_layer(const float* __restrict__ W, const float* __restrict__ b, int n_out, int n_in,
-                                            const float* in, int t, F&& f) {
+__device__ __forceinline__ void plain_layer(const MlpPlain& w, int l, const float* in, int t, F&& f) {
+    const int n_in = w.n[l], n_out = w.n[l + 1];
+    const float* W = w.W[l];
     for (int u = t; u < n_out; u += kWaves * 64) {
-        float z = b[u];
+        float z = w.b[l][u];
 #pragma clang loop unroll(disable)
-        for (int k = 0; k < n_in; ++k) z = fmaf(W[(unsigned)(u * n_in + k)], in[k], z);
+        for (int k = 0; k < n_in; ++k) z = fmaf(W[(unsigned)(u * n_in + k)], l ? leaky<false>(in[k], w.slope) : in[k], z);
         f(u, z);
     }
 }
@@ -521,18 +523,17 @@ __device__ __forceinline__ int plain_thread() {
     return t;
 }
 
-// Inputs and hidden activations of one point in plain FP32 (LDS of PlainPoint;
-// a barrier has passed since the last write).
+// Inputs and hidden z of one point in plain FP32 (LDS of PlainPoint; a barrier has
+// passed since the last write).
 struct PlainPoint {
-    float x[kMlpMaxIn], h1[kMlpMaxHidden], h2[kMlpMaxHidden], d[kMlpMaxOut];
+    float x[kMlpMaxIn], z1[kMlpMaxHidden], z2[kMlpMaxHidden], d[kMlpMaxOut];
 };
-__device__ __forceinline__ void plain_hidden(const MlpPlain& w, const float* __restrict__ row, PlainPoint& q,
-                                             int t) {
+__device__ __forceinline__ void plain_hidden(const MlpPlain& w, const float* __restrict__ row, PlainPoint& q, int t) {
     for (int k = t; k < w.n[0]; k += kWaves * 64) q.x[k] = (row[k] - w.in_mean[k]) * w.in_rstd[k];
     __syncthreads();
-    plain_layer(w.W[0], w.b[0], w.n[1], w.n[0], q.x, t, [&](int u, float z) { q.h1[u] = leaky<false>(z, w.slope); });
+    plain_layer(w, 0, q.x, t, [&](int u, float z) { q.z1[u] = z; });
     __syncthreads();
-    plain_layer(w.W[1], w.b[1], w.n[2], w.n[1], q.h1, t, [&](int u, float z) { q.h2[u] = leaky<false>(z, w.slope); });
+    plain_layer(w, 1, q.z1, t, [&](int u, float z) { q.z2[u] = z; });
     __syncthreads();
 }
 

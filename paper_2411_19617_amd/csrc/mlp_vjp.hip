@@ -74,8 +74,9 @@ __global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp_vjp(Mlp
                 unsigned bits = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    z[r] = leaky<false>(fmaf(z[r], cn, b[r]), slope);
-                    bits |= z[r] > 0.f ? 1u << r : 0u;
+                    const float x = fmaf(z[r], cn, b[r]);
+                    bits |= x > 0.f ? 1u << r : 0u;
+                    z[r] = leaky<false>(x, slope);
                 }
                 mask[l][slot] |= bits << (slot < MT ? 4 * n : 0);
             });
@@ -158,10 +159,10 @@ __global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp_vjp(Mlp
             const int t = plain_thread();
             const MlpPlain& w = *a.plain;
             plain_hidden(w, B + p * w.n[0], q, t);
-            plain_layer(w.W[2], w.b[2], w.n[3], w.n[2], q.h2, t, [&](int e, float y) {
+            plain_layer(w, 2, q.z2, t, [&](int e, float y) {
                 q.d[e] = v[p * w.n[3] + e] * w.out_scale[e] * (w.out_act && !(y > 0.f) ? w.slope : 1.f);
             });
-            // delta over the units of `h` in place, from the delta of the layer W leads to
+            // delta over the units of `z` in place, from the delta of the layer W leads to
             auto back = [&](const float* W, int fout, const float* delta, int n, auto&& f) {
                 __syncthreads();
                 for (int u = t; u < n; u += kWaves * 64) {
@@ -171,10 +172,10 @@ __global__ __launch_bounds__(kWaves * 64, waves_per_simd(MT)) void k_mlp_vjp(Mlp
                     f(u, z);
                 }
             };
-            auto through = [&](float* h) { return [h, slope = w.slope](int u, float z) { h[u] = z * (h[u] > 0.f ? 1.f : slope); }; };
-            back(w.W[2], w.n[3], q.d, w.n[2], through(q.h2));
-            back(w.W[1], w.n[2], q.h2, w.n[1], through(q.h1));
-            back(w.W[0], w.n[1], q.h1, w.n[0], [&](int k, float z) { g_out[p * w.n[0] + k] = z * w.in_rstd[k]; });
+            auto through = [&](float* z) { return [z, slope = w.slope](int u, float d) { z[u] = d * (z[u] > 0.f ? 1.f : slope); }; };
+            back(w.W[2], w.n[3], q.d, w.n[2], through(q.z2));
+            back(w.W[1], w.n[2], q.z2, w.n[1], through(q.z1));
+            back(w.W[0], w.n[1], q.z1, w.n[0], [&](int k, float z) { g_out[p * w.n[0] + k] = z * w.in_rstd[k]; });
             __syncthreads();
         }
     }
