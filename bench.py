@@ -811,7 +811,10 @@ def measure(ctx, mala, torch, snap, net, precision, steps, warmup, Bc, fl):
         "dtype": "f32" if precision == "fp32" else "bf16",
         "config": {"workload": snap.name, "n_points": snap.n_points, "n_atoms": snap.n_atoms,
                    "twojmax": snap.twojmax, "network": "-".join(map(str, net["widths"])),
-                   "network_precision": precision, "reductions": "f64", "T_K": snap.T,
+                   "network_precision": precision,
+                   "network_products": "FP32 operands as two FP16 planes, three 16-bit products, FP32 sums"
+                                       if precision == "fp32" else "BF16 operands, FP32 sums",
+                   "reductions": "f64", "T_K": snap.T,
                    "n_electrons": snap.n_electrons},
         "latency_ms": {"p50": float(np.percentile(lat, 50)), "p99": float(np.percentile(lat, 99)),
                        "kind": "single snapshot, back-to-back"},
